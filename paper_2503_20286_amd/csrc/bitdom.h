@@ -403,6 +403,7 @@ __device__ __forceinline__ void fwd_level_group(const uint32_t *__restrict__ tab
                                    : (int32_t)vld(&tabs[(size_t)bs * TS]);
         if (first >= last_run) break;
         const int32_t nb = min(cb, nblk - bs);
+        if constexpr (kLds) lds_wait();
         __syncthreads();  // every wave is done with the previous chunk
         if constexpr (kLds) {
             // one (table, objective) per wave at a time; objective 0 also
@@ -410,6 +411,7 @@ __device__ __forceinline__ void fwd_level_group(const uint32_t *__restrict__ tab
             for (int job = w; job < nb * M; job += kFwdThreads / kWave)
                 build_block_at<M, true>(fk, nf, lt + (job / M) * TS, bs + job / M,
                                         inv + w * kBlk, job % M, M);
+            lds_wait();
         } else {
             stage_tables<M>(lt, tabs, bs, nb);
         }

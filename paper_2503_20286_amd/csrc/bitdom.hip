@@ -106,6 +106,7 @@ __device__ __forceinline__ void fwd_all_item(const uint32_t *__restrict__ tabs, 
         const int32_t b0 = c * CB;
         if (b0 * kBlk >= last_run) break;  // later chunks start later still
         const int32_t nb = min(CB, nblk - b0);
+        if constexpr (kOut) lds_wait();
         __syncthreads();  // the previous chunk is consumed
         if constexpr (kOut)
             if (pb0 >= 0) flush_out_counts(oc, pb0, pnb, dom_out);
@@ -229,6 +230,7 @@ __device__ __forceinline__ void fwd_all_wide_item(
         const int32_t b0 = c * CB;
         if (b0 * kWBlk >= last_run) break;  // later chunks start later still
         const int32_t nb = min(CB, nblk - b0);
+        if constexpr (kOut) lds_wait();
         __syncthreads();  // the previous chunk is consumed
         if constexpr (kOut) {
             if (pb0 >= 0) {
@@ -338,6 +340,7 @@ __global__ __launch_bounds__(kFwdThreads) void k_fwd_level(
         fwd_level_group<M, kLevelTJ, kLds>(tabs, ig * ng * cb, cb, ng, nblk, uk, urun, nu, ucnt,
                                            jg, lt, fk, nf, inv);
         if (threadIdx.x == 0) s_item = (int32_t)(gridDim.x + atomicAdd(&work[level], 1u));
+        lds_wait();
         __syncthreads();  // every wave is done with lt
         item = s_item;
         __syncthreads();

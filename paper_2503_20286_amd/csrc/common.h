@@ -80,6 +80,13 @@ struct GridBar {
 
 struct Ws;  // workspace views, defined in the runtime
 
+// Waits for the wave's own LDS operations, before a __syncthreads() that a
+// loop reaches again after LDS writes or atomics: the compiler (ROCm 7.2)
+// leaves that wait out on the way back to a loop's head, and another wave then
+// reads or clears a counter whose increment is still on its way (out-degrees
+// at N = 3000, M = 11 came out one wave's 128 short).
+__device__ __forceinline__ void lds_wait() { __builtin_amdgcn_s_waitcnt(0xc07f); }
+
 // Dwords of one 64-member block-bitset table of an M-objective point list
 // (header and positions, then 195 dwords per objective: keys and prefix
 // masks, laid out in bitdom.h), rounded to whole 16-byte vectors.
