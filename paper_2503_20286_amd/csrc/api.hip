@@ -15,6 +15,9 @@
 
 #include "engine.h"
 #include "kernels.h"
+#include "pairs.h"
+#include "prims.h"
+#include "stage_math.h"
 
 using namespace nsga3;
 
@@ -67,6 +70,7 @@ struct nsga3_ctx {
     bool wide;                      // LaunchCfg::wide
     bool wide_levels;               // LaunchCfg::wide_levels
     bool engine_wide;               // batched counts over 128-member tables
+    bool pairs;                     // spatially ordered path where its workspace fits
     volatile int32_t *last_fronts;  // pinned: front count, then level sizes, of the latest call
     std::vector<hipEvent_t> ev_pool;   // NSGA3_NUM_PHASES + 1 events per recorded call
     size_t ev_used;
@@ -87,6 +91,9 @@ struct Layout {
     size_t lb_stride;
     size_t rank, niche, dist64, rhat64, rhat32, rhat16, p_asf, p_idx, p_nad;
     size_t rho, bcount, bstart, bcursor, gstart, bd, bi, selflag, sc, bar;
+    // spatially ordered path (layout_pairs)
+    size_t spl, cell, code, slot, trec, box, nz, idx, mask, low, U, pos, wit, sync, runs2, rune2, din2, list;
+    size_t zero, zero_words;   // counters the path clears first
     size_t total;
 };
 
@@ -96,8 +103,30 @@ size_t bump(size_t &cur, size_t bytes) {
     return at;
 }
 
+// The arrays of the stages after the sort.
+void select_layout(Layout &L, size_t &c, int64_t N, int M, int H) {
+    const size_t n = (size_t)N;
+    const int nparts = normalize_partial_blocks(N);
+    L.rank = bump(c, 4 * n);
+    L.niche = bump(c, 4 * n);
+    L.dist64 = bump(c, 8 * n);
+    L.rhat64 = bump(c, 8 * (size_t)H * M);
+    L.rhat32 = bump(c, 4 * (size_t)H * M);
+    L.rhat16 = bump(c, 2 * (size_t)((H + 31) / 32 * 32) * (M <= 8 ? 8 : 16));
+    L.p_asf = bump(c, 8 * (size_t)nparts * M);
+    L.p_idx = bump(c, 4 * (size_t)nparts * M);
+    L.p_nad = bump(c, 8 * (size_t)nparts * M);
+    L.bstart = bump(c, 4 * ((size_t)H + 1));
+    L.bcursor = bump(c, 4 * (size_t)H);
+    L.gstart = bump(c, 4 * ((size_t)H + 1));
+    L.bd = bump(c, 8 * n);
+    L.bi = bump(c, 4 * n);
+    L.selflag = bump(c, n);
+    L.sc = bump(c, sizeof(DevScalars));
+}
+
 Layout layout_for(int64_t N, int M, int H, int max_grid) {
-    Layout L;
+    Layout L = {};
     size_t c = 0;
     const size_t n = (size_t)N;
     const size_t MP = (size_t)rec_stride(M);
@@ -106,7 +135,6 @@ Layout layout_for(int64_t N, int M, int H, int max_grid) {
     if (ct > temp) temp = ct;
     const size_t ot = oneshot_temp_bytes(N);
     if (ot > temp) temp = ot;
-    const int nparts = normalize_partial_blocks(N);
     L.skey = bump(c, 8 * n);
     L.skey_alt = bump(c, 8 * n);
     L.sval = bump(c, 4 * n);
@@ -134,25 +162,59 @@ Layout layout_for(int64_t N, int M, int H, int max_grid) {
     L.lb_stride = split_state_entries(N);
     L.lbstate = bump(c, 8 * 2 * L.lb_stride);
     L.blkcnt = bump(c, 8 * (size_t)max_grid);
-    L.rank = bump(c, 4 * n);
-    L.niche = bump(c, 4 * n);
-    L.dist64 = bump(c, 8 * n);
-    L.rhat64 = bump(c, 8 * (size_t)H * M);
-    L.rhat32 = bump(c, 4 * (size_t)H * M);
-    L.rhat16 = bump(c, 2 * (size_t)((H + 31) / 32 * 32) * (M <= 8 ? 8 : 16));
-    L.p_asf = bump(c, 8 * (size_t)nparts * M);
-    L.p_idx = bump(c, 4 * (size_t)nparts * M);
-    L.p_nad = bump(c, 8 * (size_t)nparts * M);
     L.rho = bump(c, 4 * (size_t)H);
     L.bcount = bump(c, 4 * (size_t)H);
-    L.bstart = bump(c, 4 * ((size_t)H + 1));
-    L.bcursor = bump(c, 4 * (size_t)H);
-    L.gstart = bump(c, 4 * ((size_t)H + 1));
-    L.bd = bump(c, 8 * n);
-    L.bi = bump(c, 4 * n);
-    L.selflag = bump(c, n);
-    L.sc = bump(c, sizeof(DevScalars));
     L.bar = bump(c, sizeof(GridBar));
+    select_layout(L, c, N, M, H);
+    L.total = c;
+    return L;
+}
+
+// Workspace of the spatially ordered path (pairs.h).
+Layout layout_pairs(int64_t N, int M, int H) {
+    Layout L = {};
+    size_t c = 0;
+    const size_t n = (size_t)N;
+    const size_t MP = (size_t)rec_stride(M);
+    const size_t nB = (n + kWBlk - 1) / kWBlk, nBp = (nB + 63) / 64 * 64;
+    uint8_t bits[16];
+    int T = 0;
+    pair_cell_bits(N, M, bits, &T);
+    L.zero = c;
+    L.cell = bump(c, 4 * (((size_t)1 << T) + 1));
+    L.dom_in_s = bump(c, 4 * n);
+    L.dom_out_s = bump(c, 4 * n);
+    L.nz = bump(c, nB * nBp / 8);
+    L.sync = bump(c, sizeof(RankSync));
+    L.rho = bump(c, 4 * (size_t)H);
+    L.bcount = bump(c, 4 * (size_t)H);
+    L.zero_words = (c - L.zero) / 4;
+    size_t temp = compact_temp_bytes(N);
+    const size_t ot = oneshot_temp_bytes(N);
+    L.temp = bump(c, ot > temp ? ot : temp);
+    L.spl = bump(c, 4 * 64 * (size_t)M);
+    L.code = bump(c, 4 * n);
+    L.slot = bump(c, 4 * n);
+    L.trec = bump(c, 4 * n * MP);
+    L.recs = bump(c, 4 * n * MP);
+    L.sval = bump(c, 4 * n);
+    L.runstart = bump(c, 4 * n);
+    L.runend = bump(c, 4 * n);
+    const size_t n2 = pair_phases(N) > 0 ? n : 0;
+    L.runs2 = bump(c, 4 * n2);
+    L.rune2 = bump(c, 4 * n2);
+    L.din2 = bump(c, 4 * n2);
+    const size_t tgs = (nB + kPairWaves - 1) / kPairWaves;
+    L.list = bump(c, n2 ? 16 * tgs * (nB + kListItem) : 0);
+    L.tabs_all = bump(c, 4 * nB * (size_t)wblk_stride(M));
+    L.box = bump(c, 4 * 2 * (size_t)M * nBp);
+    L.low = bump(c, 4 * 2 * 2 * nB * 16);
+    L.U = bump(c, 8 * 4 * nB);
+    L.pos = bump(c, 2 * kWBlk * nB);
+    L.wit = bump(c, 16 * kWBlk * nB);
+    L.idx = bump(c, 4 * nB * nBp);
+    select_layout(L, c, N, M, H);
+    L.mask = bump(c, 16 * (size_t)kWBlk * (mask_units(nB) + 1));
     L.total = c;
     return L;
 }
@@ -195,6 +257,22 @@ nsga3_status ensure_ws(nsga3_ctx *ctx, size_t need) {
     ctx->ws = p;
     ctx->ws_bytes = need;
     return NSGA3_OK;
+}
+
+// Workspace for one selection: the spatially ordered path's where it fits
+// (pairs = true), else the smaller one of the key-sum ordered path.
+nsga3_status ensure_select_ws(nsga3_ctx *ctx, int64_t N, int32_t M, int32_t H, bool *pairs) {
+    *pairs = false;
+    if (ctx->pairs && N <= kPairsMaxN) {
+        const nsga3_status st = ensure_ws(ctx, layout_pairs(N, M, H).total);
+        if (st == NSGA3_OK) {
+            *pairs = true;
+            return NSGA3_OK;
+        }
+        // no memory for it: do not try again on every call
+        if (!ctx->opt.max_workspace_bytes) ctx->pairs = false;
+    }
+    return ensure_ws(ctx, layout_for(N, M, H, kGridCap).total);
 }
 
 // Phase boundary marker: records the next pooled event when profiling.
@@ -278,6 +356,7 @@ struct EnqArgs {
     LaunchCfg cfg;
     int assoc;
     int niching = NSGA3_NICHING_EXACT;
+    bool pairs = false;               // spatially ordered path (ws sized by layout_pairs)
     nsga3_ctx *marks;                 // record phase events into this context, or null
     volatile int32_t *last_fronts;    // pinned slot for the front count and level sizes, or null
 };
@@ -336,8 +415,57 @@ SortViews sort_views(char *w, const Layout &L, const nsga3_problem &p, int32_t *
     return sv;
 }
 
+// The spatially ordered path's problem over the workspace w carved by L.
+PairInst pair_inst(char *w, const Layout &L, const nsga3_problem &p, int32_t *rank_o) {
+#define WS(T, f) reinterpret_cast<T *>(w + L.f)
+    PairInst I;
+    I.objs = p.objs;
+    I.N = (int32_t)p.N;
+    I.M = p.M;
+    I.K = p.K;
+    I.nB = (int32_t)((p.N + kWBlk - 1) / kWBlk);
+    I.nBpad = (I.nB + 63) / 64 * 64;
+    pair_cell_bits(p.N, p.M, I.bits, &I.T);
+    const int full = (2 * I.nB + kRankWaves - 1) / kRankWaves;
+    I.groups = full <= kRankSoloRounds ? 1 : full < kRankMaxGroups ? full : kRankMaxGroups;
+    I.spl = WS(uint32_t, spl);
+    I.cell = WS(uint32_t, cell);
+    I.code = WS(uint32_t, code);
+    I.slot = WS(uint32_t, slot);
+    I.trec = WS(uint32_t, trec);
+    I.recs = WS(uint32_t, recs);
+    I.sval = WS(uint32_t, sval);
+    I.runs = WS(int32_t, runstart);
+    I.rune = WS(int32_t, runend);
+    I.tabs = WS(uint32_t, tabs_all);
+    I.box = WS(uint32_t, box);
+    I.nz = WS(uint64_t, nz);
+    I.idx = WS(uint32_t, idx);
+    I.mask = WS(uint4, mask);
+    I.poolUnits = (uint32_t)(mask_units((size_t)I.nB) / kMaskPools);
+    I.din = WS(int32_t, dom_in_s);
+    I.dout = WS(int32_t, dom_out_s);
+    I.low = WS(uint32_t, low);
+    I.lowK = kRankLowBytes / (4 * I.nBpad) < I.M ? kRankLowBytes / (4 * I.nBpad) : I.M;
+    I.U = WS(uint64_t, U);
+    I.runs2 = WS(int32_t, runs2);
+    I.rune2 = WS(int32_t, rune2);
+    I.din2 = WS(int32_t, din2);
+    I.list = WS(uint4, list);
+    I.dynN = nullptr;
+    I.pos = WS(uint16_t, pos);
+    I.wit = WS(uint4, wit);
+    I.sync = WS(RankSync, sync);
+    I.sc = WS(DevScalars, sc);
+    I.rank = rank_o;
+    I.dom_in = p.dom_in;
+    I.dom_out = p.dom_out;
+#undef WS
+    return I;
+}
+
 // Enqueues one whole selection on `stream` using the workspace at a.ws (sized
-// by layout_for for the problem).  Allocates nothing; safe to capture.
+// by layout_pairs or layout_for for the problem).  Allocates nothing; safe to capture.
 hipError_t enqueue_select(const EnqArgs &a, const nsga3_problem &p, hipStream_t stream) {
     const float *objs = p.objs, *refs = p.refs;
     const int64_t N = p.N, K = p.K;
@@ -345,7 +473,7 @@ hipError_t enqueue_select(const EnqArgs &a, const nsga3_problem &p, hipStream_t 
     int32_t *selected = p.selected, *rank = p.rank, *niche = p.niche;
     float *dist = p.dist;
     nsga3_info *info = p.info;
-    const Layout L = layout_for(N, M, H, kGridCap);
+    const Layout L = a.pairs ? layout_pairs(N, M, H) : layout_for(N, M, H, kGridCap);
     char *w = a.ws;
 #define WS(T, f) reinterpret_cast<T *>(w + L.f)
     DevScalars *sc = WS(DevScalars, sc);
@@ -357,22 +485,32 @@ hipError_t enqueue_select(const EnqArgs &a, const nsga3_problem &p, hipStream_t 
     mk.fn = [](void *x) { static_cast<PhaseMarks *>(x)->mark(); };
     mk.arg = &marks;
     marks.mark();
-    int32_t *zero_p[] = {WS(int32_t, dom_in_s), WS(int32_t, dom_out_s), WS(int32_t, rho),
-                         WS(int32_t, bcount), WS(int32_t, bar), WS(int32_t, work),
-                         WS(int32_t, lbstate)};
-    const int64_t zero_n[] = {N, N, H, H, (int64_t)(sizeof(GridBar) / sizeof(int32_t)),
-                              kMaxHostLevels, (int64_t)(2 * L.lb_stride)};
-    hipError_t e = run_init(sc, zero_p, zero_n, 7, stream);
-    if (e == hipSuccess)
-        e = run_refs(refs, H, M, WS(double, rhat64), WS(float, rhat32), WS(uint16_t, rhat16), sc,
-                     stream);
-
-    SortViews sv = sort_views(w, L, p, rank_o, mk, a.cfg);
-    const LaunchCfg &cfg = a.cfg;
-    if (e == hipSuccess) e = run_sort_stage(sv, cfg, stream);
-    if (e == hipSuccess && a.last_fronts)
-        e = hipMemcpyAsync((void *)a.last_fronts, &sc->fb[0], sizeof(int32_t) * (1 + kProfLevels),
-                           hipMemcpyDeviceToHost, stream);
+    RefArgs refa;
+    refa.refs = refs;
+    refa.H = H;
+    refa.Hpad = (H + 31) / 32 * 32;
+    refa.KP = M <= 8 ? 8 : 16;
+    refa.rhat64 = WS(double, rhat64);
+    refa.rhat32 = WS(float, rhat32);
+    refa.rhat16 = WS(uint16_t, rhat16);
+    hipError_t e;
+    if (a.pairs) {
+        const PairInst pi = pair_inst(w, L, p, rank_o);
+        e = run_pairs(pi, refa, WS(uint32_t, zero), (int64_t)L.zero_words, mk, stream);
+    } else {
+        int32_t *zero_p[] = {WS(int32_t, dom_in_s), WS(int32_t, dom_out_s), WS(int32_t, rho),
+                             WS(int32_t, bcount), WS(int32_t, bar), WS(int32_t, work),
+                             WS(int32_t, lbstate)};
+        const int64_t zero_n[] = {N, N, H, H, (int64_t)(sizeof(GridBar) / sizeof(int32_t)),
+                                  kMaxHostLevels, (int64_t)(2 * L.lb_stride)};
+        e = run_init(sc, zero_p, zero_n, 7, stream);
+        if (e == hipSuccess) e = run_refs(refa, M, sc, stream);
+        SortViews sv = sort_views(w, L, p, rank_o, mk, a.cfg);
+        if (e == hipSuccess) e = run_sort_stage(sv, a.cfg, stream);
+        if (e == hipSuccess && a.last_fronts)
+            e = hipMemcpyAsync((void *)a.last_fronts, &sc->fb[0],
+                               sizeof(int32_t) * (1 + kProfLevels), hipMemcpyDeviceToHost, stream);
+    }
 
     SelectViews xv;
     xv.objs = objs;
@@ -593,6 +731,14 @@ nsga3_status nsga3_create(nsga3_ctx **out, int device, const nsga3_options *opt)
         const int v = atoi(e);
         if (v >= 1 && v <= 32) c->phase_a_bpc = v;
     }
+    // NSGA3_PAIRS=0: the key-sum ordered path for every size.  A switch that
+    // shapes that path selects it too.
+    c->pairs = !(getenv("NSGA3_PAIRS") && atoi(getenv("NSGA3_PAIRS")) == 0);
+    for (const char *e : {"NSGA3_PAIRWISE", "NSGA3_TAIL_BLOCK", "NSGA3_SEPARATE_OUT",
+                          "NSGA3_TAIL_WORK", "NSGA3_WIDE_TABLES", "NSGA3_WIDE_LEVELS",
+                          "NSGA3_LEVEL_LDS_BUILD", "NSGA3_HOST_LEVELS", "NSGA3_PEEL_BLOCKS_PER_CU",
+                          "NSGA3_PHASE_A_BLOCKS_PER_CU"})
+        if (getenv(e)) c->pairs = false;
     c->last_fronts = nullptr;
     {
         void *h = nullptr;
@@ -648,7 +794,11 @@ nsga3_status nsga3_phase_times(nsga3_ctx *ctx, double *ms, int64_t *calls) {
 nsga3_status nsga3_reserve(nsga3_ctx *ctx, int64_t N_max, int32_t M_max, int32_t H_max) {
     if (!ctx || !sizes_ok(N_max, M_max, H_max)) return NSGA3_E_INVALID;
     DeviceGuard g(ctx->device);
-    return ensure_ws(ctx, layout_for(N_max, M_max, H_max, kGridCap).total);
+    bool pairs;
+    nsga3_status st = ensure_select_ws(ctx, N_max < kPairsMaxN ? N_max : kPairsMaxN, M_max, H_max,
+                                       &pairs);
+    if (st == NSGA3_OK) st = ensure_ws(ctx, layout_for(N_max, M_max, H_max, kGridCap).total);
+    return st;
 }
 
 nsga3_status nsga3_select(nsga3_ctx *ctx, const float *objs, int64_t N, int32_t M,
@@ -658,11 +808,12 @@ nsga3_status nsga3_select(nsga3_ctx *ctx, const float *objs, int64_t N, int32_t 
     if (!ctx || !objs || !refs || !selected) return NSGA3_E_INVALID;
     if (!sizes_ok(N, M, H) || K < 1 || K > N) return NSGA3_E_INVALID;
     DeviceGuard g(ctx->device);
-    const Layout L = layout_for(N, M, H, kGridCap);
-    nsga3_status st = ensure_ws(ctx, L.total);
+    bool pairs = false;
+    const nsga3_status st = ensure_select_ws(ctx, N, M, H, &pairs);
     if (st != NSGA3_OK) return st;
     EnqArgs a;
     a.ws = (char *)ctx->ws;
+    a.pairs = pairs;
     a.cfg = ctx_cfg(ctx, M, N);
     a.assoc = (int)ctx->opt.assoc;
     a.niching = (int)ctx->opt.niching;
@@ -679,8 +830,8 @@ nsga3_status nsga3_select_noalloc(const float *objs, int64_t N, int32_t M, const
                                   nsga3_info *info, hipStream_t stream) {
     if (!objs || !refs || !selected) return NSGA3_E_INVALID;
     if (!sizes_ok(N, M, H) || K < 1 || K > N) return NSGA3_E_INVALID;
-    const Layout L = layout_for(N, M, H, kGridCap);
-    if (L.total > (size_t)NSGA3_NOALLOC_MAX_WORKSPACE) return NSGA3_E_NOMEM;
+    if (layout_for(N, M, H, kGridCap).total > (size_t)NSGA3_NOALLOC_MAX_WORKSPACE)
+        return NSGA3_E_NOMEM;
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) { (void)hipGetLastError(); return NSGA3_E_HIP; }
     if (dev < 0 || dev >= kNoallocMaxDevices) return NSGA3_E_UNSUPPORTED;
@@ -695,6 +846,8 @@ nsga3_status nsga3_select_noalloc(const float *objs, int64_t N, int32_t M, const
     a.cfg.host_levels = kDefaultHostLevels;
     a.cfg.bitsets = true;
     a.cfg.tail_block = true;          // no cooperative launch: capture-safe
+    a.pairs = N <= kPairsMaxN &&
+              layout_pairs(N, M, H).total <= (size_t)NSGA3_NOALLOC_MAX_WORKSPACE;
     a.assoc = NSGA3_ASSOC_FP32;
     a.marks = nullptr;
     a.last_fronts = nullptr;

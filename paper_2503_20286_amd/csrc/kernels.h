@@ -105,6 +105,17 @@ void run_bit_level(const SortViews &v, const uint32_t *fk, const uint32_t *uk, c
 size_t bit_tables_bytes(int64_t N, int M);    // all points: 64- or 128-member tables
 size_t level_tables_bytes(int64_t N, int M);  // a front's 64-member tables
 
+// ---- pairs.hip ------------------------------------------------------------
+// Ranks, degrees and the last front through the spatially ordered path; the
+// unit references and the call's scalars with it.  zero[0, nzero) are the
+// counters it clears first.
+struct PairInst;
+struct RefArgs;
+hipError_t run_pairs(const PairInst &I, const RefArgs &R, uint32_t *zero, int64_t nzero,
+                     const Marker &mark, hipStream_t s);
+// ---- ranks.hip ------------------------------------------------------------
+hipError_t run_ranks(const PairInst &I, int phases, hipStream_t s);
+
 // ---- peel.hip -------------------------------------------------------------
 hipError_t run_peel(const SortViews &v, const LaunchCfg &cfg, hipStream_t s);
 // Largest cooperative grid the peeling tail may use for this M (0 on error).
@@ -197,8 +208,8 @@ struct SelectViews {
 };
 
 int normalize_partial_blocks(int64_t N);
-hipError_t run_refs(const float *refs, int H, int M, double *rhat64, float *rhat32,
-                    uint16_t *rhat16, DevScalars *sc, hipStream_t s);
+struct RefArgs;
+hipError_t run_refs(const RefArgs &R, int M, DevScalars *sc, hipStream_t s);
 hipError_t run_select_stage(const SelectViews &v, hipStream_t s);
 hipError_t run_init(DevScalars *sc, int32_t *zero_i32[], const int64_t zero_n[], int nzero,
                     hipStream_t s);

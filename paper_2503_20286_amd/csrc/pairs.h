@@ -1,0 +1,158 @@
+// Spatially ordered dominance path (internal): the points are put in an order
+// in which 128 consecutive ones are neighbours in objective space, so that
+// most pairs of 128-point blocks are decided by their bounding boxes and only
+// the rest are probed (N = 200k, M = 5: 9 % of the pairs, in 3.2 of the 5
+// objectives; in the key-sum order half of all pairs, in every objective).
+// The dominator masks those probes find are kept, and the front of every
+// point is read off them level by level.
+//
+//   order   quantile cells of the objectives (bit-interleaved), points of a
+//           cell in lexicographic key order: identical rows are adjacent
+//   tables  128-member tables (bitdom_wide.h) and the box of every block
+//   pairs   the dominators of every point within every block that may hold
+//           some: degrees, and the masks kept for the ranks
+//   ranks   one persistent launch walks the levels of Eq. (8)-(9)
+//
+// The points of a large problem lie in few fronts, and a level costs as much
+// as its unranked points have stored masks.  There the first fronts are taken
+// off whole: a pass for the degrees gives front 0 (nobody dominates it), the
+// others are copied together in order, the next pass over them gives front 1,
+// and so on; masks are stored in the last pass only, for what is left.
+//
+// Whole selections, key-sum order -> this path: N = 200k, M = 5 2.65 -> 1.39 ms,
+// N = 100k, M = 10 0.95 -> 0.61 ms, N = 50k, M = 4 0.74 -> 0.53 ms, N = 20k, M = 3
+// 0.76 -> 0.45 ms, N = 10k, M = 2 4.2 -> 0.86 ms, N = 200 0.25 -> 0.12 ms.
+#pragma once
+
+#include "bitdom_wide.h"
+#include "common.h"
+
+namespace nsga3 {
+
+constexpr int64_t kPairsMaxN = 204800;   // largest problem of this path
+constexpr int kSplitterSample = 1024;   // keys sampled per objective for the cell splitters
+constexpr int kSplitterMaxBits = 6;     // cells per objective: at most 64
+constexpr int kCellMaxBits = 16;
+constexpr int kListItem = 8;            // blocks of a listed pair item
+constexpr int kListGroups = 1536;       // work-groups that take them (six a CU)
+constexpr int kPairWaves = 4;           // 128-point tiles of a pair work-group (one per wave)
+constexpr int kRankThreads = 1024;
+constexpr int kRankWaves = kRankThreads / kWave;
+constexpr int kRankSoloRounds = 4;      // 64-point groups a wave owns when one work-group ranks all
+constexpr int kRankMaxGroups = 64;      // work-groups of the persistent rank launch, at most
+constexpr int kMaxPhases = 8;           // fronts that may be taken off before it
+
+// LDS for the smallest keys of the blocks in the rank launches; a problem with
+// more blocks looks at fewer objectives.
+constexpr int kRankLowBytes = 32768;
+
+
+// Stored masks: units of 2 KiB (128 points x 128 members) handed out from
+// kMaskPools counters.  Up to kMaskFullUnits every pair of blocks has one;
+// beyond, a sixteenth of the pairs of all points (sphere- and simplex-shaped
+// populations keep 20 % of the pairs of the points that the fronts taken off
+// first leave, which are at most half of the points).  A pair without a unit
+// is probed again when a level needs it.
+constexpr int kMaskPools = 64;
+constexpr size_t kMaskFullUnits = 16384;
+constexpr uint32_t kUnitNone = 0xffffffffu;  // no unit: probe again
+inline size_t mask_units(size_t nB) {
+    const size_t full = nB * nB;
+    size_t u = full <= kMaskFullUnits ? full : (full / 16 > kMaskFullUnits ? full / 16 : kMaskFullUnits);
+    return (u + kMaskPools - 1) / kMaskPools * kMaskPools + 8 * kMaskPools;
+}
+
+// Counters of the rank launches.  flag: what
+// each work-group of the persistent launch has done, [63:32] levels, [31:0]
+// its points of the last one (alternating by level).
+struct alignas(128) RankWord {
+    uint64_t v;
+    uint64_t pad[15];
+};
+struct RankSync {
+    uint64_t flag[2][kRankMaxGroups];
+    uint32_t lv[kMaxPhases];     // points of the fronts taken off first
+    int32_t left[kMaxPhases];    // points left after each of them
+    uint32_t chunk[kMaxPhases][kPairsMaxN / kRankThreads];   // the same of a compaction chunk
+    uint32_t items[kMaxPhases + 1], next[kMaxPhases + 1];   // listed and taken items of a pass
+    RankWord pool[kMaskPools];   // units taken (v)
+};
+
+// One problem: sizes and workspace pointers.
+struct PairInst {
+    const float *objs;
+    int32_t N, M;
+    int64_t K;
+    const int32_t *dynN;      // number of points on the device (null: N)
+    int32_t nB;               // 128-point blocks
+    int32_t nBpad;            // nB rounded to 64
+    int32_t T;                // cell code bits
+    int32_t groups;           // work-groups of the persistent rank launch
+    uint8_t bits[16];         // cell code bits per objective
+    uint32_t *spl;            // [M * 64] splitters
+    uint32_t *cell;           // [2^T + 1] counts, then starts
+    uint32_t *code, *slot;    // [N] cell, arrival position in it
+    uint32_t *trec;           // [N * rec_stride] records in cell order (keys, point index);
+                              // afterwards the other buffer of the phases
+    uint32_t *recs;           // [N * rec_stride] records in final order (keys, position)
+    uint32_t *sval;           // [N] point index of a position
+    int32_t *runs, *rune;     // [N] positions [runs, rune) hold rows identical to this one
+    uint32_t *tabs;           // [nB] wide tables
+    uint32_t *box;            // [2][M][nBpad] smallest and largest key of a block
+    uint64_t *nz;             // [nB][nBpad / 64] blocks whose masks are stored (zeroed)
+    uint4 *list;              // items of a pass: kListItem x (block and the tiles that meet it,
+                              // objectives to search for each tile, tile group)
+    uint32_t *idx;            // [nB][nBpad] mask unit of a stored pair
+    uint4 *mask;              // [units + 1][128] dominators of a point within a block; the
+                              // last unit is all ones
+    uint32_t poolUnits;       // units of one pool
+    int32_t *din, *dout;      // [N] degrees in final order (zeroed)
+    int32_t *runs2, *rune2, *din2;     // [N] other buffers of the phases
+    uint32_t *low;            // [2][2 * nB][16] smallest keys of the unranked points of a
+                              // 64-point group, double buffered by level
+    int32_t lowK;             // objectives whose smallest keys the rank launches look at
+    uint64_t *U;              // [2][2 * nB] unranked points, double buffered by level
+    uint16_t *pos;            // [nB * 128] block of a point's witness
+    uint4 *wit;               // [nB * 128] its dominators in that block
+    RankSync *sync;           // (zeroed)
+    DevScalars *sc;
+    int32_t *rank, *dom_in, *dom_out;  // outputs in original order (dom_* may be null)
+};
+
+// Members of a block at positions [lo, hi).
+__device__ __forceinline__ void range_bits128(int32_t lo, int32_t hi, uint32_t (&m)[4]) {
+    uint32_t a[4], b[4];
+    low_bits128((uint32_t)max(lo, 0), a);
+    low_bits128((uint32_t)max(hi, 0), b);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) m[q] = b[q] & ~a[q];
+}
+
+// The instance with its size read from the device.
+__device__ __forceinline__ PairInst phase_inst(PairInst I) {
+    if (I.dynN) {
+        I.N = *I.dynN;
+        I.nB = (I.N + kWBlk - 1) / kWBlk;
+        I.nBpad = (I.nB + 63) / 64 * 64;
+    }
+    return I;
+}
+
+// Fronts taken off before the masks are stored: none while one 64-point group
+// a wave of the rank launch is enough (N <= 32k).
+inline int pair_phases(int64_t N) {
+    return N <= 32768 ? 0 : N <= 65536 ? 2 : 5;
+}
+
+inline void pair_cell_bits(int64_t N, int M, uint8_t *bits, int *T) {
+    int lg = 0;
+    while (((int64_t)1 << (lg + 1)) <= N) ++lg;
+    int t = lg - 3;
+    if (t > kCellMaxBits) t = kCellMaxBits;
+    if (t > kSplitterMaxBits * M) t = kSplitterMaxBits * M;
+    if (t < 1) t = 1;
+    for (int k = 0; k < 16; ++k) bits[k] = (uint8_t)(k < M ? t / M + (k < t % M ? 1 : 0) : 0);
+    *T = t;
+}
+
+}  // namespace nsga3

@@ -67,6 +67,27 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x) {
     return x;
 }
 
+// Wave-wide unsigned maximum or minimum by the same lane moves (the running
+// result of the highest lane is the wave's); every lane must be active.
+template <bool kMax>
+__device__ __forceinline__ uint32_t wave_extreme(uint32_t x) {
+    constexpr uint32_t kId = kMax ? 0u : 0xffffffffu;
+#define NSGA3_DPP_STEP(ctrl, rows)                                                              \
+    {                                                                                           \
+        const uint32_t t = (uint32_t)__builtin_amdgcn_update_dpp((int)kId, (int)x, ctrl, rows,  \
+                                                                 0xf, false);                   \
+        x = kMax ? (x > t ? x : t) : (x < t ? x : t);                                           \
+    }
+    NSGA3_DPP_STEP(0x111, 0xf)
+    NSGA3_DPP_STEP(0x112, 0xf)
+    NSGA3_DPP_STEP(0x114, 0xf)
+    NSGA3_DPP_STEP(0x118, 0xf)
+    NSGA3_DPP_STEP(0x142, 0xa)
+    NSGA3_DPP_STEP(0x143, 0xc)
+#undef NSGA3_DPP_STEP
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, kWave - 1);
+}
+
 // Block-wide exclusive scan of one uint32 per thread (blockDim.x a multiple of
 // 64, at most 1024).  Returns the exclusive prefix; *total receives the sum.
 // `lds` needs blockDim.x / 64 + 1 entries.

@@ -1,0 +1,635 @@
+// Fronts of the spatially ordered path (see pairs.h): Eq. (8)-(9) level by
+// level from the stored dominator masks, and the last admitted front (end of
+// Sec. IV-A.1).
+#include "kernels.h"
+#include "pairs.h"
+#include "prims.h"
+
+namespace nsga3 {
+
+// ---------------------------------------------------------------------------
+// ranks.  Front 0 are the points without a dominator.  At a later level a
+// point whose stored masks still hold an unranked dominator stays; the others
+// are the front.  A wave owns groups of 64 points.  Per level it first looks
+// at the block where a point last had an unranked dominator (its witness);
+// points that lost theirs go through the stored blocks below it downwards, all
+// 64 in step, so that a block's masks are one 1 KiB load.  Blocks whose
+// unranked points have, in some objective, a smallest key above every such
+// point's are passed (N = 50k, M = 5: a point reads 4.5 masks in all, not 17,
+// and has one witness on average).  After the first blocks the rest of a row
+// is shared among the work-group's waves, a 64-block word each: the rows at
+// the far corner of objective space are the longest by far, and 64-point
+// groups next to each other go to different work-groups.
+//
+// Small problems take one work-group, others one persistent launch with a
+// barrier per level; the points' state is in registers where a wave owns one
+// group.  The unranked sets go from level to level through global memory by
+// device-scope stores and loads (one work-group: through LDS).  Large problems
+// come here without their first fronts (see pairs.h).
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ uint64_t agent_ld(const uint64_t *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Dominators of the point at position `at` within block a, from the tables
+// (a pair whose masks were not stored).
+__device__ __forceinline__ uint4 probe_again(const PairInst &I, int32_t at, int32_t a) {
+    const int M = I.M, MP = rec_stride(M);
+    const uint32_t *T = I.tabs + (size_t)a * wblk_stride(M);
+    uint32_t m[4];
+    low_bits128(T[2], m);
+    for (int k = 0; k < M; ++k) {
+        const uint32_t x = I.recs[(size_t)at * MP + k];
+        int c = 0;  // member keys <= x
+        for (int st = 64; st >= 1; st >>= 1)
+            if (T[wblk_key_slot(k, c + st - 1)] <= x) c += st;
+        if (c == 127 && T[wblk_key_slot(k, 127)] <= x) c = 128;
+        for (int q = 0; q < 4; ++q) m[q] &= T[wblk_mask(k, q, c)];
+    }
+    uint32_t r[4];
+    range_bits128(I.runs[at] - a * kWBlk, I.rune[at] - a * kWBlk, r);
+    return make_uint4(m[0] & ~r[0], m[1] & ~r[1], m[2] & ~r[2], m[3] & ~r[3]);
+}
+
+// Whether mask m holds an unranked member of block a.
+__device__ __forceinline__ bool mask_hits(const uint4 &m, const uint64_t *Ul, int32_t a) {
+    const uint4 u = *reinterpret_cast<const uint4 *>(Ul + 2 * a);
+    return ((m.x & u.x) | (m.y & u.y) | (m.z & u.z) | (m.w & u.w)) != 0u;
+}
+
+// A wave-uniform value in scalar registers.
+__device__ __forceinline__ int32_t uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ uint64_t uniform(uint64_t v) {
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32 |
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+}
+
+// What a rank work-group keeps in LDS; slots are its 64-point groups (round *
+// kRankWaves + wave).
+struct RankLds {
+    uint64_t *U;      // [2 * nBpad] unranked points
+    uint64_t *blkU;   // [nBpad / 64] blocks with any
+    uint64_t *rows;   // [slots][nBpad / 64] stored blocks of the slot's tile
+    uint64_t *open;   // [slots] points that lost their witness
+    uint64_t *left;   // [slots] those that have not found another
+    uint32_t *low;    // [lowK][nBpad] smallest keys of a block's unranked points
+    uint32_t *half;   // [2 * nBpad][M] the same of a 64-point group (one work-group only)
+    uint32_t *xm;     // [slots][M] largest keys of the open points
+    uint64_t *hit;    // [slots][64] highest block found with an unranked dominator: [63:32]
+                      // 1 + block, [31:0] its mask unit
+    int32_t *bound;   // [slots] blocks from here on are done with
+    int32_t *list;    // [slots] slots with open points
+    uint4 *wit;       // [slots][64] witness masks and blocks (one work-group, several
+    uint16_t *pos;    // slots per wave)
+};
+
+__host__ __device__ inline size_t rank_lds_words(int nBp, int M, int lowK, int slots, int solo,
+                                                 RankLds *S, uint32_t *base) {
+    size_t c = 0;
+    auto take = [&](size_t words) {
+        const size_t at = c;
+        c += (words + 3) / 4 * 4;
+        return at;
+    };
+    const size_t nW = (size_t)nBp / 64;
+    const size_t oU = take(4 * (size_t)nBp), oB = take(2 * nW), oR = take(2 * slots * nW);
+    const size_t oO = take(4 * (size_t)slots), oL = take((size_t)lowK * nBp);
+    const size_t oH = take(solo ? 2 * (size_t)nBp * M : 0), oX = take((size_t)slots * M);
+    const size_t oT = take(128 * (size_t)slots), oN = take(slots), oI = take(slots);
+    const bool own = solo && slots > kRankWaves;
+    const size_t oW = take(own ? 256 * (size_t)slots : 0), oP = take(own ? 32 * (size_t)slots : 0);
+    if (S) {
+        S->U = reinterpret_cast<uint64_t *>(base + oU);
+        S->blkU = reinterpret_cast<uint64_t *>(base + oB);
+        S->rows = reinterpret_cast<uint64_t *>(base + oR);
+        S->open = reinterpret_cast<uint64_t *>(base + oO);
+        S->left = S->open + slots;
+        S->low = base + oL;
+        S->half = base + oH;
+        S->xm = base + oX;
+        S->hit = reinterpret_cast<uint64_t *>(base + oT);
+        S->bound = reinterpret_cast<int32_t *>(base + oN);
+        S->list = reinterpret_cast<int32_t *>(base + oI);
+        S->wit = reinterpret_cast<uint4 *>(base + oW);
+        S->pos = reinterpret_cast<uint16_t *>(base + oP);
+    }
+    return c;
+}
+
+// A lane's point of one slot.
+template <int M>
+struct RankPoint {
+    uint32_t x[M];       // keys
+    uint4 wit;           // its dominators in block p
+    int32_t p;           // block of the witness; blocks from p on hold no other unranked dominator
+    uint32_t low;        // lane k: smallest key k of the group's unranked points
+    uint32_t i;          // point index
+    int32_t din, dout;   // degrees
+};
+
+// More batches than a word has blocks (a batch may hold a single block).
+constexpr int kWholeWord = 1 << 20;
+
+// Goes down the stored blocks of word w below `bound`, until about `most` of
+// them are looked at (a batch counts as kAhead),
+// for the open lanes of a slot: hit receives 1 + the highest block with an
+// unranked dominator (upper half) and its mask unit, open is cleared.  iv:
+// mask units of the word's blocks, one a lane.  Returns the block all above
+// which are done with.
+template <int M>
+__device__ __forceinline__ int32_t scan_word(const PairInst &I, const RankLds &S, int32_t h,
+                                             const uint64_t *row, const uint32_t *xm, int32_t w,
+                                             int32_t bound, int most, uint32_t iv, bool &open,
+                                             uint64_t &hit) {
+    constexpr int kAhead = 8;  // masks read at once
+    const int lane = (int)lane_id();
+    const int32_t lim = bound - (w << 6);
+    uint64_t t = uniform(row[w] & S.blkU[w]) & (lim >= 64 ? ~0ull : (1ull << lim) - 1ull);
+    const uint64_t none = ballot(iv == kUnitNone);
+    if (t) {
+        bool ok = true;  // the lane's block against the open points
+#pragma unroll
+        for (int k = 0; k < M; ++k)
+            if (k < I.lowK) ok = ok && S.low[k * I.nBpad + (w << 6) + lane] <= xm[k];
+        t &= ballot(ok);
+    }
+    // (everything but the masks and their tests is scalar: a batch is 8 loads
+    // and 60 vector instructions)
+    const char *mk = reinterpret_cast<const char *>(I.mask);
+    const uint32_t mine = (uint32_t)((h & 1) * kWave + lane) * 16u;
+    int32_t hb = -1;   // highest block with an unranked dominator of the lane's point
+    uint32_t hu = 0;
+    while (t && most > 0) {
+        int32_t b[kAhead];
+        uint32_t u[kAhead];
+        uint4 m[kAhead];
+        int32_t top = 63 - __builtin_clzll(t);
+        if ((none >> top) & 1) {  // not stored: this block alone
+            m[0] = probe_again(I, min(h * kWave + lane, I.N - 1), (w << 6) + top);
+            t &= ~(1ull << top);
+            --most;
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q) {
+                b[q] = top;
+                u[q] = kUnitNone;
+                if (q) m[q] = make_uint4(0, 0, 0, 0);
+            }
+        } else {
+            // up to kAhead blocks; a short batch repeats its last one
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q) {
+                b[q] = top;
+                u[q] = (uint32_t)__builtin_amdgcn_readlane((int)iv, top);
+                t &= ~(1ull << top);
+                const int32_t nx = t ? 63 - __builtin_clzll(t) : top;
+                top = (none >> nx) & 1 ? top : nx;
+                m[q] = *reinterpret_cast<const uint4 *>(mk + (size_t)u[q] * (16 * kWBlk) + mine);
+            }
+            most -= kAhead;
+        }
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+            const bool in = open && mask_hits(m[q], S.U, (w << 6) + b[q]);
+            hb = in ? b[q] : hb;
+            hu = in ? u[q] : hu;
+            open = open && !in;
+        }
+        bound = (w << 6) + b[kAhead - 1];
+        if (!ballot(open)) {
+            t = 1;  // (bound stays)
+            break;
+        }
+    }
+    if (hb >= 0) hit = (uint64_t)(uint32_t)((w << 6) + hb + 1) << 32 | hu;
+    return t ? bound : w << 6;
+}
+
+// One level for the slots of a work-group; `rounds` slots per wave, at most
+// `slots` in all.  Slot q is the 64-point group q * G + g.  Returns the wave's
+// number of points of this front.  kKeep: one slot per wave, its state stays
+// in P over the levels; else it is read from and written to I.pos and I.wit.
+template <int M, bool kKeep, bool kSolo>
+__device__ __forceinline__ uint32_t rank_level(const PairInst &I, int32_t level, int32_t base, int32_t g,
+                                               int32_t G, int32_t rounds, int32_t slots,
+                                               const RankLds &S, RankPoint<M> &P, int32_t *s_n) {
+    constexpr int MP = rec_stride(M);
+    constexpr int kFirst = 8;  // blocks a wave looks at by itself before sharing a row
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int lane = (int)lane_id();
+    const int32_t nB = I.nB, nW = I.nBpad / 64, nH = 2 * nB;
+    const int32_t rel = level - base;
+    uint32_t fresh = 0;
+    // front 0 by in-degree, later levels: points that lost their witness
+#pragma unroll 1
+    for (int r = 0; r < (kKeep ? 1 : rounds); ++r) {
+        const int slot = r * kRankWaves + w;
+        const int32_t h = slot * G + g;
+        if (slot >= slots || h >= nH) break;
+        const uint64_t un = uniform(S.U[h]);
+        uint64_t open_m = 0;
+        if (un) {
+            const int32_t at = h * kWave + lane;
+            const bool mem = ((un >> lane) & 1) != 0;
+            if (rel == 0) {
+                P.p = nB;
+                P.wit = make_uint4(0, 0, 0, 0);
+            } else if (!kKeep) {
+                P.p = mem ? (int32_t)I.pos[at] : nB;
+                P.wit = mem ? I.wit[at] : make_uint4(0, 0, 0, 0);
+            }
+            if (kKeep && rel == 0) {
+                P.i = mem ? I.sval[at] : 0u;
+                P.din = mem ? I.din[at] : 1;
+                P.dout = mem && I.dom_out ? I.dout[at] : 0;
+                P.low = lane < M ? I.low[(size_t)h * 16 + lane] : 0u;
+#pragma unroll
+                for (int k = 0; k < M; ++k) P.x[k] = mem ? I.recs[(size_t)at * MP + k] : 0xffffffffu;
+            }
+            bool open;
+            if (rel == 0)
+                open = mem && (kKeep ? P.din : I.din[at]) == 0;
+            else
+                open = mem && (P.p >= nB || !mask_hits(P.wit, S.U, P.p));
+            open_m = ballot(open);
+            if (open_m) {
+                S.hit[slot * kWave + lane] = 0ull;
+                if (rel > 0) {
+                    if (!kKeep) {
+#pragma unroll
+                        for (int k = 0; k < M; ++k)
+                            P.x[k] = mem ? I.recs[(size_t)at * MP + k] : 0xffffffffu;
+                    }
+#pragma unroll
+                    for (int k = 0; k < M; ++k) {
+                        const uint32_t x = wave_extreme<true>(open ? P.x[k] : 0u);
+                        if (lane == 0) S.xm[slot * M + k] = x;
+                    }
+                    const int32_t bd = (int32_t)wave_extreme<true>(open ? (uint32_t)P.p : 0u);
+                    if (lane == 0) S.bound[slot] = bd;
+                }
+            }
+        }
+        if (lane == 0) {
+            S.open[slot] = open_m;
+            S.left[slot] = open_m;
+        }
+    }
+    if (rel > 0) {
+        // a wave's own slots first, a few blocks each, all points in step: most
+        // find a witness there
+#pragma unroll 1
+        for (int r = 0; r < (kKeep ? 1 : rounds); ++r) {
+            const int slot = r * kRankWaves + w;
+            const int32_t h = slot * G + g;
+            if (slot >= slots || h >= nH) break;
+            const uint64_t om = uniform(S.left[slot]);
+            if (!om) continue;
+            const uint64_t *row = S.rows + (size_t)slot * nW;
+            int32_t bound = uniform(S.bound[slot]);
+            int32_t wd = (bound + 63) / 64 - 1;  // the highest word with blocks
+            while (wd >= 0 && uniform(row[wd] & S.blkU[wd]) == 0ull) --wd;
+            if (wd < 0) continue;
+            const uint32_t iv = I.idx[(size_t)(h >> 1) * I.nBpad + wd * 64 + lane];
+            uint32_t xm[M];
+#pragma unroll
+            for (int k = 0; k < M; ++k) xm[k] = S.xm[slot * M + k];
+            bool open = ((om >> lane) & 1) != 0;
+            uint64_t hit = 0;
+            bound = scan_word<M>(I, S, h, row, xm, wd, bound, kFirst, iv, open, hit);
+            if (hit) S.hit[slot * kWave + lane] = hit;
+            const uint64_t still = ballot(open);
+            if (lane == 0) {
+                S.left[slot] = still;
+                S.bound[slot] = bound;
+                if (still && bound > 0) S.list[atomicAdd(s_n, 1)] = slot;
+            }
+        }
+        __syncthreads();
+        // the rest of the rows, a word at a time over all waves
+        const int32_t nE = uniform(*s_n);
+#pragma unroll 1
+        for (int32_t u = w; u < nE * nW; u += kRankWaves) {
+            const int32_t slot = uniform(S.list[u % nE]);
+            const int32_t wd = nW - 1 - u / nE;
+            const int32_t h = slot * G + g;
+            const int32_t bound = uniform(S.bound[slot]);
+            const uint64_t *row = S.rows + (size_t)slot * nW;
+            if (bound <= wd << 6 || uniform(row[wd] & S.blkU[wd]) == 0ull) continue;
+            const uint32_t iv = I.idx[(size_t)(h >> 1) * I.nBpad + wd * 64 + lane];
+            uint32_t xm[M];
+#pragma unroll
+            for (int k = 0; k < M; ++k) xm[k] = S.xm[slot * M + k];
+            bool open = ((uniform(S.left[slot]) >> lane) & 1) != 0;
+            uint64_t hit = 0;
+            scan_word<M>(I, S, h, row, xm, wd, bound, kWholeWord, iv, open, hit);
+            if (hit)
+                atomicMax((unsigned long long *)&S.hit[slot * kWave + lane],
+                          (unsigned long long)hit);
+        }
+        __syncthreads();
+    }
+    // fronts, and the unranked sets of the next level
+#pragma unroll 1
+    for (int r = 0; r < (kKeep ? 1 : rounds); ++r) {
+        const int slot = r * kRankWaves + w;
+        const int32_t h = slot * G + g;
+        if (slot >= slots || h >= nH) break;
+        const uint64_t un = uniform(S.U[h]);
+        const uint64_t om = uniform(S.open[slot]);
+        uint64_t front = 0;
+        const int32_t at = h * kWave + lane;
+        const bool mem = ((un >> lane) & 1) != 0;
+        if (om) {
+            const bool open = ((om >> lane) & 1) != 0;
+            const uint64_t hit = open ? S.hit[slot * kWave + lane] : 0ull;
+            if (hit) {
+                // (a block whose masks are not stored is looked at again next level)
+                const uint32_t u = (uint32_t)hit;
+                const int32_t p = (int32_t)(hit >> 32) - (u == kUnitNone ? 0 : 1);
+                uint4 wit = make_uint4(0, 0, 0, 0);
+                if (u != kUnitNone) wit = I.mask[(size_t)u * kWBlk + (h & 1) * kWave + lane];
+                if (kKeep) {
+                    P.p = p;
+                    P.wit = wit;
+                } else {
+                    I.pos[at] = (uint16_t)p;
+                    I.wit[at] = wit;
+                }
+            }
+            front = ballot(open && !hit);
+            if (open && !hit) {
+                const uint32_t i = kKeep ? P.i : I.sval[at];
+                I.rank[i] = level;
+                if (I.dom_in) I.dom_in[i] = kKeep ? P.din : I.din[at];
+                if (I.dom_out) I.dom_out[i] = kKeep ? P.dout : I.dout[at];
+            }
+            fresh += (uint32_t)__popcll(front);
+        }
+        if (rel == 0 && !kKeep && mem && !((front >> lane) & 1)) {
+            I.pos[at] = (uint16_t)nB;
+            I.wit[at] = make_uint4(0, 0, 0, 0);
+        }
+        if (un) {
+            // smallest keys of what stays
+            uint32_t low = kKeep ? P.low : 0u;
+            if (front) {
+                const bool stays = mem && !((front >> lane) & 1);
+#pragma unroll
+                for (int k = 0; k < M; ++k) {
+                    const uint32_t x = kKeep ? P.x[k] : I.recs[(size_t)min(at, I.N - 1) * MP + k];
+                    const uint32_t l = wave_extreme<false>(stays ? x : 0xffffffffu);
+                    if (lane == k) low = l;
+                }
+                if (kKeep) P.low = low;
+            } else if (!kKeep && lane < M) {
+                low = kSolo && rel > 0
+                          ? S.half[h * M + lane]
+                          : __hip_atomic_load(&I.low[((size_t)(rel & 1) * 2 * nB + h) * 16 + lane],
+                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            if (kSolo) {
+                if (lane < M) S.half[h * M + lane] = low;
+            } else if (lane < I.lowK) {
+                __hip_atomic_store(&I.low[((size_t)((rel + 1) & 1) * 2 * nB + h) * 16 + lane], low,
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        if (lane == 0) {
+            if (kSolo)
+                S.U[h] = un & ~front;
+            else
+                __hip_atomic_store(&I.U[(size_t)((rel + 1) & 1) * 2 * nB + h], un & ~front,
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    return fresh;
+}
+
+// The unranked set of the rel-th level into LDS (the first: every point).
+template <int M, bool kSolo>
+__device__ __forceinline__ void load_unranked(const PairInst &I, int32_t rel, const RankLds &S) {
+    const int32_t N = I.N, nB = I.nB, nBp = I.nBpad;
+    for (int32_t a0 = 0; a0 < nBp; a0 += kRankThreads) {
+        const int32_t a = a0 + (int32_t)threadIdx.x;
+        uint64_t u0 = 0, u1 = 0;
+        if (a < nB) {
+            if (rel == 0) {
+                const int32_t n = N - a * kWBlk;
+                u0 = n >= 64 ? ~0ull : ((1ull << n) - 1ull);
+                u1 = n >= 128 ? ~0ull : (n <= 64 ? 0ull : ((1ull << (n - 64)) - 1ull));
+            } else if (kSolo) {
+                u0 = S.U[2 * a];
+                u1 = S.U[2 * a + 1];
+            } else {
+                const uint64_t *U = I.U + (size_t)(rel & 1) * 2 * nB;
+                u0 = agent_ld(&U[2 * a]);
+                u1 = agent_ld(&U[2 * a + 1]);
+            }
+            if (!kSolo || rel == 0) {
+                S.U[2 * a] = u0;
+                S.U[2 * a + 1] = u1;
+            }
+            if (rel > 0) {  // (front 0 looks at no block)
+                uint64_t y0[(M + 1) / 2], y1[(M + 1) / 2];
+                const uint64_t *L = reinterpret_cast<const uint64_t *>(
+                    I.low + ((size_t)(rel & 1) * 2 * nB + 2 * a) * 16);
+                if (!kSolo) {  // (every load before the first use)
+#pragma unroll
+                    for (int k = 0; k < M; k += 2) {
+                        const bool in = k < I.lowK;
+                        y0[k / 2] = in ? agent_ld(&L[k / 2]) : 0ull;
+                        y1[k / 2] = in ? agent_ld(&L[8 + k / 2]) : 0ull;
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < M; ++k) {
+                    uint32_t z0, z1;
+                    if (kSolo) {
+                        z0 = S.half[(2 * a) * M + k];
+                        z1 = S.half[(2 * a + 1) * M + k];
+                    } else {
+                        z0 = (uint32_t)(y0[k / 2] >> (32 * (k & 1)));
+                        z1 = (uint32_t)(y1[k / 2] >> (32 * (k & 1)));
+                    }
+                    if (k < I.lowK) S.low[k * nBp + a] = min(u0 ? z0 : ~0u, u1 ? z1 : ~0u);
+                }
+            }
+        }
+        const uint64_t m = ballot((u0 | u1) != 0ull);
+        if (lane_id() == 0 && a < nBp) S.blkU[a >> 6] = m;
+    }
+}
+
+// Stored-block rows of the work-group's slots.
+__device__ __forceinline__ void load_rows(const PairInst &I, int32_t g, int32_t G, int32_t slots,
+                                          const RankLds &S) {
+    const int32_t nW = I.nBpad / 64;
+    for (int32_t q = (int32_t)threadIdx.x; q < slots * nW; q += kRankThreads) {
+        const int32_t tile = (q / nW * G + g) >> 1;
+        S.rows[q] = tile < I.nB ? I.nz[(size_t)tile * nW + q % nW] : 0ull;
+    }
+}
+
+// Points of the fronts before level0.
+__device__ __forceinline__ uint32_t rank_done(const PairInst &I, int32_t level0) {
+    uint32_t n = 0;
+    for (int32_t l = 0; l < level0; ++l) n += I.sync->lv[l];
+    return n;
+}
+
+// Every level from level0 on, for the points that I still holds.
+template <int M, bool kKeep, bool kSolo>
+__device__ __forceinline__ void rank_levels(PairInst I, int32_t level0, uint32_t *dyn,
+                                            uint32_t *s_new, uint32_t *s_fp, int32_t *s_np) {
+    uint32_t &s_f = *s_fp;
+    int32_t &s_n = *s_np;
+    const int tid = (int)threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int lane = (int)lane_id();
+    const int32_t g = kSolo ? 0 : (int32_t)blockIdx.x, G = kSolo ? 1 : (int32_t)gridDim.x;
+    const int32_t rounds = (2 * I.nB + G * kRankWaves - 1) / (G * kRankWaves);
+    RankLds S;
+    rank_lds_words(I.nBpad, M, I.lowK, rounds * kRankWaves, kSolo, &S, dyn);
+    if (kSolo && !kKeep) {  // the points' state in LDS
+        I.pos = S.pos;
+        I.wit = S.wit;
+    }
+    load_rows(I, g, G, rounds * kRankWaves, S);
+    RankPoint<M> P;
+    uint32_t done = 0;             // points ranked before this level
+    bool found = false;
+    auto close = [&](int32_t level, uint32_t f) {  // level `level` has f points
+        if (g == 0 && tid == 0) {
+            if (!found && (int64_t)done + f >= I.K) {
+                found = true;
+                I.sc->last_front = level;
+                I.sc->last_front_size = (int32_t)f;
+                I.sc->n_before = done;
+                I.sc->num_from_last = I.K - done;
+            }
+            I.sc->num_fronts = level + 1;
+        }
+        done += f;
+    };
+    const uint32_t total = (uint32_t)I.N + rank_done(I, level0);
+    for (int32_t level = 0; level < level0; ++level) {
+        const uint32_t f = I.sync->lv[level];
+        if (f) close(level, f);
+    }
+    if (I.N == 0) return;
+    for (int32_t level = level0;; ++level) {
+        if (tid == 0) s_n = 0;
+        load_unranked<M, kSolo>(I, level - level0, S);
+        __syncthreads();
+        const uint32_t fresh = rank_level<M, kKeep, kSolo>(I, level, level0, g, G, rounds,
+                                                             rounds * kRankWaves, S, P, &s_n);
+        if (lane == 0) s_new[w] = fresh;
+        if (!kSolo) __builtin_amdgcn_s_waitcnt(0);  // this wave's part of the next set is written
+        __syncthreads();
+        uint32_t f = 0;
+        if (kSolo) {
+            for (int q = 0; q < kRankWaves; ++q) f += s_new[q];
+            __syncthreads();  // s_new is free again
+        } else {
+            // one wave: this work-group's flag, then everyone's
+            if (w == 0) {
+                uint32_t n = lane < kRankWaves ? s_new[lane] : 0u;
+                n = wave_sum(n);
+                uint64_t *flag = I.sync->flag[(level - level0) & 1];
+                const uint32_t tag = (uint32_t)(level - level0 + 1);
+                if (lane == 0)
+                    __hip_atomic_store(&flag[g], (uint64_t)tag << 32 | n, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+                uint64_t v = 0, spins = 0;
+                while (true) {
+                    v = lane < G ? agent_ld(&flag[lane]) : (uint64_t)tag << 32;
+                    if (ballot((uint32_t)(v >> 32) != tag) == 0ull) break;
+                    __builtin_amdgcn_s_sleep(1);
+                    if (++spins > (1ull << 26)) {  // a work-group never arrived
+                        if (lane == 0) atomicOr(&I.sc->err, (uint32_t)kErrBarrierTimeout);
+                        v = ~0ull;
+                        break;
+                    }
+                }
+                const uint32_t all = wave_sum((uint32_t)v);
+                if (lane == 0) s_f = ballot(v == ~0ull) ? ~0u : all;
+            }
+            __syncthreads();
+            f = s_f;
+            if (f == ~0u) return;
+        }
+        close(level, f);
+        if (done >= total) return;
+        if (f == 0) {  // impossible for a partial order
+            if (tid == 0) atomicOr(&I.sc->err, (uint32_t)kErrInternal);
+            return;
+        }
+    }
+}
+
+template <int M, bool kKeep, bool kSolo>
+__global__ __launch_bounds__(kRankThreads) void k_ranks(PairInst I) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
+    __shared__ uint32_t s_new[kRankWaves];
+    __shared__ uint32_t s_f;
+    __shared__ int32_t s_n;
+    if (I.sc->err) return;
+    rank_levels<M, kKeep, kSolo>(I, 0, dyn, s_new, &s_f, &s_n);
+}
+
+// The levels that the first `phases` fronts leave (their number of points is
+// on the device).
+template <int M>
+__global__ __launch_bounds__(kRankThreads) void k_ranks_rest(PairInst I, int32_t phases) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
+    __shared__ uint32_t s_new[kRankWaves];
+    __shared__ uint32_t s_f;
+    __shared__ int32_t s_n;
+    if (I.sc->err) return;
+    I = phase_inst(I);
+    if (2 * I.nB <= (int32_t)gridDim.x * kRankWaves)
+        rank_levels<M, true, false>(I, phases, dyn, s_new, &s_f, &s_n);
+    else
+        rank_levels<M, false, false>(I, phases, dyn, s_new, &s_f, &s_n);
+}
+
+static int rank_rounds(const PairInst &I, int G) {
+    return (2 * I.nB + G * kRankWaves - 1) / (G * kRankWaves);
+}
+
+static size_t ranks_lds_bytes(const PairInst &I, int slots, bool solo) {
+    return 4 * rank_lds_words(I.nBpad, I.M, I.lowK, slots, solo, nullptr, nullptr);
+}
+
+template <int M>
+static hipError_t launch_ranks(const PairInst &I, int phases, hipStream_t s) {
+    const int rounds = rank_rounds(I, I.groups);
+    const dim3 gr((unsigned)I.groups), th(kRankThreads);
+    if (phases > 0) {
+        hipLaunchKernelGGL(k_ranks_rest<M>, gr, th, ranks_lds_bytes(I, rounds * kRankWaves, false),
+                           s, I, phases);
+    } else if (I.groups == 1) {
+        const size_t lds = ranks_lds_bytes(I, rounds * kRankWaves, true);
+        if (rounds == 1)
+            hipLaunchKernelGGL((k_ranks<M, true, true>), gr, th, lds, s, I);
+        else
+            hipLaunchKernelGGL((k_ranks<M, false, true>), gr, th, lds, s, I);
+    } else {
+        hipLaunchKernelGGL((k_ranks<M, true, false>), gr, th, ranks_lds_bytes(I, kRankWaves, false),
+                           s, I);
+    }
+    return hipGetLastError();
+}
+
+hipError_t run_ranks(const PairInst &I, int phases, hipStream_t s) {
+    switch (I.M) {
+#define NSGA3_CASE(m) case m: return launch_ranks<m>(I, phases, s);
+        NSGA3_CASE(2) NSGA3_CASE(3) NSGA3_CASE(4) NSGA3_CASE(5) NSGA3_CASE(6) NSGA3_CASE(7)
+        NSGA3_CASE(8) NSGA3_CASE(9) NSGA3_CASE(10) NSGA3_CASE(11) NSGA3_CASE(12) NSGA3_CASE(13)
+        NSGA3_CASE(14) NSGA3_CASE(15) NSGA3_CASE(16)
+#undef NSGA3_CASE
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace nsga3

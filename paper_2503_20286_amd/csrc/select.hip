@@ -37,29 +37,7 @@ constexpr int kNormBlocksMax = 256;
 // ---------------------------------------------------------------------------
 // init: clear per-call scalars and counters (fill kernels, no memset nodes)
 // ---------------------------------------------------------------------------
-__global__ void k_init_scalars(DevScalars *sc) {
-    const int t = threadIdx.x;
-    if (t == 0) {
-        sc->err = 0;
-        sc->last_front = 0;
-        sc->num_fronts = 0;
-        sc->last_front_size = 0;
-        sc->n_before = 0;
-        sc->num_from_last = 0;
-        sc->fallback = 0;
-        sc->near_ties = 0;
-        sc->nf = sc->nu = 0;
-        sc->bar_count = 0;
-        sc->bar_gen = 0;
-        sc->level_V = 0;
-        sc->ref_thr = 0;
-    }
-    if (t < 16) {
-        sc->min_key[t] = 0xffffffffu;
-        sc->a[t] = 1.0;
-        sc->z[t] = 0.0;
-    }
-}
+__global__ void k_init_scalars(DevScalars *sc) { init_scalars(sc, (int)threadIdx.x); }
 
 __global__ void k_fill_i32(int32_t *p, int64_t n, int32_t v) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -81,28 +59,8 @@ hipError_t run_init(DevScalars *sc, int32_t *zero_i32[], const int64_t zero_n[],
 // ---------------------------------------------------------------------------
 // reference directions: validity and unit vectors (float64 and float32)
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ uint16_t bf16_rne(float f) {
-    const uint32_t u = __float_as_uint(f);
-    return (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);  // finite inputs only
-}
-
-// Unit reference directions in float64 and float32, and in bfloat16 for the
-// matrix-core screening: [Hpad x KP] (KP = 8 for M <= 8, else 16), rows and
-// columns beyond (H, M) zero.
-__global__ void k_refs(const float *__restrict__ refs, int H, int M, double *__restrict__ rhat64,
-                       float *__restrict__ rhat32, uint16_t *__restrict__ rhat16, int Hpad, int KP,
-                       DevScalars *__restrict__ sc) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < Hpad && rhat16) {
-        for (int k = 0; k < KP; ++k) rhat16[(int64_t)j * KP + k] = 0;
-    }
-    if (j >= H) return;
-    if (!unit_reference(refs, j, M, rhat64, rhat32)) {
-        atomicOr(&sc->err, (uint32_t)kErrBadRef);
-        return;
-    }
-    if (rhat16)
-        for (int k = 0; k < M; ++k) rhat16[(int64_t)j * KP + k] = bf16_rne(rhat32[(int64_t)j * M + k]);
+__global__ void k_refs(RefArgs R, int M, DevScalars *__restrict__ sc) {
+    reference_item(R, M, (int)(blockIdx.x * blockDim.x + threadIdx.x), sc);
 }
 
 __device__ __forceinline__ double ideal(const DevScalars *sc, int k) {
@@ -832,12 +790,8 @@ hipError_t run_select_stage(const SelectViews &v, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t run_refs(const float *refs, int H, int M, double *rhat64, float *rhat32,
-                    uint16_t *rhat16, DevScalars *sc, hipStream_t s) {
-    const int Hpad = (H + 31) / 32 * 32;
-    const int KP = M <= 8 ? 8 : 16;
-    hipLaunchKernelGGL(k_refs, dim3((Hpad + 255) / 256), dim3(256), 0, s, refs, H, M, rhat64,
-                       rhat32, rhat16, Hpad, KP, sc);
+hipError_t run_refs(const RefArgs &R, int M, DevScalars *sc, hipStream_t s) {
+    hipLaunchKernelGGL(k_refs, dim3((unsigned)((R.Hpad + 255) / 256)), dim3(256), 0, s, R, M, sc);
     return hipGetLastError();
 }
 

@@ -290,4 +290,58 @@ __device__ __forceinline__ bool unit_reference(const float *refs, int j, int M, 
     return true;
 }
 
+__device__ __forceinline__ uint16_t bf16_rne(float f) {
+    const uint32_t u = __float_as_uint(f);
+    return (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);  // finite inputs only
+}
+
+// Unit reference directions in float64 and float32, and in bfloat16 for the
+// matrix-core screening: [Hpad x KP] (KP = 8 for M <= 8, else 16), rows and
+// columns beyond (H, M) zero.
+struct RefArgs {
+    const float *refs;
+    int H, Hpad, KP;
+    double *rhat64;
+    float *rhat32;
+    uint16_t *rhat16;
+};
+
+__device__ __forceinline__ void reference_item(const RefArgs &R, int M, int j, DevScalars *sc) {
+    if (j < R.Hpad && R.rhat16) {
+        for (int k = 0; k < R.KP; ++k) R.rhat16[(int64_t)j * R.KP + k] = 0;
+    }
+    if (j >= R.H) return;
+    if (!unit_reference(R.refs, j, M, R.rhat64, R.rhat32)) {
+        atomicOr(&sc->err, (uint32_t)kErrBadRef);
+        return;
+    }
+    if (R.rhat16)
+        for (int k = 0; k < M; ++k)
+            R.rhat16[(int64_t)j * R.KP + k] = bf16_rne(R.rhat32[(int64_t)j * M + k]);
+}
+
+// Per-call scalars, by one work-group of at least 16 threads.
+__device__ __forceinline__ void init_scalars(DevScalars *sc, int t) {
+    if (t == 0) {
+        sc->err = 0;
+        sc->last_front = 0;
+        sc->num_fronts = 0;
+        sc->last_front_size = 0;
+        sc->n_before = 0;
+        sc->num_from_last = 0;
+        sc->fallback = 0;
+        sc->near_ties = 0;
+        sc->nf = sc->nu = 0;
+        sc->bar_count = 0;
+        sc->bar_gen = 0;
+        sc->level_V = 0;
+        sc->ref_thr = 0;
+    }
+    if (t < 16) {
+        sc->min_key[t] = 0xffffffffu;
+        sc->a[t] = 1.0;
+        sc->z[t] = 0.0;
+    }
+}
+
 }  // namespace nsga3
