@@ -219,6 +219,25 @@ Layout layout_pairs(int64_t N, int M, int H) {
     return L;
 }
 
+// Offsets of the arrays a HypE selection needs beside those of its sort.
+struct HypeTail {
+    size_t tabs, skey, skey_alt, sval, sval_alt, temp, total;
+};
+
+HypeTail hype_tail(size_t c, int64_t N, int M) {
+    HypeTail T;
+    const size_t n = (size_t)N;
+    const size_t rt = radix_sort_temp_bytes(N), ct = compact_temp_bytes(N);
+    T.tabs = bump(c, bit_tables_bytes(N, M));
+    T.skey = bump(c, 8 * n);
+    T.skey_alt = bump(c, 8 * n);
+    T.sval = bump(c, 4 * n);
+    T.sval_alt = bump(c, 4 * n);
+    T.temp = bump(c, rt > ct ? rt : ct);
+    T.total = c;
+    return T;
+}
+
 bool sizes_ok(int64_t N, int32_t M, int32_t H) {
     return N >= 1 && N <= 2147483647LL && M >= 2 && M <= 16 && H >= 1 && H <= 65535;
 }
@@ -418,7 +437,7 @@ SortViews sort_views(char *w, const Layout &L, const nsga3_problem &p, int32_t *
 // The spatially ordered path's problem over the workspace w carved by L.
 PairInst pair_inst(char *w, const Layout &L, const nsga3_problem &p, int32_t *rank_o) {
 #define WS(T, f) reinterpret_cast<T *>(w + L.f)
-    PairInst I;
+    PairInst I = {};
     I.objs = p.objs;
     I.N = (int32_t)p.N;
     I.M = p.M;
@@ -888,34 +907,57 @@ nsga3_status nsga3_hype_select(nsga3_ctx *ctx, const float *objs, int64_t N, int
     if (!ctx || !objs || !vref || !U || !selected) return NSGA3_E_INVALID;
     if (!sizes_ok(N, M, 1) || n < 1 || n > N || s < 1 || s > 2147483647LL) return NSGA3_E_INVALID;
     DeviceGuard g(ctx->device);
-    const Layout L = layout_for(N, M, 1, kGridCap);
     const size_t extra = hype_extra_bytes(N, M, s);
-    const nsga3_status st = ensure_ws(ctx, L.total + extra);
+    HypeTail T = {};
+    bool pairs = false;
+    Layout L = {};
+    nsga3_status st = NSGA3_E_NOMEM;
+    if (ctx->pairs && N <= kPairsMaxN) {  // as in ensure_select_ws
+        L = layout_pairs(N, M, 1);
+        T = hype_tail(L.total, N, M);
+        st = ensure_ws(ctx, T.total + extra);
+        pairs = st == NSGA3_OK;
+    }
+    if (!pairs) {
+        L = layout_for(N, M, 1, kGridCap);
+        T = {L.tabs_all, L.skey, L.skey_alt, L.sval, L.sval_alt, L.temp, L.total};
+        st = ensure_ws(ctx, T.total + extra);
+    }
     if (st != NSGA3_OK) return st;
     char *w = (char *)ctx->ws;
 #define WS(T, f) reinterpret_cast<T *>(w + L.f)
     DevScalars *sc = WS(DevScalars, sc);
     int32_t *rank_o = rank ? rank : WS(int32_t, rank);
-    const LaunchCfg cfg = ctx_cfg(ctx, M, N);
     PhaseMarks marks(nullptr, stream);   // phase timing covers nsga3_select only
     Marker mk;
     mk.fn = [](void *x) { static_cast<PhaseMarks *>(x)->mark(); };
     mk.arg = &marks;
-    int32_t *zero_p[] = {WS(int32_t, dom_in_s), WS(int32_t, dom_out_s), WS(int32_t, bar),
-                         WS(int32_t, work), WS(int32_t, lbstate)};
-    const int64_t zero_n[] = {N, N, (int64_t)(sizeof(GridBar) / sizeof(int32_t)), kMaxHostLevels,
-                              (int64_t)(2 * L.lb_stride)};
-    hipError_t e = run_init(sc, zero_p, zero_n, 5, stream);
-    // ranks and the last front for a population of n (no out-degrees needed)
+    // ranks and the last front for a population of n (no out-degrees needed),
+    // and 64-member tables of all points for the sample probes
     const nsga3_problem p = {objs, N, M, vref, 1, n, selected, rank_o, nullptr, nullptr,
                              nullptr, nullptr, nullptr};
-    SortViews sv = sort_views(w, L, p, rank_o, mk, cfg);
-    if (e == hipSuccess) e = run_sort_stage(sv, cfg, stream);
-    if (e == hipSuccess && ctx->last_fronts)
-        e = hipMemcpyAsync((void *)ctx->last_fronts, &sc->fb[0], sizeof(int32_t) * (1 + kProfLevels),
-                           hipMemcpyDeviceToHost, stream);
-    // the sample probes read 64-member tables of all points
-    if (e == hipSuccess && (!cfg.bitsets || counts_use_wide(sv))) e = run_build_all_tables(sv, stream);
+    hipError_t e;
+    if (pairs) {
+        PairInst pi = pair_inst(w, L, p, rank_o);
+        pi.tabs64 = reinterpret_cast<uint32_t *>(w + T.tabs);
+        const RefArgs none = {};
+        e = run_pairs(pi, none, WS(uint32_t, zero), (int64_t)L.zero_words, mk, stream);
+    } else {
+        const LaunchCfg cfg = ctx_cfg(ctx, M, N);
+        int32_t *zero_p[] = {WS(int32_t, dom_in_s), WS(int32_t, dom_out_s), WS(int32_t, bar),
+                             WS(int32_t, work), WS(int32_t, lbstate)};
+        const int64_t zero_n[] = {N, N, (int64_t)(sizeof(GridBar) / sizeof(int32_t)), kMaxHostLevels,
+                                  (int64_t)(2 * L.lb_stride)};
+        e = run_init(sc, zero_p, zero_n, 5, stream);
+        SortViews sv = sort_views(w, L, p, rank_o, mk, cfg);
+        if (e == hipSuccess) e = run_sort_stage(sv, cfg, stream);
+        if (e == hipSuccess && ctx->last_fronts)
+            e = hipMemcpyAsync((void *)ctx->last_fronts, &sc->fb[0], sizeof(int32_t) * (1 + kProfLevels),
+                               hipMemcpyDeviceToHost, stream);
+        // the sample probes read 64-member tables of all points
+        if (e == hipSuccess && (!cfg.bitsets || counts_use_wide(sv)))
+            e = run_build_tables(sv.recs, N, M, sv.tabs_all, sc, stream);
+    }
     if (e == hipSuccess) {
         HypeViews hv;
         hv.objs = objs;
@@ -928,16 +970,19 @@ nsga3_status nsga3_hype_select(nsga3_ctx *ctx, const float *objs, int64_t N, int
         hv.selected = selected;
         hv.d = d;
         hv.rank = rank_o;
-        hv.tabs_all = WS(uint32_t, tabs_all);
-        hv.skey = WS(uint64_t, skey);
-        hv.skey_alt = WS(uint64_t, skey_alt);
-        hv.sval = WS(uint32_t, sval);
-        hv.sval_alt = WS(uint32_t, sval_alt);
-        hv.temp = WS(uint32_t, temp);
+        hv.tabs_all = reinterpret_cast<uint32_t *>(w + T.tabs);
+        hv.skey = reinterpret_cast<uint64_t *>(w + T.skey);
+        hv.skey_alt = reinterpret_cast<uint64_t *>(w + T.skey_alt);
+        hv.sval = reinterpret_cast<uint32_t *>(w + T.sval);
+        hv.sval_alt = reinterpret_cast<uint32_t *>(w + T.sval_alt);
+        hv.temp = reinterpret_cast<uint32_t *>(w + T.temp);
         hv.selflag = WS(uint8_t, selflag);
         hv.sc = sc;
         hv.info = info;
-        hv.extra = w + L.total;
+        // partial estimates, 64 bytes a point: over the list buffers of the levels,
+        // or the stored masks
+        hv.part = pairs ? WS(double, mask) : WS(double, fk0);
+        hv.extra = w + T.total;
         e = run_hype(hv, stream);
     }
 #undef WS

@@ -92,8 +92,9 @@ hipError_t run_sort_stage(const SortViews &v, const LaunchCfg &cfg, hipStream_t 
 
 // ---- bitdom.hip -----------------------------------------------------------
 hipError_t run_bit_counts(const SortViews &v, hipStream_t s);
-// Block tables of all sorted points (tabs_all), as the count stage builds them.
-hipError_t run_build_all_tables(const SortViews &v, hipStream_t s);
+// 64-member block tables of N records.
+hipError_t run_build_tables(const uint32_t *recs, int64_t N, int M, uint32_t *tabs,
+                            const DevScalars *sc, hipStream_t s);
 // Whether the count stage of v builds 128-member tables in tabs_all (which the
 // 64-member probes of later stages cannot read).
 bool counts_use_wide(const SortViews &v);
@@ -147,6 +148,7 @@ struct HypeViews {
     uint32_t *sval, *sval_alt;
     uint32_t *temp;              // radix-sort / scan scratch
     uint8_t *selflag;            // [N]
+    double *part;                // [8 * N] partial estimates
     DevScalars *sc;
     nsga3_info *info;
     void *extra;                 // hype_extra_bytes(N, M, s)

@@ -117,6 +117,7 @@ struct PairInst {
     RankSync *sync;           // (zeroed)
     DevScalars *sc;
     int32_t *rank, *dom_in, *dom_out;  // outputs in original order (dom_* may be null)
+    uint32_t *tabs64;         // 64-member tables of all points, for a caller that probes them (or null)
 };
 
 // Members of a block at positions [lo, hi).

@@ -698,6 +698,10 @@ static hipError_t launch_pairs(const PairInst &I, const Marker &mark, hipStream_
     const unsigned nbN = (unsigned)((I.N + 255) / 256);
     hipLaunchKernelGGL(k_cell_sort<M>, dim3(nbN), dim3(256), 0, s, I);
     mark();
+    if (I.tabs64) {
+        const hipError_t e = run_build_tables(I.recs, I.N, M, I.tabs64, I.sc, s);
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(k_pair_build<M>, dim3((unsigned)I.nB), dim3(M * kWave), 0, s, I);
     const unsigned tgs = (unsigned)((I.nB + kPairWaves - 1) / kPairWaves);
     const dim3 th(kPairWaves * kWave);
