@@ -92,7 +92,7 @@ struct Layout {
     size_t rank, niche, dist64, rhat64, rhat32, rhat16, p_asf, p_idx, p_nad;
     size_t rho, bcount, bstart, bcursor, gstart, bd, bi, selflag, sc, bar;
     // spatially ordered path (layout_pairs)
-    size_t spl, cell, code, slot, trec, box, nz, idx, mask, low, U, pos, wit, sync, runs2, rune2, din2, list;
+    size_t spl, cell, code, slot, trec, box, nz, idx, mask, low, ex, pos, wit, sync, runs2, rune2, din2, list;
     size_t zero, zero_words;   // counters the path clears first
     size_t total;
 };
@@ -186,6 +186,7 @@ Layout layout_pairs(int64_t N, int M, int H) {
     L.dom_out_s = bump(c, 4 * n);
     L.nz = bump(c, nB * nBp / 8);
     L.sync = bump(c, sizeof(RankSync));
+    L.ex = bump(c, 8 * 2 * ((size_t)M + 2) * 2 * nBp);
     L.rho = bump(c, 4 * (size_t)H);
     L.bcount = bump(c, 4 * (size_t)H);
     L.zero_words = (c - L.zero) / 4;
@@ -208,8 +209,7 @@ Layout layout_pairs(int64_t N, int M, int H) {
     L.list = bump(c, n2 ? 16 * tgs * (nB + kListItem) : 0);
     L.tabs_all = bump(c, 4 * nB * (size_t)wblk_stride(M));
     L.box = bump(c, 4 * 2 * (size_t)M * nBp);
-    L.low = bump(c, 4 * 2 * 2 * nB * 16);
-    L.U = bump(c, 8 * 4 * nB);
+    L.low = bump(c, 4 * 2 * nB * 16);
     L.pos = bump(c, 2 * kWBlk * nB);
     L.wit = bump(c, 16 * kWBlk * nB);
     L.idx = bump(c, 4 * nB * nBp);
@@ -466,7 +466,7 @@ PairInst pair_inst(char *w, const Layout &L, const nsga3_problem &p, int32_t *ra
     I.dout = WS(int32_t, dom_out_s);
     I.low = WS(uint32_t, low);
     I.lowK = kRankLowBytes / (4 * I.nBpad) < I.M ? kRankLowBytes / (4 * I.nBpad) : I.M;
-    I.U = WS(uint64_t, U);
+    I.ex = WS(uint64_t, ex);
     I.runs2 = WS(int32_t, runs2);
     I.rune2 = WS(int32_t, rune2);
     I.din2 = WS(int32_t, din2);

@@ -62,15 +62,12 @@ inline size_t mask_units(size_t nB) {
     return (u + kMaskPools - 1) / kMaskPools * kMaskPools + 8 * kMaskPools;
 }
 
-// Counters of the rank launches.  flag: what
-// each work-group of the persistent launch has done, [63:32] levels, [31:0]
-// its points of the last one (alternating by level).
+// Counters of the rank launches.
 struct alignas(128) RankWord {
     uint64_t v;
     uint64_t pad[15];
 };
 struct RankSync {
-    uint64_t flag[2][kRankMaxGroups];
     uint32_t lv[kMaxPhases];     // points of the fronts taken off first
     int32_t left[kMaxPhases];    // points left after each of them
     uint32_t chunk[kMaxPhases][kPairsMaxN / kRankThreads];   // the same of a compaction chunk
@@ -108,10 +105,11 @@ struct PairInst {
     uint32_t poolUnits;       // units of one pool
     int32_t *din, *dout;      // [N] degrees in final order (zeroed)
     int32_t *runs2, *rune2, *din2;     // [N] other buffers of the phases
-    uint32_t *low;            // [2][2 * nB][16] smallest keys of the unranked points of a
-                              // 64-point group, double buffered by level
+    uint32_t *low;            // [2 * nB][16] smallest keys of the points of a 64-point group
     int32_t lowK;             // objectives whose smallest keys the rank launches look at
-    uint64_t *U;              // [2][2 * nB] unranked points, double buffered by level
+    uint64_t *ex;             // [2][M + 2][2 * nBpad] of the unranked points of a 64-point group:
+                              // smallest keys, and their set in two halves; [31:0] of a word,
+                              // [63:32] the level, double buffered by level (zeroed)
     uint16_t *pos;            // [nB * 128] block of a point's witness
     uint4 *wit;               // [nB * 128] its dominators in that block
     RankSync *sync;           // (zeroed)

@@ -24,8 +24,11 @@ namespace nsga3 {
 // Small problems take one work-group, others one persistent launch with a
 // barrier per level; the points' state is in registers where a wave owns one
 // group.  The unranked sets go from level to level through global memory by
-// device-scope stores and loads (one work-group: through LDS).  Large problems
-// come here without their first fronts (see pairs.h).
+// device-scope stores and loads (one work-group: through LDS); every 64-bit
+// word carries its level, so a work-group waits for the words themselves and
+// not for a barrier after them (a level of N = 20k, M = 3 9.6 us with flags
+// behind the stores).  Large problems come here without their first fronts
+// (see pairs.h).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint64_t agent_ld(const uint64_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -70,6 +73,7 @@ struct RankLds {
     uint64_t *U;      // [2 * nBpad] unranked points
     uint64_t *blkU;   // [nBpad / 64] blocks with any
     uint64_t *rows;   // [slots][nBpad / 64] stored blocks of the slot's tile
+    uint32_t *idx;    // [slots][nBpad] their mask units, where they fit (or null)
     uint64_t *open;   // [slots] points that lost their witness
     uint64_t *left;   // [slots] those that have not found another
     uint32_t *low;    // [lowK][nBpad] smallest keys of a block's unranked points
@@ -82,6 +86,9 @@ struct RankLds {
     uint4 *wit;       // [slots][64] witness masks and blocks (one work-group, several
     uint16_t *pos;    // slots per wave)
 };
+
+// LDS words for the mask units of a work-group's rows.
+constexpr int kRankIdxWords = 12288;
 
 __host__ __device__ inline size_t rank_lds_words(int nBp, int M, int lowK, int slots, int solo,
                                                  RankLds *S, uint32_t *base) {
@@ -97,11 +104,14 @@ __host__ __device__ inline size_t rank_lds_words(int nBp, int M, int lowK, int s
     const size_t oH = take(solo ? 2 * (size_t)nBp * M : 0), oX = take((size_t)slots * M);
     const size_t oT = take(128 * (size_t)slots), oN = take(slots), oI = take(slots);
     const bool own = solo && slots > kRankWaves;
+    const bool near = slots * nBp <= kRankIdxWords;
+    const size_t oQ = take(near ? (size_t)slots * nBp : 0);
     const size_t oW = take(own ? 256 * (size_t)slots : 0), oP = take(own ? 32 * (size_t)slots : 0);
     if (S) {
         S->U = reinterpret_cast<uint64_t *>(base + oU);
         S->blkU = reinterpret_cast<uint64_t *>(base + oB);
         S->rows = reinterpret_cast<uint64_t *>(base + oR);
+        S->idx = near ? base + oQ : nullptr;
         S->open = reinterpret_cast<uint64_t *>(base + oO);
         S->left = S->open + slots;
         S->low = base + oL;
@@ -126,6 +136,13 @@ struct RankPoint {
     uint32_t i;          // point index
     int32_t din, dout;   // degrees
 };
+
+// Mask units of word wd of a slot's row, one a lane.
+__device__ __forceinline__ uint32_t row_units(const PairInst &I, const RankLds &S, int32_t slot,
+                                              int32_t h, int32_t wd) {
+    const int32_t b = wd * 64 + (int32_t)lane_id();
+    return S.idx ? S.idx[slot * I.nBpad + b] : I.idx[(size_t)(h >> 1) * I.nBpad + b];
+}
 
 // More batches than a word has blocks (a batch may hold a single block).
 constexpr int kWholeWord = 1 << 20;
@@ -202,6 +219,13 @@ __device__ __forceinline__ int32_t scan_word(const PairInst &I, const RankLds &S
     }
     if (hb >= 0) hit = (uint64_t)(uint32_t)((w << 6) + hb + 1) << 32 | hu;
     return t ? bound : w << 6;
+}
+
+// Word of the exchange before level rel: field f (keys, then the set's halves)
+// of group h.
+template <int M>
+__device__ __forceinline__ size_t ex_word(const PairInst &I, int32_t rel, int32_t f, int32_t h) {
+    return ((size_t)(rel & 1) * (M + 2) + f) * 2 * I.nBpad + h;
 }
 
 // One level for the slots of a work-group; `rounds` slots per wave, at most
@@ -289,7 +313,7 @@ __device__ __forceinline__ uint32_t rank_level(const PairInst &I, int32_t level,
             int32_t wd = (bound + 63) / 64 - 1;  // the highest word with blocks
             while (wd >= 0 && uniform(row[wd] & S.blkU[wd]) == 0ull) --wd;
             if (wd < 0) continue;
-            const uint32_t iv = I.idx[(size_t)(h >> 1) * I.nBpad + wd * 64 + lane];
+            const uint32_t iv = row_units(I, S, slot, h, wd);
             uint32_t xm[M];
 #pragma unroll
             for (int k = 0; k < M; ++k) xm[k] = S.xm[slot * M + k];
@@ -315,7 +339,7 @@ __device__ __forceinline__ uint32_t rank_level(const PairInst &I, int32_t level,
             const int32_t bound = uniform(S.bound[slot]);
             const uint64_t *row = S.rows + (size_t)slot * nW;
             if (bound <= wd << 6 || uniform(row[wd] & S.blkU[wd]) == 0ull) continue;
-            const uint32_t iv = I.idx[(size_t)(h >> 1) * I.nBpad + wd * 64 + lane];
+            const uint32_t iv = row_units(I, S, slot, h, wd);
             uint32_t xm[M];
 #pragma unroll
             for (int k = 0; k < M; ++k) xm[k] = S.xm[slot * M + k];
@@ -369,6 +393,7 @@ __device__ __forceinline__ uint32_t rank_level(const PairInst &I, int32_t level,
             I.pos[at] = (uint16_t)nB;
             I.wit[at] = make_uint4(0, 0, 0, 0);
         }
+        uint32_t keep_low = 0u;
         if (un) {
             // smallest keys of what stays
             uint32_t low = kKeep ? P.low : 0u;
@@ -382,82 +407,97 @@ __device__ __forceinline__ uint32_t rank_level(const PairInst &I, int32_t level,
                 }
                 if (kKeep) P.low = low;
             } else if (!kKeep && lane < M) {
-                low = kSolo && rel > 0
-                          ? S.half[h * M + lane]
-                          : __hip_atomic_load(&I.low[((size_t)(rel & 1) * 2 * nB + h) * 16 + lane],
-                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (rel == 0)
+                    low = I.low[(size_t)h * 16 + lane];
+                else
+                    low = kSolo ? S.half[h * M + lane]
+                                : (uint32_t)agent_ld(&I.ex[ex_word<M>(I, rel, lane, h)]);
             }
-            if (kSolo) {
-                if (lane < M) S.half[h * M + lane] = low;
-            } else if (lane < I.lowK) {
-                __hip_atomic_store(&I.low[((size_t)((rel + 1) & 1) * 2 * nB + h) * 16 + lane], low,
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+            if (kSolo && lane < M) S.half[h * M + lane] = low;
+            keep_low = low;
         }
-        if (lane == 0) {
-            if (kSolo)
-                S.U[h] = un & ~front;
-            else
-                __hip_atomic_store(&I.U[(size_t)((rel + 1) & 1) * 2 * nB + h], un & ~front,
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (kSolo) {
+            if (lane == 0) S.U[h] = un & ~front;
+        } else if (lane < M + 2 && (lane >= M || lane < I.lowK)) {
+            const uint64_t u = un & ~front;
+            const uint32_t v = lane < M ? keep_low : (uint32_t)(lane == M ? u : u >> 32);
+            __hip_atomic_store(&I.ex[ex_word<M>(I, rel + 1, lane, h)],
+                               (uint64_t)(uint32_t)(rel + 1) << 32 | v, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
         }
     }
     return fresh;
 }
 
 // The unranked set of the rel-th level into LDS (the first: every point).
+// Returns this thread's share of it; s_f is set where a work-group's words never
+// came.
 template <int M, bool kSolo>
-__device__ __forceinline__ void load_unranked(const PairInst &I, int32_t rel, const RankLds &S) {
-    const int32_t N = I.N, nB = I.nB, nBp = I.nBpad;
-    for (int32_t a0 = 0; a0 < nBp; a0 += kRankThreads) {
-        const int32_t a = a0 + (int32_t)threadIdx.x;
-        uint64_t u0 = 0, u1 = 0;
-        if (a < nB) {
+__device__ __forceinline__ uint32_t load_unranked(const PairInst &I, int32_t rel, const RankLds &S,
+                                                  uint32_t &s_f) {
+    const int32_t nBp = I.nBpad, nH = 2 * I.nB;
+    uint32_t mine = 0;
+    for (int32_t h0 = 0; h0 < 2 * nBp; h0 += kRankThreads) {
+        const int32_t h = h0 + (int32_t)threadIdx.x;  // a thread takes a 64-point group
+        uint64_t u = 0;
+        uint32_t z[M];
+#pragma unroll
+        for (int k = 0; k < M; ++k) z[k] = ~0u;
+        if (h < nH) {
             if (rel == 0) {
-                const int32_t n = N - a * kWBlk;
-                u0 = n >= 64 ? ~0ull : ((1ull << n) - 1ull);
-                u1 = n >= 128 ? ~0ull : (n <= 64 ? 0ull : ((1ull << (n - 64)) - 1ull));
+                const int32_t n = I.N - h * kWave;
+                u = n >= kWave ? ~0ull : (n <= 0 ? 0ull : (1ull << n) - 1ull);
             } else if (kSolo) {
-                u0 = S.U[2 * a];
-                u1 = S.U[2 * a + 1];
+                u = S.U[h];
+#pragma unroll
+                for (int k = 0; k < M; ++k) z[k] = S.half[h * M + k];
             } else {
-                const uint64_t *U = I.U + (size_t)(rel & 1) * 2 * nB;
-                u0 = agent_ld(&U[2 * a]);
-                u1 = agent_ld(&U[2 * a + 1]);
-            }
-            if (!kSolo || rel == 0) {
-                S.U[2 * a] = u0;
-                S.U[2 * a + 1] = u1;
-            }
-            if (rel > 0) {  // (front 0 looks at no block)
-                uint64_t y0[(M + 1) / 2], y1[(M + 1) / 2];
-                const uint64_t *L = reinterpret_cast<const uint64_t *>(
-                    I.low + ((size_t)(rel & 1) * 2 * nB + 2 * a) * 16);
-                if (!kSolo) {  // (every load before the first use)
+                const uint64_t *e = I.ex + ex_word<M>(I, rel, 0, h);
+                uint32_t spins = 0;
+                while (true) {  // (every load before the first use)
+                    uint64_t y[M + 2];
+                    uint32_t off = 0;
 #pragma unroll
-                    for (int k = 0; k < M; k += 2) {
-                        const bool in = k < I.lowK;
-                        y0[k / 2] = in ? agent_ld(&L[k / 2]) : 0ull;
-                        y1[k / 2] = in ? agent_ld(&L[8 + k / 2]) : 0ull;
-                    }
-                }
+                    for (int k = 0; k < M + 2; ++k)
+                        y[k] = k >= M || k < I.lowK ? agent_ld(&e[(size_t)k * 2 * nBp])
+                                                    : (uint64_t)(uint32_t)rel << 32;
 #pragma unroll
-                for (int k = 0; k < M; ++k) {
-                    uint32_t z0, z1;
-                    if (kSolo) {
-                        z0 = S.half[(2 * a) * M + k];
-                        z1 = S.half[(2 * a + 1) * M + k];
-                    } else {
-                        z0 = (uint32_t)(y0[k / 2] >> (32 * (k & 1)));
-                        z1 = (uint32_t)(y1[k / 2] >> (32 * (k & 1)));
+                    for (int k = 0; k < M + 2; ++k) off |= (uint32_t)(y[k] >> 32) ^ (uint32_t)rel;
+                    u = (uint32_t)y[M] | y[M + 1] << 32;
+#pragma unroll
+                    for (int k = 0; k < M; ++k) z[k] = (uint32_t)y[k];
+                    if (off == 0u) break;
+                    if (++spins > (1u << 26)) {  // a work-group never arrived
+                        atomicOr(&I.sc->err, (uint32_t)kErrBarrierTimeout);
+                        s_f = ~0u;
+                        break;
                     }
-                    if (k < I.lowK) S.low[k * nBp + a] = min(u0 ? z0 : ~0u, u1 ? z1 : ~0u);
                 }
             }
         }
-        const uint64_t m = ballot((u0 | u1) != 0ull);
-        if (lane_id() == 0 && a < nBp) S.blkU[a >> 6] = m;
+        if (h < 2 * nBp) {  // (whole waves)
+            if (!kSolo || rel == 0) S.U[h] = u;
+            if (rel > 0) {  // (front 0 looks at no block)
+#pragma unroll
+                for (int k = 0; k < M; ++k) {
+                    const uint32_t v = u ? z[k] : ~0u;
+                    const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0xb1,
+                                                                             0xf, 0xf, false);
+                    if (k < I.lowK && (h & 1) == 0) S.low[k * nBp + (h >> 1)] = min(v, o);
+                }
+            }
+            uint64_t m = ballot(u != 0ull);
+            m = (m | m >> 1) & 0x5555555555555555ull;  // a bit per block, then together
+            m = (m | m >> 1) & 0x3333333333333333ull;
+            m = (m | m >> 2) & 0x0f0f0f0f0f0f0f0full;
+            m = (m | m >> 4) & 0x00ff00ff00ff00ffull;
+            m = (m | m >> 8) & 0x0000ffff0000ffffull;
+            m = m | m >> 16;
+            if (lane_id() == 0) reinterpret_cast<uint32_t *>(S.blkU)[h >> 6] = (uint32_t)m;
+            mine += (uint32_t)__popcll(u);
+        }
     }
+    return mine;
 }
 
 // Stored-block rows of the work-group's slots.
@@ -468,6 +508,11 @@ __device__ __forceinline__ void load_rows(const PairInst &I, int32_t g, int32_t 
         const int32_t tile = (q / nW * G + g) >> 1;
         S.rows[q] = tile < I.nB ? I.nz[(size_t)tile * nW + q % nW] : 0ull;
     }
+    if (S.idx)
+        for (int32_t q = (int32_t)threadIdx.x; q < slots * I.nBpad; q += kRankThreads) {
+            const int32_t tile = (q / I.nBpad * G + g) >> 1;
+            S.idx[q] = tile < I.nB ? I.idx[(size_t)tile * I.nBpad + q % I.nBpad] : 0u;
+        }
 }
 
 // Points of the fronts before level0.
@@ -517,52 +562,47 @@ __device__ __forceinline__ void rank_levels(PairInst I, int32_t level0, uint32_t
         if (f) close(level, f);
     }
     if (I.N == 0) return;
+    if (tid == 0) s_f = 0;
+    uint32_t prev = 0;  // points unranked before the last level
+    __syncthreads();
     for (int32_t level = level0;; ++level) {
         if (tid == 0) s_n = 0;
-        load_unranked<M, kSolo>(I, level - level0, S);
+        const uint32_t mine = load_unranked<M, kSolo>(I, level - level0, S, s_f);
+        if (!kSolo) {
+            const uint32_t n = wave_sum(mine);
+            if (lane == 0) s_new[w] = n;
+        }
+        lds_wait();
         __syncthreads();
+        if (!kSolo) {
+            if (s_f == ~0u) return;
+            uint32_t left = 0;
+            for (int q = 0; q < kRankWaves; ++q) left += s_new[q];
+            if (level > level0) {
+                close(level - 1, prev - left);
+                if (left == 0) return;
+                if (left == prev) {  // impossible for a partial order
+                    if (tid == 0) atomicOr(&I.sc->err, (uint32_t)kErrInternal);
+                    return;
+                }
+            }
+            prev = left;
+        }
         const uint32_t fresh = rank_level<M, kKeep, kSolo>(I, level, level0, g, G, rounds,
                                                              rounds * kRankWaves, S, P, &s_n);
-        if (lane == 0) s_new[w] = fresh;
-        if (!kSolo) __builtin_amdgcn_s_waitcnt(0);  // this wave's part of the next set is written
+        if (kSolo && lane == 0) s_new[w] = fresh;
+        lds_wait();
         __syncthreads();
-        uint32_t f = 0;
         if (kSolo) {
+            uint32_t f = 0;
             for (int q = 0; q < kRankWaves; ++q) f += s_new[q];
             __syncthreads();  // s_new is free again
-        } else {
-            // one wave: this work-group's flag, then everyone's
-            if (w == 0) {
-                uint32_t n = lane < kRankWaves ? s_new[lane] : 0u;
-                n = wave_sum(n);
-                uint64_t *flag = I.sync->flag[(level - level0) & 1];
-                const uint32_t tag = (uint32_t)(level - level0 + 1);
-                if (lane == 0)
-                    __hip_atomic_store(&flag[g], (uint64_t)tag << 32 | n, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-                uint64_t v = 0, spins = 0;
-                while (true) {
-                    v = lane < G ? agent_ld(&flag[lane]) : (uint64_t)tag << 32;
-                    if (ballot((uint32_t)(v >> 32) != tag) == 0ull) break;
-                    __builtin_amdgcn_s_sleep(1);
-                    if (++spins > (1ull << 26)) {  // a work-group never arrived
-                        if (lane == 0) atomicOr(&I.sc->err, (uint32_t)kErrBarrierTimeout);
-                        v = ~0ull;
-                        break;
-                    }
-                }
-                const uint32_t all = wave_sum((uint32_t)v);
-                if (lane == 0) s_f = ballot(v == ~0ull) ? ~0u : all;
+            close(level, f);
+            if (done >= total) return;
+            if (f == 0) {  // impossible for a partial order
+                if (tid == 0) atomicOr(&I.sc->err, (uint32_t)kErrInternal);
+                return;
             }
-            __syncthreads();
-            f = s_f;
-            if (f == ~0u) return;
-        }
-        close(level, f);
-        if (done >= total) return;
-        if (f == 0) {  // impossible for a partial order
-            if (tid == 0) atomicOr(&I.sc->err, (uint32_t)kErrInternal);
-            return;
         }
     }
 }
@@ -606,8 +646,10 @@ static hipError_t launch_ranks(const PairInst &I, int phases, hipStream_t s) {
     const int rounds = rank_rounds(I, I.groups);
     const dim3 gr((unsigned)I.groups), th(kRankThreads);
     if (phases > 0) {
-        hipLaunchKernelGGL(k_ranks_rest<M>, gr, th, ranks_lds_bytes(I, rounds * kRankWaves, false),
-                           s, I, phases);
+        // (fewer blocks may bring the mask units into LDS)
+        hipLaunchKernelGGL(k_ranks_rest<M>, gr, th,
+                           ranks_lds_bytes(I, rounds * kRankWaves, false) + 4 * kRankIdxWords, s, I,
+                           phases);
     } else if (I.groups == 1) {
         const size_t lds = ranks_lds_bytes(I, rounds * kRankWaves, true);
         if (rounds == 1)
