@@ -58,6 +58,7 @@ struct DevScalars {
     int32_t level_V;           // niching threshold level
     int32_t ref_thr;           // niching threshold reference
     uint32_t n_selected;       // number of selection flags set (must equal K)
+    uint32_t ext_done;         // work-groups whose extreme-point partials are written
     double a[16];              // intercepts
     double z[16];              // ideal point (float64 of the float32 minimum)
     int32_t fb[1 + kProfLevels];  // front count, then points left after each level

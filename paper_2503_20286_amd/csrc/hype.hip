@@ -490,8 +490,7 @@ hipError_t run_hype(const HypeViews &v, hipStream_t st) {
         hipLaunchKernelGGL(k_hv_select, dim3(1), dim3(1024), 0, st, v.skey, v.sval, v.selflag, hs,
                            v.sc);
     }
-    compact_flags(v.selflag, N, v.selected, v.n, v.temp, &v.sc->n_selected, st);
-    if (v.info) run_finalize(v.info, v.n, v.sc, st);
+    run_compact(v.selflag, N, v.selected, v.n, v.temp, v.sc, v.info, st);
     e = hipGetLastError();
     return e;
 }

@@ -68,22 +68,38 @@ __device__ __forceinline__ double ideal(const DevScalars *sc, int k) {
 }
 
 // ---------------------------------------------------------------------------
-// a4: extreme-point partials per block (ASF argmin per axis) and nadir partials
+// a4: extreme-point partials per work-group (ASF argmin per axis) and nadir
+// partials; the last work-group to finish takes a5: reduces the partials,
+// builds E, solves E b = 1 (intercepts / fallback).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kNormThreads) void k_extreme_partial(
-    const float *__restrict__ objs, int64_t N, int M, const int32_t *__restrict__ rank,
-    const DevScalars *__restrict__ sc, double *__restrict__ p_asf, int32_t *__restrict__ p_idx,
-    double *__restrict__ p_nad) {
-    __shared__ double s_asf[kNormThreads / kWave][16];
-    __shared__ int32_t s_idx[kNormThreads / kWave][16];
-    __shared__ double s_nad[kNormThreads / kWave][16];
+// (value, index) minimum and maximum over a wave.
+__device__ __forceinline__ void fold_extreme(double &b, int32_t &bi, double &nd) {
+    for (int o = 32; o > 0; o >>= 1) {
+        const double ob = __shfl_xor(b, o, 64);
+        const int32_t oi = __shfl_xor(bi, o, 64);
+        if (ob < b || (ob == b && oi < bi)) { b = ob; bi = oi; }
+        const double on = __shfl_xor(nd, o, 64);
+        nd = on > nd ? on : nd;
+    }
+}
+
+template <int M>
+__global__ __launch_bounds__(kNormThreads) void k_extreme(
+    const float *__restrict__ objs, int64_t N, const int32_t *__restrict__ rank,
+    DevScalars *__restrict__ sc, double *p_asf, int32_t *p_idx, double *p_nad) {
+    constexpr int kW = kNormThreads / kWave;
+    __shared__ double s_asf[kW][M], s_nad[kW][M];
+    __shared__ int32_t s_idx[kW][M];
+    __shared__ int32_t s_e[M];
+    __shared__ double s_nadir[M];
+    __shared__ uint32_t s_last;
     if (sc->err) return;
     const int32_t l = sc->last_front;
-    double z[16], best[16], nad[16];
-    int32_t bidx[16];
+    double z[M], best[M], nad[M];
+    int32_t bidx[M];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        z[k] = k < M ? ideal(sc, k) : 0.0;
+    for (int k = 0; k < M; ++k) {
+        z[k] = ideal(sc, k);
         best[k] = DBL_MAX;
         bidx[k] = 0x7fffffff;
         nad[k] = 0.0;
@@ -91,26 +107,16 @@ __global__ __launch_bounds__(kNormThreads) void k_extreme_partial(
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += stride) {
         if (rank[i] > l) continue;
-        double g[16];
+        double g[M];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) g[k] = k < M ? (double)objs[i * M + k] - z[k] : 0.0;
-        asf_fold<16>(g, M, (int32_t)i, best, bidx, nad);
+        for (int k = 0; k < M; ++k) g[k] = (double)objs[i * M + k] - z[k];
+        asf_fold<M>(g, M, (int32_t)i, best, bidx, nad);
     }
     const int w = threadIdx.x / kWave;
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        if (j >= M) continue;
-        double b = best[j];
-        int32_t bi = bidx[j];
-        double nd = nad[j];
-        for (int o = 32; o > 0; o >>= 1) {
-            const double ob = __shfl_xor(b, o, 64);
-            const int32_t oi = __shfl_xor(bi, o, 64);
-            if (ob < b || (ob == b && oi < bi)) { b = ob; bi = oi; }
-            const double on = __shfl_xor(nd, o, 64);
-            nd = on > nd ? on : nd;
-        }
-        if (lane_id() == 0) { s_asf[w][j] = b; s_idx[w][j] = bi; s_nad[w][j] = nd; }
+    for (int j = 0; j < M; ++j) {
+        fold_extreme(best[j], bidx[j], nad[j]);
+        if (lane_id() == 0) { s_asf[w][j] = best[j]; s_idx[w][j] = bidx[j]; s_nad[w][j] = nad[j]; }
     }
     __syncthreads();
     if ((int)threadIdx.x < M) {
@@ -118,76 +124,39 @@ __global__ __launch_bounds__(kNormThreads) void k_extreme_partial(
         double b = s_asf[0][j];
         int32_t bi = s_idx[0][j];
         double nd = s_nad[0][j];
-        for (int q = 1; q < kNormThreads / kWave; ++q) {
+        for (int q = 1; q < kW; ++q) {
             if (s_asf[q][j] < b || (s_asf[q][j] == b && s_idx[q][j] < bi)) { b = s_asf[q][j]; bi = s_idx[q][j]; }
             nd = s_nad[q][j] > nd ? s_nad[q][j] : nd;
         }
         p_asf[blockIdx.x * M + j] = b;
         p_idx[blockIdx.x * M + j] = bi;
         p_nad[blockIdx.x * M + j] = nd;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// a5: reduce the partials, build E, solve E b = 1, intercepts / fallback.
-// One block of kSolveThreads: every thread folds its share of the partials
-// for all axes, the waves fold across lanes, wave 0 across waves.
-// ---------------------------------------------------------------------------
-constexpr int kSolveThreads = 1024;
-
-template <int M>
-__global__ __launch_bounds__(kSolveThreads) void k_solve(const float *__restrict__ objs, int nparts,
-                                                         const double *__restrict__ p_asf,
-                                                         const int32_t *__restrict__ p_idx,
-                                                         const double *__restrict__ p_nad,
-                                                         DevScalars *__restrict__ sc) {
-    constexpr int kW = kSolveThreads / kWave;
-    __shared__ double w_asf[kW][16], w_nad[kW][16];
-    __shared__ int32_t w_idx[kW][16];
-    __shared__ int32_t s_e[16];
-    __shared__ double s_nadir[16];
-    if (sc->err) return;
-    const int lane = (int)lane_id(), wid = (int)threadIdx.x / kWave;
-    for (int j = 0; j < M; ++j) {
-        double b = DBL_MAX;
-        int32_t bi = 0x7fffffff;
-        double nd = 0.0;
-        for (int q = threadIdx.x; q < nparts; q += kSolveThreads) {
-            const double a = p_asf[q * M + j];
-            const int32_t ai = p_idx[q * M + j];
-            if (a < b || (a == b && ai < bi)) { b = a; bi = ai; }
-            const double n = p_nad[q * M + j];
-            nd = n > nd ? n : nd;
-        }
-        for (int o = 32; o > 0; o >>= 1) {
-            const double ob = __shfl_xor(b, o, 64);
-            const int32_t oi = __shfl_xor(bi, o, 64);
-            if (ob < b || (ob == b && oi < bi)) { b = ob; bi = oi; }
-            const double on = __shfl_xor(nd, o, 64);
-            nd = on > nd ? on : nd;
-        }
-        if (lane == 0) { w_asf[wid][j] = b; w_idx[wid][j] = bi; w_nad[wid][j] = nd; }
+        __threadfence();
     }
     __syncthreads();
-    if (wid != 0) return;
-    for (int j = 0; j < M; ++j) {
-        double b = lane < kW ? w_asf[lane][j] : DBL_MAX;
-        int32_t bi = lane < kW ? w_idx[lane][j] : 0x7fffffff;
-        double nd = lane < kW ? w_nad[lane][j] : 0.0;
-        for (int o = 32; o > 0; o >>= 1) {
-            const double ob = __shfl_xor(b, o, 64);
-            const int32_t oi = __shfl_xor(bi, o, 64);
-            if (ob < b || (ob == b && oi < bi)) { b = ob; bi = oi; }
-            const double on = __shfl_xor(nd, o, 64);
-            nd = on > nd ? on : nd;
+    if (threadIdx.x == 0) s_last = atomicAdd(&sc->ext_done, 1u) + 1u == gridDim.x ? 1u : 0u;
+    __syncthreads();
+    if (!s_last) return;
+    __threadfence();  // every work-group's partials
+    // a wave folds every kW-th axis
+    for (int j = w; j < M; j += kW) {
+        double b = DBL_MAX, nd = 0.0;
+        int32_t bi = 0x7fffffff;
+        for (int q = (int)lane_id(); q < (int)gridDim.x; q += kWave) {
+            const double x = __hip_atomic_load(&p_asf[q * M + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const int32_t xi = __hip_atomic_load(&p_idx[q * M + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const double xn = __hip_atomic_load(&p_nad[q * M + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (x < b || (x == b && xi < bi)) { b = x; bi = xi; }
+            nd = xn > nd ? xn : nd;
         }
-        if (lane == 0) { s_e[j] = bi; s_nadir[j] = nd; }
+        fold_extreme(b, bi, nd);
+        if (lane_id() == 0) { s_e[j] = bi; s_nadir[j] = nd; }
     }
-    double z[M], a[M];
-#pragma unroll
-    for (int k = 0; k < M; ++k) z[k] = ideal(sc, k);
+    __syncthreads();
+    if (w != 0) return;
+    double a[M];
     const int fb = solve_intercepts_wave<M>(objs, s_e, s_nadir, z, a);
-    if (lane != 0) return;
+    if (lane_id() != 0) return;
     for (int k = 0; k < M; ++k) {
         sc->z[k] = z[k];
         sc->a[k] = a[k];
@@ -197,43 +166,146 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(const float *__restrict
 
 // ---------------------------------------------------------------------------
 // a6/a7: association (float32 screening, float64 re-scoring) and counts.
-// The reference loop is uniform, so the float32 unit references stream
-// through scalar loads.
 // ---------------------------------------------------------------------------
+// References that pass the screen of a lane's point wait in a list of up to
+// four (16 bits each) and are re-scored together: a wave then goes through the
+// float64 distance as often as its busiest lane needs it, not once for every
+// reference that some lane needs (N = 200k, M = 5, 210 references: 53 us).
+// The two smallest distances and the lowest index of the smallest do not
+// depend on the order.
 template <int M>
+struct Rescore {
+    double d1 = DBL_MAX, d2 = DBL_MAX;
+    int32_t best = 0;
+    uint64_t list = 0;
+    int n = 0;
+    __device__ __forceinline__ void add(bool pass, int j) {
+        if (pass) {
+            list = list << 16 | (uint64_t)j;
+            ++n;
+        }
+    }
+    __device__ __forceinline__ bool full() const { return ballot(n == 4) != 0ull; }
+    __device__ __forceinline__ void run(const double (&fp)[M], const double *__restrict__ rhat64) {
+        while (ballot(n > 0)) {
+            if (n > 0) {
+                const int32_t j = (int32_t)(list & 0xffffu);
+                list >>= 16;
+                --n;
+                const double d = line_distance<M>(fp, rhat64 + (int64_t)j * M);
+                if (d < d1 || (d == d1 && j < best)) { d2 = d1; d1 = d; best = j; }
+                else if (d < d2) { d2 = d; }
+            }
+        }
+    }
+    // with the lane that holds other references of the same point
+    __device__ __forceinline__ void merge(int o) {
+        const double e1 = __shfl_xor(d1, o, 64), e2 = __shfl_xor(d2, o, 64);
+        const int32_t eb = __shfl_xor(best, o, 64);
+        if (e1 < d1 || (e1 == d1 && eb < best)) {
+            d2 = fmin(d1, e2);
+            d1 = e1;
+            best = eb;
+        } else {
+            d2 = fmin(d2, e1);
+        }
+    }
+};
+
+// S adjacent lanes share a point, each with every S-th reference, which are
+// staged in LDS; one lane a point (S = 1) reads them through scalar loads.
+constexpr int kAssocFloats = 4096;
+
+template <int M, int S>
 __global__ __launch_bounds__(kNormThreads) void k_associate(
     const float *__restrict__ objs, int64_t N, const int32_t *__restrict__ rank,
     const double *__restrict__ rhat64, const float *__restrict__ rhat32, int H,
     int32_t *__restrict__ niche, float *__restrict__ dist, double *__restrict__ dist64,
     int32_t *__restrict__ rho, int32_t *__restrict__ bcount, uint8_t *__restrict__ selflag,
     DevScalars *__restrict__ sc) {
+    constexpr int kRefs = kAssocFloats / M / S * S;  // references staged at once
     __shared__ int32_t hist[2 * kLdsNicheRefs];
+    __shared__ __attribute__((aligned(16))) float lr[S > 1 ? kRefs * M : 1];
     if (sc->err) return;
-    const float *__restrict__ R = rhat32;  // uniform reads: scalar loads
     const int32_t l = sc->last_front;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int sub = S > 1 ? (int)threadIdx.x % S : 0;
+    const int64_t i = (int64_t)blockIdx.x * (kNormThreads / S) + (int)threadIdx.x / S;
     const int32_t r = i < N ? rank[i] : 0x7fffffff;
-    int cls = -1;
-    int32_t best = 0;
-    if (r <= l) {
-        double fp[M];
-        float y[M];
-        const float l1 = normalise_point<M>(objs + i * M, sc->z, sc->a, fp, y);
-        double d1, d2;
-        associate_point<M>(fp, y, l1, R, rhat64, H, best, d1, d2);
-        niche[i] = best;
-        if (dist) dist[i] = (float)d1;
-        dist64[i] = d1;
-        if (near_tie(d1, d2)) atomicAdd(&sc->near_ties, 1);
-        cls = r < l ? 0 : 1;
-        selflag[i] = r < l ? 1 : 0;
-    } else if (i < N) {
-        niche[i] = -1;
-        if (dist) dist[i] = -1.0f;
-        dist64[i] = -1.0;
-        selflag[i] = 0;
+    const bool mine = r <= l && i < N;
+    const bool any = ballot(mine) != 0ull;
+    double fp[M];
+    float y[M];
+    float l1 = 0.0f;
+#pragma unroll
+    for (int k = 0; k < M; ++k) { fp[k] = 0.0; y[k] = 0.0f; }
+    if (mine) l1 = normalise_point<M>(objs + i * M, sc->z, sc->a, fp, y);
+    auto stage = [&](int c0) {
+        if (S == 1) return;
+        const int n = (H - c0 < kRefs ? H - c0 : kRefs) * M;
+        __syncthreads();
+        for (int q = threadIdx.x; q < n; q += kNormThreads) lr[q] = rhat32[(int64_t)c0 * M + q];
+        __syncthreads();
+    };
+    float smax = -FLT_MAX;
+    for (int c0 = 0; c0 < H; c0 += kRefs) {
+        stage(c0);
+        const int n = H - c0 < kRefs ? H - c0 : kRefs;
+        if (any) {
+            int j = sub;
+            for (; j + 3 * S < n; j += 4 * S) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    smax = fmaxf(smax, screen_dot<M>(y, S > 1 ? lr + (j + u * S) * M
+                                                              : rhat32 + (c0 + j + u) * M));
+            }
+            for (; j < n; j += S)
+                smax = fmaxf(smax, screen_dot<M>(y, S > 1 ? lr + j * M : rhat32 + (c0 + j) * M));
+        }
     }
-    niche_count_block(H, cls, best, rho, bcount, hist);
+    for (int o = 1; o < S; o <<= 1) smax = fmaxf(smax, __shfl_xor(smax, o, 64));
+    const float thr = smax - fp32_band<M>(l1);
+    Rescore<M> R;
+    for (int c0 = 0; c0 < H; c0 += kRefs) {
+        if (H > kRefs) stage(c0);
+        const int n = H - c0 < kRefs ? H - c0 : kRefs;
+        if (any) {
+            for (int jb = 0; jb < n; jb += 4 * S) {
+                bool pass[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int j = jb + u * S + sub;
+                    const int jc = j < n ? j : n - 1;
+                    const float s = screen_dot<M>(y, S > 1 ? lr + jc * M : rhat32 + (c0 + jc) * M);
+                    pass[u] = mine && j < n && !(s < thr);
+                }
+                if (!ballot(pass[0] || pass[1] || pass[2] || pass[3])) continue;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    R.add(pass[u], c0 + jb + u * S + sub);
+                    if (R.full()) R.run(fp, rhat64);
+                }
+            }
+        }
+    }
+    R.run(fp, rhat64);
+    for (int o = 1; o < S; o <<= 1) R.merge(o);
+    int cls = -1;
+    if (sub == 0) {
+        if (mine) {
+            niche[i] = R.best;
+            if (dist) dist[i] = (float)R.d1;
+            dist64[i] = R.d1;
+            if (near_tie(R.d1, R.d2)) atomicAdd(&sc->near_ties, 1);
+            cls = r < l ? 0 : 1;
+            selflag[i] = r < l ? 1 : 0;
+        } else if (i < N) {
+            niche[i] = -1;
+            if (dist) dist[i] = -1.0f;
+            dist64[i] = -1.0;
+            selflag[i] = 0;
+        }
+    }
+    niche_count_block(H, cls, R.best, rho, bcount, hist);
 }
 
 // ---------------------------------------------------------------------------
@@ -333,8 +405,8 @@ __global__ __launch_bounds__(256) void k_associate_bf16(
     // |s_bf16 - s| <= (2 u + u^2) ||y||_2 + float32 rounding, u = 2^-8; doubled
     const float band = 2.0f * 1.01f * (0.0078125f + 0.000244f) * sqrtf(n2) + 1e-30f;
     const float thr = smax - band;
-    double d1 = DBL_MAX, d2 = DBL_MAX;
-    int32_t best = 0x7fffffff;
+    Rescore<M> R;
+    R.best = 0x7fffffff;
     for (int tl = 0; tl < ntiles; ++tl) {
         const typename Op::T aop = *reinterpret_cast<const typename Op::T *>(
             rhat16 + ((int64_t)(tl * 32 + (lane & 31)) * KP + KL * half));
@@ -343,23 +415,14 @@ __global__ __launch_bounds__(256) void k_associate_bf16(
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int j = tl * 32 + 8 * (v / 4) + 4 * half + (v % 4);
-            if (j >= H || acc[v] < thr || !active) continue;
-            const double d = line_distance<M>(fp, rhat64 + (int64_t)j * M);
-            if (d < d1 || (d == d1 && j < best)) { d2 = d1; d1 = d; best = j; }
-            else if (d < d2 || d == d2) { d2 = d < d2 ? d : d2; }
+            R.add(active && j < H && !(acc[v] < thr), j);
+            if (R.full()) R.run(fp, rhat64);
         }
     }
-    // merge with the lane holding the other 16 references of every tile
-    const double od1 = __shfl_xor(d1, 32, 64);
-    const double od2 = __shfl_xor(d2, 32, 64);
-    const int32_t obest = __shfl_xor(best, 32, 64);
-    if (od1 < d1 || (od1 == d1 && obest < best)) {
-        d2 = fmin(d1, od2);
-        d1 = od1;
-        best = obest;
-    } else {
-        d2 = fmin(d2, od1);
-    }
+    R.run(fp, rhat64);
+    R.merge(32);  // the lane with the other 16 references of every tile
+    const double d1 = R.d1, d2 = R.d2;
+    const int32_t best = R.best;
     int cls = -1;
     if (inrange && half == 0) {
         if (!active) {
@@ -576,10 +639,10 @@ __global__ __launch_bounds__(kRankGroup) void k_bucket_rank(int H, const int32_t
     if (lev < V || (lev == V && j < sc->ref_thr)) selflag[i] = 1;
 }
 
-__global__ void k_finalize(nsga3_info *info, int64_t K, const DevScalars *__restrict__ sc) {
-    if (threadIdx.x != 0) return;
+__device__ __forceinline__ void finalize_item(nsga3_info *info, int64_t K, int64_t n_selected,
+                                              const DevScalars *__restrict__ sc) {
     uint32_t e = sc->err;
-    if (e == 0 && (int64_t)sc->n_selected != K) e |= kErrInternal;
+    if (e == 0 && n_selected != K) e |= kErrInternal;
     nsga3_info v;
     v.status = e == 0 ? NSGA3_OK
                : (e & (kErrNonfiniteObj | kErrBadRef)) ? NSGA3_E_NONFINITE
@@ -593,6 +656,58 @@ __global__ void k_finalize(nsga3_info *info, int64_t K, const DevScalars *__rest
     v.reserved = (int32_t)e;
     *info = v;
 }
+
+__global__ void k_finalize(nsga3_info *info, int64_t K, const DevScalars *__restrict__ sc) {
+    if (threadIdx.x == 0) finalize_item(info, K, sc->n_selected, sc);
+}
+
+// The indices of the set flags (0 / 1, 16-byte aligned), at most cap of them,
+// and the call's info, by one work-group.
+__device__ __forceinline__ void compact_item(const uint8_t *flag, int64_t N, int32_t *out,
+                                             int64_t cap, uint32_t *lds, DevScalars *sc,
+                                             nsga3_info *info) {
+    uint32_t base = 0;
+    for (int64_t c0 = 0; c0 < N; c0 += 16 * (int64_t)blockDim.x) {
+        const int64_t p = c0 + 16 * (int64_t)threadIdx.x;
+        uint32_t v[4] = {0, 0, 0, 0};
+        if (p + 16 <= N) {
+            const uint4 f = *reinterpret_cast<const uint4 *>(flag + p);
+            v[0] = f.x; v[1] = f.y; v[2] = f.z; v[3] = f.w;
+        } else {
+            for (int q = 0; q < 16; ++q)
+                if (p + q < N) v[q / 4] |= (uint32_t)flag[p + q] << (8 * (q % 4));
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] &= 0x01010101u;
+        const uint32_t n = (uint32_t)(__popc(v[0]) + __popc(v[1]) + __popc(v[2]) + __popc(v[3]));
+        uint32_t tot;
+        uint32_t at = base + block_exclusive_scan(n, lds, &tot);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            for (uint32_t w = v[q]; w; w &= w - 1u) {
+                if ((int64_t)at < cap) out[at] = (int32_t)(p + 4 * q + __builtin_ctz(w) / 8);
+                ++at;
+            }
+        base += tot;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        sc->n_selected = base;
+        if (info) finalize_item(info, cap, base, sc);
+    }
+}
+
+__global__ __launch_bounds__(1024) void k_compact_one(const uint8_t *__restrict__ flag, int64_t N,
+                                                      int32_t *__restrict__ out, int64_t cap,
+                                                      DevScalars *__restrict__ sc,
+                                                      nsga3_info *__restrict__ info) {
+    __shared__ uint32_t lds[17];
+    compact_item(flag, N, out, cap, lds, sc, info);
+}
+
+// Up to this many flags one work-group compacts them: 16 bytes a thread and
+// step, where counts, scan, write and info are four launches.
+constexpr int64_t kCompactOne = 65536;
 
 // ---------------------------------------------------------------------------
 // One-shot niche selection (Sec. IV-A.5; the niche-selection steps of
@@ -710,8 +825,14 @@ size_t oneshot_temp_bytes(int64_t n) {
     return (size_t)(2 * (nb + 64) + 64) * sizeof(uint32_t);
 }
 
-void run_finalize(nsga3_info *info, int64_t K, const DevScalars *sc, hipStream_t s) {
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(64), 0, s, info, K, sc);
+void run_compact(const uint8_t *flag, int64_t N, int32_t *out, int64_t K, uint32_t *temp,
+                 DevScalars *sc, nsga3_info *info, hipStream_t s) {
+    if (N <= kCompactOne) {
+        hipLaunchKernelGGL(k_compact_one, dim3(1), dim3(1024), 0, s, flag, N, out, K, sc, info);
+        return;
+    }
+    compact_flags(flag, N, out, K, temp, &sc->n_selected, s);
+    if (info) hipLaunchKernelGGL(k_finalize, dim3(1), dim3(64), 0, s, info, K, sc);
 }
 
 int normalize_partial_blocks(int64_t N) {
@@ -721,18 +842,23 @@ int normalize_partial_blocks(int64_t N) {
     return (int)nb;
 }
 
+// Lanes that share a point of the association: few points leave the chip idle
+// while each lane walks the references alone, many pay for every lane's own
+// normalisation.  1 / 4 / 16 lanes: N = 200, M = 3 14.7 / 7.9 / 6.8 us; 2503, 5
+// 34.4 / 13.9 / 9.2; 10007, 2 14.7 / 10.0 / 14.1; 20000, 3 16.0 / 13.6 / 25.6;
+// 50021, 4 21.9 / 22.7 / 46.9; 200000, 5 52 / 79 / 143.
+static int assoc_split(int64_t N) { return N <= 4096 ? 16 : N <= 32768 ? 4 : 1; }
+
 hipError_t run_select_stage(const SelectViews &v, hipStream_t s) {
     const int64_t N = v.N;
     const int M = v.M;
     const int nparts = normalize_partial_blocks(N);
     v.mark();
-    hipLaunchKernelGGL(k_extreme_partial, dim3(nparts), dim3(kNormThreads), 0, s, v.objs, N, M,
-                       v.rank, v.sc, v.p_asf, v.p_idx, v.p_nad);
     switch (M) {
 #define NSGA3_CASE(m)                                                                               \
     case m:                                                                                         \
-        hipLaunchKernelGGL(k_solve<m>, dim3(1), dim3(kSolveThreads), 0, s, v.objs, nparts, v.p_asf, \
-                           v.p_idx, v.p_nad, v.sc);                                                 \
+        hipLaunchKernelGGL(k_extreme<m>, dim3(nparts), dim3(kNormThreads), 0, s, v.objs, N, v.rank, \
+                           v.sc, v.p_asf, v.p_idx, v.p_nad);                                        \
         break;
         NSGA3_CASE(2) NSGA3_CASE(3) NSGA3_CASE(4) NSGA3_CASE(5) NSGA3_CASE(6) NSGA3_CASE(7)
         NSGA3_CASE(8) NSGA3_CASE(9) NSGA3_CASE(10) NSGA3_CASE(11) NSGA3_CASE(12) NSGA3_CASE(13)
@@ -743,21 +869,30 @@ hipError_t run_select_stage(const SelectViews &v, hipStream_t s) {
     const unsigned nbN = (unsigned)((N + 255) / 256);
     v.mark();
     const unsigned nbW = (unsigned)((N + 127) / 128);  // 32 points per wave, 4 waves per block
+    const int S = assoc_split(N);
+    const unsigned nbS = (unsigned)((N * S + kNormThreads - 1) / kNormThreads);
     switch (M) {
+#define NSGA3_ASSOC(m, q)                                                                           \
+    hipLaunchKernelGGL((k_associate<m, q>), dim3(nbS), dim3(kNormThreads), 0, s, v.objs, N, v.rank, \
+                       v.rhat64, v.rhat32, v.H, v.niche, v.dist, v.dist64, v.rho, v.bcount,         \
+                       v.selflag, v.sc)
 #define NSGA3_CASE(m)                                                                               \
     case m:                                                                                         \
         if (v.assoc_mode == NSGA3_ASSOC_BF16)                                                       \
             hipLaunchKernelGGL(k_associate_bf16<m>, dim3(nbW), dim3(256), 0, s, v.objs, N, v.rank,  \
                                v.rhat64, v.rhat16, v.H, v.niche, v.dist, v.dist64, v.rho,           \
                                v.bcount, v.selflag, v.sc);                                          \
+        else if (S == 16)                                                                           \
+            NSGA3_ASSOC(m, 16);                                                                     \
+        else if (S == 4)                                                                            \
+            NSGA3_ASSOC(m, 4);                                                                      \
         else                                                                                        \
-            hipLaunchKernelGGL(k_associate<m>, dim3(nbN), dim3(kNormThreads), 0, s, v.objs, N,      \
-                               v.rank, v.rhat64, v.rhat32, v.H, v.niche, v.dist, v.dist64, v.rho,   \
-                               v.bcount, v.selflag, v.sc);                                          \
+            NSGA3_ASSOC(m, 1);                                                                      \
         break;
         NSGA3_CASE(2) NSGA3_CASE(3) NSGA3_CASE(4) NSGA3_CASE(5) NSGA3_CASE(6) NSGA3_CASE(7)
         NSGA3_CASE(8) NSGA3_CASE(9) NSGA3_CASE(10) NSGA3_CASE(11) NSGA3_CASE(12) NSGA3_CASE(13)
         NSGA3_CASE(14) NSGA3_CASE(15) NSGA3_CASE(16)
+#undef NSGA3_ASSOC
 #undef NSGA3_CASE
         default: return hipErrorInvalidValue;
     }
@@ -784,8 +919,7 @@ hipError_t run_select_stage(const SelectViews &v, hipStream_t s) {
         hipLaunchKernelGGL(k_bucket_rank, dim3(nbG), dim3(kRankGroup), 0, s, v.H, v.rho, v.bstart,
                            v.gstart, v.bd, v.bi, v.selflag, v.sc);
     }
-    compact_flags(v.selflag, N, v.selected, v.K, v.temp, &v.sc->n_selected, s);
-    if (v.info) hipLaunchKernelGGL(k_finalize, dim3(1), dim3(64), 0, s, v.info, v.K, v.sc);
+    run_compact(v.selflag, N, v.selected, v.K, v.temp, v.sc, v.info, s);
     v.mark();
     return hipGetLastError();
 }

@@ -18,17 +18,23 @@ __device__ __forceinline__ void asf_fold(const double (&g)[MM], int M, int32_t i
 #pragma unroll
     for (int k = 0; k < MM; ++k)
         if (k < M && g[k] > nad[k]) nad[k] = g[k];
+    // the largest weighted value and the largest of the others, so that axis j's
+    // maximum over the other axes is one of the two
+    double m1 = -DBL_MAX, m2 = -DBL_MAX;
+    int at = -1;
+#pragma unroll
+    for (int k = 0; k < MM; ++k) {
+        if (k < M) {
+            const double v = g[k] * 1e6;
+            if (v > m1) { m2 = m1; m1 = v; at = k; }
+            else if (v > m2) { m2 = v; }
+        }
+    }
 #pragma unroll
     for (int j = 0; j < MM; ++j) {
         if (j < M) {
-            double asf = -DBL_MAX;
-#pragma unroll
-            for (int k = 0; k < MM; ++k) {
-                if (k < M) {
-                    const double v = (k == j) ? g[k] : g[k] * 1e6;
-                    if (v > asf) asf = v;
-                }
-            }
+            double asf = j == at ? m2 : m1;
+            if (g[j] > asf) asf = g[j];
             if (asf < best[j]) { best[j] = asf; bidx[j] = i; }
         }
     }
@@ -336,6 +342,7 @@ __device__ __forceinline__ void init_scalars(DevScalars *sc, int t) {
         sc->bar_gen = 0;
         sc->level_V = 0;
         sc->ref_thr = 0;
+        sc->ext_done = 0;
     }
     if (t < 16) {
         sc->min_key[t] = 0xffffffffu;
