@@ -448,16 +448,20 @@ __global__ __launch_bounds__(256) void k_associate_bf16(
 // have level < V.  V* = max{V : C(V) <= R}; the remaining R - C(V*) picks are
 // the level-V* members of the lowest-indexed references.  One block.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void k_niche_plan(int H, const int32_t *__restrict__ rho,
-                                                     const int32_t *__restrict__ bcount,
-                                                     int32_t *__restrict__ bstart,
-                                                     int32_t *__restrict__ bcursor,
-                                                     int32_t *__restrict__ gstart,
-                                                     DevScalars *__restrict__ sc) {
-    __shared__ uint32_t lds[17];
-    __shared__ int64_t red[16];
-    __shared__ int64_t s_vmax;
-    if (sc->err) return;
+struct NicheLds {
+    static constexpr int kRefs = 4096;
+    uint32_t scan[17];
+    int64_t red[16];
+    int64_t vmax, V;
+    int32_t thr;
+    int32_t rho[kRefs], bc[kRefs];
+};
+
+__device__ __forceinline__ void niche_plan_item(int H, const int32_t *rho, const int32_t *bcount,
+                                                int32_t *bstart, int32_t *bcursor, int32_t *gstart,
+                                                DevScalars *sc, NicheLds &W) {
+    uint32_t *lds = W.scan;
+    int64_t *red = W.red;
     const int64_t R = sc->num_from_last;
     // bucket starts (exclusive scan of bcount), chunked by blockDim
     uint32_t run = 0, grun = 0;
@@ -490,28 +494,25 @@ __global__ __launch_bounds__(1024) void k_niche_plan(int H, const int32_t *__res
     if (threadIdx.x == 0) {
         int64_t m = 0;
         for (unsigned q = 0; q < blockDim.x / kWave; ++q) m = red[q] > m ? red[q] : m;
-        s_vmax = m;
+        W.vmax = m;
     }
     __syncthreads();
     // binary search for V* in [0, vmax]: C is non-decreasing, C(0) = 0 <= R;
     // the counts are read from LDS when they fit (one global read each, not
     // one per search step)
-    constexpr int kLdsRefs = 4096;
-    __shared__ int32_t s_rho[kLdsRefs], s_bc[kLdsRefs];
     const int32_t *rho_r = rho, *bc_r = bcount;
-    if (H <= kLdsRefs) {
+    if (H <= NicheLds::kRefs) {
         for (int j = threadIdx.x; j < H; j += blockDim.x) {
-            s_rho[j] = rho[j];
-            s_bc[j] = bcount[j];
+            W.rho[j] = rho[j];
+            W.bc[j] = bcount[j];
         }
         __syncthreads();
-        rho_r = s_rho;
-        bc_r = s_bc;
+        rho_r = W.rho;
+        bc_r = W.bc;
     }
     // (one wave searches: no block barriers inside the loop)
-    __shared__ int64_t s_V;
     if (threadIdx.x < kWave) {
-        int64_t lo = 0, hi = s_vmax;
+        int64_t lo = 0, hi = W.vmax;
         while (lo < hi) {
             const int64_t mid = (lo + hi + 1) >> 1;
             int64_t c = 0;
@@ -523,10 +524,10 @@ __global__ __launch_bounds__(1024) void k_niche_plan(int H, const int32_t *__res
             c = wave_sum(c);
             if (c <= R) lo = mid; else hi = mid - 1;
         }
-        if (threadIdx.x == 0) s_V = lo;
+        if (threadIdx.x == 0) W.V = lo;
     }
     __syncthreads();
-    const int64_t V = s_V;
+    const int64_t V = W.V;
     int64_t cV = 0;
     for (int j = threadIdx.x; j < H; j += blockDim.x) {
         int64_t t = V - rho[j];
@@ -543,8 +544,7 @@ __global__ __launch_bounds__(1024) void k_niche_plan(int H, const int32_t *__res
     // reference threshold: the rem-th reference (ascending) with a member at level V
     int32_t thr = 0;
     uint32_t seen = 0;
-    __shared__ int32_t s_thr;
-    if (threadIdx.x == 0) s_thr = (rem <= 0) ? 0 : H;
+    if (threadIdx.x == 0) W.thr = (rem <= 0) ? 0 : H;
     __syncthreads();
     if (rem > 0) {
         for (int base = 0; base < H; base += blockDim.x) {
@@ -552,18 +552,29 @@ __global__ __launch_bounds__(1024) void k_niche_plan(int H, const int32_t *__res
             const uint32_t has = (j < H && rho[j] <= V && V < (int64_t)rho[j] + bcount[j]) ? 1u : 0u;
             uint32_t tot;
             const uint32_t ex = block_exclusive_scan(has, lds, &tot);
-            if (has && (int64_t)(seen + ex) == rem - 1) s_thr = j + 1;
+            if (has && (int64_t)(seen + ex) == rem - 1) W.thr = j + 1;
             seen += tot;
             __syncthreads();
             if ((int64_t)seen >= rem) break;
         }
     }
     __syncthreads();
-    thr = s_thr;
+    thr = W.thr;
     if (threadIdx.x == 0) {
         sc->level_V = (int32_t)V;
         sc->ref_thr = thr;
     }
+}
+
+__global__ __launch_bounds__(1024) void k_niche_plan(int H, const int32_t *__restrict__ rho,
+                                                     const int32_t *__restrict__ bcount,
+                                                     int32_t *__restrict__ bstart,
+                                                     int32_t *__restrict__ bcursor,
+                                                     int32_t *__restrict__ gstart,
+                                                     DevScalars *__restrict__ sc) {
+    __shared__ NicheLds W;
+    if (sc->err) return;
+    niche_plan_item(H, rho, bcount, bstart, bcursor, gstart, sc, W);
 }
 
 // last-front members -> reference buckets (order inside a bucket is arbitrary)
@@ -703,6 +714,58 @@ __global__ __launch_bounds__(1024) void k_compact_one(const uint8_t *__restrict_
                                                       nsga3_info *__restrict__ info) {
     __shared__ uint32_t lds[17];
     compact_item(flag, N, out, cap, lds, sc, info);
+}
+
+// Small problems: plan, buckets, picks, compaction and info by one work-group,
+// which keeps the last front's members and the flags in LDS.  A member counts
+// its bucket alone, so one reference that holds all of N = 1024 members costs
+// 1024 steps (about 9 us); seven launches are at least 30 us.
+constexpr int kNicheOne = 1024;
+constexpr int kNicheOneRefs = kLdsNicheRefs;
+
+__global__ __launch_bounds__(1024) void k_niche_one(int N, int H, const int32_t *rank,
+                                                    const int32_t *niche, const double *dist64,
+                                                    const int32_t *rho, const int32_t *bcount,
+                                                    int32_t *bstart, int32_t *bcursor,
+                                                    int32_t *gstart, const uint8_t *selflag,
+                                                    int32_t *out, int64_t K, DevScalars *sc,
+                                                    nsga3_info *info) {
+    __shared__ NicheLds W;
+    __shared__ int32_t s_cur[kNicheOneRefs];
+    __shared__ double s_d[kNicheOne];
+    __shared__ int32_t s_i[kNicheOne];
+    __shared__ __attribute__((aligned(16))) uint8_t s_f[kNicheOne];
+    const int t = (int)threadIdx.x;
+    s_f[t] = 0;
+    __syncthreads();
+    if (!sc->err) {
+        niche_plan_item(H, rho, bcount, bstart, bcursor, gstart, sc, W);
+        __syncthreads();
+        for (int j = t; j < H; j += kNicheOne) s_cur[j] = bstart[j];
+        __syncthreads();
+        const bool in = t < N;
+        const bool member = in && rank[t] == sc->last_front;
+        const int32_t j = member ? niche[t] : 0;
+        const double d = member ? dist64[t] : 0.0;
+        if (in) s_f[t] = selflag[t];
+        if (member) {
+            const int32_t slot = atomicAdd(&s_cur[j], 1);
+            s_d[slot] = d;
+            s_i[slot] = t;
+        }
+        __syncthreads();
+        if (member) {
+            int32_t n = 0;
+            const int32_t b1 = bstart[j + 1];
+            for (int32_t m = bstart[j]; m < b1; ++m)
+                n += (s_d[m] < d || (s_d[m] == d && s_i[m] < t)) ? 1 : 0;
+            const int64_t lev = (int64_t)rho[j] + n;
+            const int64_t V = sc->level_V;
+            if (lev < V || (lev == V && j < sc->ref_thr)) s_f[t] = 1;
+        }
+        __syncthreads();
+    }
+    compact_item(s_f, N, out, K, W.scan, sc, info);
 }
 
 // Up to this many flags one work-group compacts them: 16 bytes a thread and
@@ -897,6 +960,13 @@ hipError_t run_select_stage(const SelectViews &v, hipStream_t s) {
         default: return hipErrorInvalidValue;
     }
     v.mark();
+    if (N <= kNicheOne && v.H <= kNicheOneRefs && v.niching_mode != NSGA3_NICHING_ONESHOT) {
+        hipLaunchKernelGGL(k_niche_one, dim3(1), dim3(1024), 0, s, (int)N, v.H, v.rank, v.niche,
+                           v.dist64, v.rho, v.bcount, v.bstart, v.bcursor, v.gstart, v.selflag,
+                           v.selected, v.K, v.sc, v.info);
+        v.mark();
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_niche_plan, dim3(1), dim3(1024), 0, s, v.H, v.rho, v.bcount, v.bstart,
                        v.bcursor, v.gstart, v.sc);
     hipLaunchKernelGGL(k_bucket_scatter, dim3(nbN), dim3(256), 0, s, N, v.H, v.rank, v.niche, v.dist64,

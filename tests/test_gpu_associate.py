@@ -32,3 +32,22 @@ def test_association_splits(N, M, H, bf16, near):
     rep = compare_full(f, refs, K, g)
     rep.pop("near_ties")
     assert not any(rep.values()), rep
+
+
+@pytest.mark.parametrize("N,M,H,kind", [
+    (2, 2, 1, "sphere"), (200, 3, 91, "sphere"), (1023, 5, 1, "front"), (1024, 3, 2048, "same"),
+    (1024, 16, 2049, "front"), (1024, 2, 4097, "sphere"), (1025, 3, 91, "same"),
+])
+def test_small_problems(N, M, H, kind):
+    """One work-group's order and niching, and the sizes where they end."""
+    rng = np.random.Generator(np.random.PCG64(N * H))
+    f = workloads.sphere_shell(rng, N, M, lambda r, n: r.uniform(0, 0.5, n), 0.2)
+    if kind == "front":
+        f /= np.linalg.norm(f, axis=1, keepdims=True)
+    if kind == "same":
+        f = f[rng.integers(0, N // 3, N)]
+    f, refs = f.astype(np.float32), (rng.random((H, M)) + 1e-3).astype(np.float32)
+    for K in sorted({1, N // 2, N}):
+        rep = compare_full(f, refs, K, gpu_select(f, refs, K))
+        rep.pop("near_ties")
+        assert not any(rep.values()), (K, rep)
