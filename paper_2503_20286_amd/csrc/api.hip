@@ -201,7 +201,7 @@ Layout layout_pairs(int64_t N, int M, int H) {
     L.sval = bump(c, 4 * n);
     L.runstart = bump(c, 4 * n);
     L.runend = bump(c, 4 * n);
-    const size_t n2 = pair_phases(N) > 0 ? n : 0;
+    const size_t n2 = pair_phases(N, M) > 0 ? n : 0;
     L.runs2 = bump(c, 4 * n2);
     L.rune2 = bump(c, 4 * n2);
     L.din2 = bump(c, 4 * n2);
@@ -446,7 +446,7 @@ PairInst pair_inst(char *w, const Layout &L, const nsga3_problem &p, int32_t *ra
     I.nBpad = (I.nB + 63) / 64 * 64;
     pair_cell_bits(p.N, p.M, I.bits, &I.T);
     const int full = (2 * I.nB + kRankWaves - 1) / kRankWaves;
-    I.groups = full <= kRankSoloRounds ? 1 : full < kRankMaxGroups ? full : kRankMaxGroups;
+    I.groups = full < kRankMaxGroups ? full : kRankMaxGroups;
     I.spl = WS(uint32_t, spl);
     I.cell = WS(uint32_t, cell);
     I.code = WS(uint32_t, code);

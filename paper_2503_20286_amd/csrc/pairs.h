@@ -38,7 +38,6 @@ constexpr int kListGroups = 1536;       // work-groups that take them (six a CU)
 constexpr int kPairWaves = 4;           // 128-point tiles of a pair work-group (one per wave)
 constexpr int kRankThreads = 1024;
 constexpr int kRankWaves = kRankThreads / kWave;
-constexpr int kRankSoloRounds = 4;      // 64-point groups a wave owns when one work-group ranks all
 constexpr int kRankMaxGroups = 64;      // work-groups of the persistent rank launch, at most
 constexpr int kMaxPhases = 8;           // fronts that may be taken off before it
 
@@ -139,8 +138,10 @@ __device__ __forceinline__ PairInst phase_inst(PairInst I) {
 
 // Fronts taken off before the masks are stored: none while one 64-point group
 // a wave of the rank launch is enough (N <= 32k).
-inline int pair_phases(int64_t N) {
-    return N <= 32768 ? 0 : N <= 65536 ? 2 : 5;
+// Of many objectives the first two fronts hold nearly all points (N = 100k,
+// M = 10: one front; three phases more are twelve empty launches, 54 us).
+inline int pair_phases(int64_t N, int M) {
+    return N <= 32768 ? 0 : N <= 65536 || M >= 8 ? 2 : 5;
 }
 
 inline void pair_cell_bits(int64_t N, int M, uint8_t *bits, int *T) {

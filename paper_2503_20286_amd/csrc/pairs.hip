@@ -21,17 +21,23 @@ __device__ __forceinline__ void splitters_item(const PairInst &I, int k, uint32_
     if (nb == 0) return;
     const int S = I.N < kSplitterSample ? I.N : kSplitterSample;
     const int t = (int)threadIdx.x;
-    s[t] = t < S ? order_key(I.objs[((int64_t)t * I.N / S) * I.M + k]) : 0xffffffffu;
-    for (int len = 2; len <= kSplitterSample; len <<= 1)
+    uint32_t v = t < S ? order_key(I.objs[((int64_t)t * I.N / S) * I.M + k]) : 0xffffffffu;
+    for (int len = 2; len <= kSplitterSample; len <<= 1) {
         for (int d = len >> 1; d > 0; d >>= 1) {
-            __syncthreads();
-            const int o = t ^ d;
-            if (o > t) {
-                const uint32_t a = s[t], b = s[o];
-                const bool up = (t & len) == 0;
-                if ((a > b) == up) { s[t] = b; s[o] = a; }
+            uint32_t o;
+            if (d >= kWave) {  // (the partner is in another wave)
+                s[t] = v;
+                __syncthreads();
+                o = s[t ^ d];
+                __syncthreads();
+            } else {
+                o = (uint32_t)__shfl_xor((int)v, d, kWave);
             }
+            const bool low = ((t & len) == 0) == ((t & d) == 0);
+            v = low ? (o < v ? o : v) : (o > v ? o : v);
         }
+    }
+    s[t] = v;
     __syncthreads();
     const int n = 1 << nb;
     if (t < n - 1) I.spl[k * 64 + t] = s[(int)((int64_t)(t + 1) * S / n)];
@@ -121,17 +127,43 @@ __global__ __launch_bounds__(1024) void k_cell_scan(PairInst I, RefArgs R) {
         reference_item(R, I.M, (int)(blockIdx.x - 1) * 1024 + (int)threadIdx.x, I.sc);
         return;
     }
+    // a thread's up to 64 consecutive counts stay in registers between the sum
+    // and the starts (65536 cells: 24 us when they were read one by one, twice)
+    constexpr int kVec = (1 << kCellMaxBits) / 1024 / 4;
     const int n = 1 << I.T;
-    const int per = (n + 1023) / 1024;
-    const int s0 = min((int)threadIdx.x * per, n), s1 = min(s0 + per, n);
+    const int per = n >= 4096 ? n / 1024 : 4;  // (a multiple of 4; few cells: few threads)
+    const int s0 = (int)threadIdx.x * per;
+    uint32_t *c = I.cell + s0;
+    uint32_t v[4 * kVec];
     uint32_t sum = 0;
-    for (int q = s0; q < s1; ++q) sum += I.cell[q];
+#pragma unroll
+    for (int q = 0; q < kVec; ++q) {
+        uint4 x = make_uint4(0, 0, 0, 0);
+        if (4 * q < per && s0 + 4 * q + 4 <= n)
+            x = *reinterpret_cast<const uint4 *>(c + 4 * q);
+        else if (q == 0 && n < 4 && s0 == 0) {
+            x.x = c[0];
+            x.y = n > 1 ? c[1] : 0u;
+        }
+        v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
+        sum += x.x + x.y + x.z + x.w;
+    }
     uint32_t tot;
     uint32_t run = block_exclusive_scan(sum, lds, &tot);
-    for (int q = s0; q < s1; ++q) {
-        const uint32_t t = I.cell[q];
-        I.cell[q] = run;
-        run += t;
+#pragma unroll
+    for (int q = 0; q < kVec; ++q) {
+        uint4 x;
+        x.x = run;
+        x.y = x.x + v[4 * q];
+        x.z = x.y + v[4 * q + 1];
+        x.w = x.z + v[4 * q + 2];
+        run = x.w + v[4 * q + 3];
+        if (4 * q < per && s0 + 4 * q + 4 <= n)
+            *reinterpret_cast<uint4 *>(c + 4 * q) = x;
+        else if (q == 0 && n < 4 && s0 == 0) {
+            c[0] = x.x;
+            if (n > 1) c[1] = x.y;
+        }
     }
     if (threadIdx.x == 0) I.cell[n] = tot;
 }
@@ -777,7 +809,7 @@ static hipError_t launch_pairs(const PairInst &I, const RefArgs &R, bool one, ui
     hipLaunchKernelGGL(k_pair_build<M>, dim3((unsigned)I.nB), dim3(M * kWave), 0, s, I);
     const unsigned tgs = (unsigned)((I.nB + kPairWaves - 1) / kPairWaves);
     const dim3 th(kPairWaves * kWave);
-    const int phases = pair_phases(I.N);
+    const int phases = pair_phases(I.N, M);
     if (phases == 0) {
         const int32_t G = pair_range(I.nB);
         const dim3 grid(tgs, (unsigned)((I.nB + G - 1) / G));

@@ -83,8 +83,6 @@ struct RankLds {
                       // 1 + block, [31:0] its mask unit
     int32_t *bound;   // [slots] blocks from here on are done with
     int32_t *list;    // [slots] slots with open points
-    uint4 *wit;       // [slots][64] witness masks and blocks (one work-group, several
-    uint16_t *pos;    // slots per wave)
 };
 
 // LDS words for the mask units of a work-group's rows.
@@ -103,10 +101,8 @@ __host__ __device__ inline size_t rank_lds_words(int nBp, int M, int lowK, int s
     const size_t oO = take(4 * (size_t)slots), oL = take((size_t)lowK * nBp);
     const size_t oH = take(solo ? 2 * (size_t)nBp * M : 0), oX = take((size_t)slots * M);
     const size_t oT = take(128 * (size_t)slots), oN = take(slots), oI = take(slots);
-    const bool own = solo && slots > kRankWaves;
     const bool near = slots * nBp <= kRankIdxWords;
     const size_t oQ = take(near ? (size_t)slots * nBp : 0);
-    const size_t oW = take(own ? 256 * (size_t)slots : 0), oP = take(own ? 32 * (size_t)slots : 0);
     if (S) {
         S->U = reinterpret_cast<uint64_t *>(base + oU);
         S->blkU = reinterpret_cast<uint64_t *>(base + oB);
@@ -120,8 +116,6 @@ __host__ __device__ inline size_t rank_lds_words(int nBp, int M, int lowK, int s
         S->hit = reinterpret_cast<uint64_t *>(base + oT);
         S->bound = reinterpret_cast<int32_t *>(base + oN);
         S->list = reinterpret_cast<int32_t *>(base + oI);
-        S->wit = reinterpret_cast<uint4 *>(base + oW);
-        S->pos = reinterpret_cast<uint16_t *>(base + oP);
     }
     return c;
 }
@@ -535,10 +529,6 @@ __device__ __forceinline__ void rank_levels(PairInst I, int32_t level0, uint32_t
     const int32_t rounds = (2 * I.nB + G * kRankWaves - 1) / (G * kRankWaves);
     RankLds S;
     rank_lds_words(I.nBpad, M, I.lowK, rounds * kRankWaves, kSolo, &S, dyn);
-    if (kSolo && !kKeep) {  // the points' state in LDS
-        I.pos = S.pos;
-        I.wit = S.wit;
-    }
     load_rows(I, g, G, rounds * kRankWaves, S);
     RankPoint<M> P;
     uint32_t done = 0;             // points ranked before this level
@@ -607,14 +597,14 @@ __device__ __forceinline__ void rank_levels(PairInst I, int32_t level0, uint32_t
     }
 }
 
-template <int M, bool kKeep, bool kSolo>
+template <int M, bool kSolo>
 __global__ __launch_bounds__(kRankThreads) void k_ranks(PairInst I) {
     extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
     __shared__ uint32_t s_new[kRankWaves];
     __shared__ uint32_t s_f;
     __shared__ int32_t s_n;
     if (I.sc->err) return;
-    rank_levels<M, kKeep, kSolo>(I, 0, dyn, s_new, &s_f, &s_n);
+    rank_levels<M, true, kSolo>(I, 0, dyn, s_new, &s_f, &s_n);
 }
 
 // The levels that the first `phases` fronts leave (their number of points is
@@ -651,13 +641,9 @@ static hipError_t launch_ranks(const PairInst &I, int phases, hipStream_t s) {
                            ranks_lds_bytes(I, rounds * kRankWaves, false) + 4 * kRankIdxWords, s, I,
                            phases);
     } else if (I.groups == 1) {
-        const size_t lds = ranks_lds_bytes(I, rounds * kRankWaves, true);
-        if (rounds == 1)
-            hipLaunchKernelGGL((k_ranks<M, true, true>), gr, th, lds, s, I);
-        else
-            hipLaunchKernelGGL((k_ranks<M, false, true>), gr, th, lds, s, I);
+        hipLaunchKernelGGL((k_ranks<M, true>), gr, th, ranks_lds_bytes(I, kRankWaves, true), s, I);
     } else {
-        hipLaunchKernelGGL((k_ranks<M, true, false>), gr, th, ranks_lds_bytes(I, kRankWaves, false),
+        hipLaunchKernelGGL((k_ranks<M, false>), gr, th, ranks_lds_bytes(I, kRankWaves, false),
                            s, I);
     }
     return hipGetLastError();

@@ -40,8 +40,15 @@ __device__ __forceinline__ void asf_fold(const double (&g)[MM], int M, int32_t i
     }
 }
 
+__device__ __forceinline__ double lane_read(double x, int l) {
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l);
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
 // a5: intercepts from the extreme points, by one whole wave (lane r holds
-// row r of E; lanes >= M only take part in the shuffles).  e[j] is the index
+// row r of E; lanes >= M take part in nothing).  e[j] is the index
 // of the extreme point of axis j, nadir[k] the largest translated value over
 // S, z the ideal point.  Solves E b = 1 by Gaussian elimination with partial
 // pivoting (largest |pivot|, lowest row on ties; singular when a pivot is
@@ -66,31 +73,37 @@ __device__ __forceinline__ int solve_intercepts_wave(const float *objs, const in
         const double av = fabs(row[k]);
         mx = av > mx ? av : mx;
     }
-    double maxabs = own ? mx : 0.0;
-    for (int o = 32; o > 0; o >>= 1) {
-        const double t = __shfl_xor(maxabs, o, 64);
+    // (values of one lane come over by lane reads, M of them in less time than
+    // the six exchanges of a reduction over the wave)
+    double maxabs = 0.0;
+#pragma unroll
+    for (int r = 0; r < M; ++r) {
+        const double t = lane_read(mx, r);
         maxabs = t > maxabs ? t : maxabs;
     }
     bool ok = maxabs > 0.0;
 #pragma unroll
     for (int c = 0; c < M; ++c) {
-        double pv = (own && lane >= c) ? fabs(row[c]) : -1.0;
-        int p = lane;
-        for (int o = 32; o > 0; o >>= 1) {
-            const double ov = __shfl_xor(pv, o, 64);
-            const int op = __shfl_xor(p, o, 64);
-            if (ov > pv || (ov == pv && op < p)) { pv = ov; p = op; }
+        const double av = fabs(row[c]);
+        double pv = lane_read(av, c);
+        int p = c;
+#pragma unroll
+        for (int r = c + 1; r < M; ++r) {
+            const double v = lane_read(av, r);
+            if (v > pv) { pv = v; p = r; }
         }
+        p = __builtin_amdgcn_readfirstlane(p);
         ok = ok && pv > 1e-10 * maxabs;
         // rows c and p trade places
-        const int src = lane == c ? p : (lane == p ? c : lane);
-#pragma unroll
-        for (int k = c; k < M; ++k) row[k] = __shfl(row[k], src, 64);
-        rhs = __shfl(rhs, src, 64);
         double prow[M];
 #pragma unroll
-        for (int k = c; k < M; ++k) prow[k] = __shfl(row[k], c, 64);
-        const double prhs = __shfl(rhs, c, 64);
+        for (int k = c; k < M; ++k) {
+            const double rc = lane_read(row[k], c);
+            prow[k] = lane_read(row[k], p);
+            row[k] = lane == c ? prow[k] : (lane == p ? rc : row[k]);
+        }
+        const double hc = lane_read(rhs, c), prhs = lane_read(rhs, p);
+        rhs = lane == c ? prhs : (lane == p ? hc : rhs);
         if (own && lane > c) {
             const double f = row[c] / prow[c];
 #pragma unroll
@@ -103,10 +116,10 @@ __device__ __forceinline__ int solve_intercepts_wave(const float *objs, const in
         double b[M];
 #pragma unroll
         for (int c = M - 1; c >= 0; --c) {
-            double s = __shfl(rhs, c, 64);
+            double s = lane_read(rhs, c);
 #pragma unroll
-            for (int k = c + 1; k < M; ++k) s = s - __shfl(row[k], c, 64) * b[k];
-            b[c] = s / __shfl(row[c], c, 64);
+            for (int k = c + 1; k < M; ++k) s = s - lane_read(row[k], c) * b[k];
+            b[c] = s / lane_read(row[c], c);
         }
 #pragma unroll
         for (int k = 0; k < M; ++k) {
