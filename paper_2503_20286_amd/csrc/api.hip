@@ -445,7 +445,8 @@ PairInst pair_inst(char *w, const Layout &L, const nsga3_problem &p, int32_t *ra
     I.nB = (int32_t)((p.N + kWBlk - 1) / kWBlk);
     I.nBpad = (I.nB + 63) / 64 * 64;
     pair_cell_bits(p.N, p.M, I.bits, &I.T);
-    const int full = (2 * I.nB + kRankWaves - 1) / kRankWaves;
+    const int waves = pair_phases(p.N, p.M) ? kRestWaves : kRankWaves;
+    const int full = (2 * I.nB + waves - 1) / waves;
     I.groups = full < kRankMaxGroups ? full : kRankMaxGroups;
     I.spl = WS(uint32_t, spl);
     I.cell = WS(uint32_t, cell);

@@ -36,9 +36,14 @@ constexpr int kCellMaxBits = 16;
 constexpr int kListItem = 8;            // blocks of a listed pair item
 constexpr int kListGroups = 1536;       // work-groups that take them (six a CU)
 constexpr int kPairWaves = 4;           // 128-point tiles of a pair work-group (one per wave)
-constexpr int kRankThreads = 1024;
-constexpr int kRankWaves = kRankThreads / kWave;
-constexpr int kRankMaxGroups = 64;      // work-groups of the persistent rank launch, at most
+constexpr int kPhaseThreads = 1024;     // positions of a compaction chunk
+// Work-groups of the persistent rank launch: 8 waves while one 64-point group a
+// wave is enough (N <= 32768; 16 waves took 5 % longer, N = 20k, M = 3 and
+// N = 10k, M = 2), 16 for what the phases leave of larger problems.
+constexpr int kRankWaves = 8, kRestWaves = 16;
+constexpr int kRankMaxGroups = 64;      // of them, at most: the CUs hold four such launches at
+                                        // once, one from each hardware queue, so that none can
+                                        // keep a part of another out while it waits
 constexpr int kMaxPhases = 8;           // fronts that may be taken off before it
 
 // LDS for the smallest keys of the blocks in the rank launches; a problem with
@@ -69,7 +74,7 @@ struct alignas(128) RankWord {
 struct RankSync {
     uint32_t lv[kMaxPhases];     // points of the fronts taken off first
     int32_t left[kMaxPhases];    // points left after each of them
-    uint32_t chunk[kMaxPhases][kPairsMaxN / kRankThreads];   // the same of a compaction chunk
+    uint32_t chunk[kMaxPhases][kPairsMaxN / kPhaseThreads];   // the same of a compaction chunk
     uint32_t items[kMaxPhases + 1], next[kMaxPhases + 1];   // listed and taken items of a pass
     RankWord pool[kMaskPools];   // units taken (v)
 };

@@ -710,25 +710,25 @@ __global__ __launch_bounds__(kPairWaves * kWave) void k_pairs_list(PairInst I, i
 // the same order (a block that straddled two distant chunks would meet half of
 // all tiles: without the order the second pass took as long as the first).  A
 // work-group takes the rows whose run of identical rows starts in its
-// kRankThreads positions, publishes how many stay, and reads the numbers of
+// kPhaseThreads positions, publishes how many stay, and reads the numbers of
 // the work-groups before it.
 // ---------------------------------------------------------------------------
 template <int M>
-__global__ __launch_bounds__(kRankThreads) void k_phase(PairInst I, PairInst J, int32_t phase) {
+__global__ __launch_bounds__(kPhaseThreads) void k_phase(PairInst I, PairInst J, int32_t phase) {
     constexpr int MP = rec_stride(M);
-    __shared__ uint32_t lds[kRankThreads / kWave + 1];
+    __shared__ uint32_t lds[kPhaseThreads / kWave + 1];
     __shared__ uint32_t s_n;
     __shared__ int32_t s_at;
     if (I.sc->err) return;
     I = phase_inst(I);
-    const int32_t c0 = (int32_t)blockIdx.x * kRankThreads;
+    const int32_t c0 = (int32_t)blockIdx.x * kPhaseThreads;
     if (c0 >= I.N) return;  // (work-groups after this one return too)
-    const int32_t c1 = c0 + kRankThreads;
+    const int32_t c1 = c0 + kPhaseThreads;
     const int32_t p0 = I.runs[c0] == c0 ? c0 : I.rune[c0];
     const int32_t p1 = c1 >= I.N ? I.N : (I.runs[c1] == c1 ? c1 : I.rune[c1]);
     if (threadIdx.x == 0) s_n = 0;
     __syncthreads();
-    for (int32_t b = p0; b < p1; b += kRankThreads) {
+    for (int32_t b = p0; b < p1; b += kPhaseThreads) {
         const int32_t p = b + (int32_t)threadIdx.x;
         const uint64_t m = ballot(p < p1 && I.din[p < p1 ? p : p0] != 0);
         if (lane_id() == 0 && m) atomicAdd(&s_n, (uint32_t)__popcll(m));
@@ -758,7 +758,7 @@ __global__ __launch_bounds__(kRankThreads) void k_phase(PairInst I, PairInst J, 
     }
     __syncthreads();
     int32_t base = s_at;
-    for (int32_t b = p0; b < p1; b += kRankThreads) {
+    for (int32_t b = p0; b < p1; b += kPhaseThreads) {
         const int32_t p = b + (int32_t)threadIdx.x;
         const bool in = p < p1;
         const int32_t d = in ? I.din[p] : 1;
@@ -834,8 +834,8 @@ static hipError_t launch_pairs(const PairInst &I, const RefArgs &R, bool one, ui
     alt.rune = I.rune2;
     alt.din = I.din2;
     for (int p = 0; p < phases; ++p) {  // (the sizes are on the device from here on)
-        hipLaunchKernelGGL(k_phase<M>, dim3((unsigned)((I.N + kRankThreads - 1) / kRankThreads)),
-                           dim3(kRankThreads), 0, s, cur, alt, p);
+        hipLaunchKernelGGL(k_phase<M>, dim3((unsigned)((I.N + kPhaseThreads - 1) / kPhaseThreads)),
+                           dim3(kPhaseThreads), 0, s, cur, alt, p);
         PairInst t = cur;
         cur = alt;
         alt = t;

@@ -68,7 +68,7 @@ __device__ __forceinline__ uint64_t uniform(uint64_t v) {
 }
 
 // What a rank work-group keeps in LDS; slots are its 64-point groups (round *
-// kRankWaves + wave).
+// waves + wave).
 struct RankLds {
     uint64_t *U;      // [2 * nBpad] unranked points
     uint64_t *blkU;   // [nBpad / 64] blocks with any
@@ -226,7 +226,7 @@ __device__ __forceinline__ size_t ex_word(const PairInst &I, int32_t rel, int32_
 // `slots` in all.  Slot q is the 64-point group q * G + g.  Returns the wave's
 // number of points of this front.  kKeep: one slot per wave, its state stays
 // in P over the levels; else it is read from and written to I.pos and I.wit.
-template <int M, bool kKeep, bool kSolo>
+template <int M, int kW, bool kKeep, bool kSolo>
 __device__ __forceinline__ uint32_t rank_level(const PairInst &I, int32_t level, int32_t base, int32_t g,
                                                int32_t G, int32_t rounds, int32_t slots,
                                                const RankLds &S, RankPoint<M> &P, int32_t *s_n) {
@@ -240,7 +240,7 @@ __device__ __forceinline__ uint32_t rank_level(const PairInst &I, int32_t level,
     // front 0 by in-degree, later levels: points that lost their witness
 #pragma unroll 1
     for (int r = 0; r < (kKeep ? 1 : rounds); ++r) {
-        const int slot = r * kRankWaves + w;
+        const int slot = r * kW + w;
         const int32_t h = slot * G + g;
         if (slot >= slots || h >= nH) break;
         const uint64_t un = uniform(S.U[h]);
@@ -297,7 +297,7 @@ __device__ __forceinline__ uint32_t rank_level(const PairInst &I, int32_t level,
         // find a witness there
 #pragma unroll 1
         for (int r = 0; r < (kKeep ? 1 : rounds); ++r) {
-            const int slot = r * kRankWaves + w;
+            const int slot = r * kW + w;
             const int32_t h = slot * G + g;
             if (slot >= slots || h >= nH) break;
             const uint64_t om = uniform(S.left[slot]);
@@ -326,7 +326,7 @@ __device__ __forceinline__ uint32_t rank_level(const PairInst &I, int32_t level,
         // the rest of the rows, a word at a time over all waves
         const int32_t nE = uniform(*s_n);
 #pragma unroll 1
-        for (int32_t u = w; u < nE * nW; u += kRankWaves) {
+        for (int32_t u = w; u < nE * nW; u += kW) {
             const int32_t slot = uniform(S.list[u % nE]);
             const int32_t wd = nW - 1 - u / nE;
             const int32_t h = slot * G + g;
@@ -349,7 +349,7 @@ __device__ __forceinline__ uint32_t rank_level(const PairInst &I, int32_t level,
     // fronts, and the unranked sets of the next level
 #pragma unroll 1
     for (int r = 0; r < (kKeep ? 1 : rounds); ++r) {
-        const int slot = r * kRankWaves + w;
+        const int slot = r * kW + w;
         const int32_t h = slot * G + g;
         if (slot >= slots || h >= nH) break;
         const uint64_t un = uniform(S.U[h]);
@@ -426,12 +426,12 @@ __device__ __forceinline__ uint32_t rank_level(const PairInst &I, int32_t level,
 // The unranked set of the rel-th level into LDS (the first: every point).
 // Returns this thread's share of it; s_f is set where a work-group's words never
 // came.
-template <int M, bool kSolo>
+template <int M, int kW, bool kSolo>
 __device__ __forceinline__ uint32_t load_unranked(const PairInst &I, int32_t rel, const RankLds &S,
                                                   uint32_t &s_f) {
     const int32_t nBp = I.nBpad, nH = 2 * I.nB;
     uint32_t mine = 0;
-    for (int32_t h0 = 0; h0 < 2 * nBp; h0 += kRankThreads) {
+    for (int32_t h0 = 0; h0 < 2 * nBp; h0 += kW * kWave) {
         const int32_t h = h0 + (int32_t)threadIdx.x;  // a thread takes a 64-point group
         uint64_t u = 0;
         uint32_t z[M];
@@ -495,15 +495,16 @@ __device__ __forceinline__ uint32_t load_unranked(const PairInst &I, int32_t rel
 }
 
 // Stored-block rows of the work-group's slots.
+template <int kW>
 __device__ __forceinline__ void load_rows(const PairInst &I, int32_t g, int32_t G, int32_t slots,
                                           const RankLds &S) {
     const int32_t nW = I.nBpad / 64;
-    for (int32_t q = (int32_t)threadIdx.x; q < slots * nW; q += kRankThreads) {
+    for (int32_t q = (int32_t)threadIdx.x; q < slots * nW; q += kW * kWave) {
         const int32_t tile = (q / nW * G + g) >> 1;
         S.rows[q] = tile < I.nB ? I.nz[(size_t)tile * nW + q % nW] : 0ull;
     }
     if (S.idx)
-        for (int32_t q = (int32_t)threadIdx.x; q < slots * I.nBpad; q += kRankThreads) {
+        for (int32_t q = (int32_t)threadIdx.x; q < slots * I.nBpad; q += kW * kWave) {
             const int32_t tile = (q / I.nBpad * G + g) >> 1;
             S.idx[q] = tile < I.nB ? I.idx[(size_t)tile * I.nBpad + q % I.nBpad] : 0u;
         }
@@ -517,7 +518,7 @@ __device__ __forceinline__ uint32_t rank_done(const PairInst &I, int32_t level0)
 }
 
 // Every level from level0 on, for the points that I still holds.
-template <int M, bool kKeep, bool kSolo>
+template <int M, int kW, bool kKeep, bool kSolo>
 __device__ __forceinline__ void rank_levels(PairInst I, int32_t level0, uint32_t *dyn,
                                             uint32_t *s_new, uint32_t *s_fp, int32_t *s_np) {
     uint32_t &s_f = *s_fp;
@@ -526,10 +527,10 @@ __device__ __forceinline__ void rank_levels(PairInst I, int32_t level0, uint32_t
     const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int lane = (int)lane_id();
     const int32_t g = kSolo ? 0 : (int32_t)blockIdx.x, G = kSolo ? 1 : (int32_t)gridDim.x;
-    const int32_t rounds = (2 * I.nB + G * kRankWaves - 1) / (G * kRankWaves);
+    const int32_t rounds = (2 * I.nB + G * kW - 1) / (G * kW);
     RankLds S;
-    rank_lds_words(I.nBpad, M, I.lowK, rounds * kRankWaves, kSolo, &S, dyn);
-    load_rows(I, g, G, rounds * kRankWaves, S);
+    rank_lds_words(I.nBpad, M, I.lowK, rounds * kW, kSolo, &S, dyn);
+    load_rows<kW>(I, g, G, rounds * kW, S);
     RankPoint<M> P;
     uint32_t done = 0;             // points ranked before this level
     bool found = false;
@@ -557,7 +558,7 @@ __device__ __forceinline__ void rank_levels(PairInst I, int32_t level0, uint32_t
     __syncthreads();
     for (int32_t level = level0;; ++level) {
         if (tid == 0) s_n = 0;
-        const uint32_t mine = load_unranked<M, kSolo>(I, level - level0, S, s_f);
+        const uint32_t mine = load_unranked<M, kW, kSolo>(I, level - level0, S, s_f);
         if (!kSolo) {
             const uint32_t n = wave_sum(mine);
             if (lane == 0) s_new[w] = n;
@@ -567,7 +568,7 @@ __device__ __forceinline__ void rank_levels(PairInst I, int32_t level0, uint32_t
         if (!kSolo) {
             if (s_f == ~0u) return;
             uint32_t left = 0;
-            for (int q = 0; q < kRankWaves; ++q) left += s_new[q];
+            for (int q = 0; q < kW; ++q) left += s_new[q];
             if (level > level0) {
                 close(level - 1, prev - left);
                 if (left == 0) return;
@@ -578,14 +579,14 @@ __device__ __forceinline__ void rank_levels(PairInst I, int32_t level0, uint32_t
             }
             prev = left;
         }
-        const uint32_t fresh = rank_level<M, kKeep, kSolo>(I, level, level0, g, G, rounds,
-                                                             rounds * kRankWaves, S, P, &s_n);
+        const uint32_t fresh = rank_level<M, kW, kKeep, kSolo>(I, level, level0, g, G, rounds,
+                                                             rounds * kW, S, P, &s_n);
         if (kSolo && lane == 0) s_new[w] = fresh;
         lds_wait();
         __syncthreads();
         if (kSolo) {
             uint32_t f = 0;
-            for (int q = 0; q < kRankWaves; ++q) f += s_new[q];
+            for (int q = 0; q < kW; ++q) f += s_new[q];
             __syncthreads();  // s_new is free again
             close(level, f);
             if (done >= total) return;
@@ -598,33 +599,29 @@ __device__ __forceinline__ void rank_levels(PairInst I, int32_t level0, uint32_t
 }
 
 template <int M, bool kSolo>
-__global__ __launch_bounds__(kRankThreads) void k_ranks(PairInst I) {
+__global__ __launch_bounds__(kRankWaves * kWave) void k_ranks(PairInst I) {
     extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
     __shared__ uint32_t s_new[kRankWaves];
     __shared__ uint32_t s_f;
     __shared__ int32_t s_n;
     if (I.sc->err) return;
-    rank_levels<M, true, kSolo>(I, 0, dyn, s_new, &s_f, &s_n);
+    rank_levels<M, kRankWaves, true, kSolo>(I, 0, dyn, s_new, &s_f, &s_n);
 }
 
 // The levels that the first `phases` fronts leave (their number of points is
 // on the device).
 template <int M>
-__global__ __launch_bounds__(kRankThreads) void k_ranks_rest(PairInst I, int32_t phases) {
+__global__ __launch_bounds__(kRestWaves * kWave) void k_ranks_rest(PairInst I, int32_t phases) {
     extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
-    __shared__ uint32_t s_new[kRankWaves];
+    __shared__ uint32_t s_new[kRestWaves];
     __shared__ uint32_t s_f;
     __shared__ int32_t s_n;
     if (I.sc->err) return;
     I = phase_inst(I);
-    if (2 * I.nB <= (int32_t)gridDim.x * kRankWaves)
-        rank_levels<M, true, false>(I, phases, dyn, s_new, &s_f, &s_n);
+    if (2 * I.nB <= (int32_t)gridDim.x * kRestWaves)
+        rank_levels<M, kRestWaves, true, false>(I, phases, dyn, s_new, &s_f, &s_n);
     else
-        rank_levels<M, false, false>(I, phases, dyn, s_new, &s_f, &s_n);
-}
-
-static int rank_rounds(const PairInst &I, int G) {
-    return (2 * I.nB + G * kRankWaves - 1) / (G * kRankWaves);
+        rank_levels<M, kRestWaves, false, false>(I, phases, dyn, s_new, &s_f, &s_n);
 }
 
 static size_t ranks_lds_bytes(const PairInst &I, int slots, bool solo) {
@@ -633,18 +630,19 @@ static size_t ranks_lds_bytes(const PairInst &I, int slots, bool solo) {
 
 template <int M>
 static hipError_t launch_ranks(const PairInst &I, int phases, hipStream_t s) {
-    const int rounds = rank_rounds(I, I.groups);
-    const dim3 gr((unsigned)I.groups), th(kRankThreads);
+    const dim3 gr((unsigned)I.groups);
     if (phases > 0) {
+        const int per = I.groups * kRestWaves, rounds = (2 * I.nB + per - 1) / per;
         // (fewer blocks may bring the mask units into LDS)
-        hipLaunchKernelGGL(k_ranks_rest<M>, gr, th,
-                           ranks_lds_bytes(I, rounds * kRankWaves, false) + 4 * kRankIdxWords, s, I,
+        hipLaunchKernelGGL(k_ranks_rest<M>, gr, dim3(kRestWaves * kWave),
+                           ranks_lds_bytes(I, rounds * kRestWaves, false) + 4 * kRankIdxWords, s, I,
                            phases);
     } else if (I.groups == 1) {
-        hipLaunchKernelGGL((k_ranks<M, true>), gr, th, ranks_lds_bytes(I, kRankWaves, true), s, I);
+        hipLaunchKernelGGL((k_ranks<M, true>), gr, dim3(kRankWaves * kWave),
+                           ranks_lds_bytes(I, kRankWaves, true), s, I);
     } else {
-        hipLaunchKernelGGL((k_ranks<M, false>), gr, th, ranks_lds_bytes(I, kRankWaves, false),
-                           s, I);
+        hipLaunchKernelGGL((k_ranks<M, false>), gr, dim3(kRankWaves * kWave),
+                           ranks_lds_bytes(I, kRankWaves, false), s, I);
     }
     return hipGetLastError();
 }
