@@ -18,8 +18,8 @@
 //  k_hv_weights  w_i = alpha_{count_i} for 1 <= count_i <= k (else 0), and the
 //                flags of those samples (compacted in order afterwards)
 //  k_hv_sum      per point of r <= l: the weights of the kept samples it
-//                dominates, added in sample order in float64 within a part of the
-//                samples, staged through LDS
+//                dominates, added in float64 with their rounding errors kept, a
+//                part of the samples at a time, staged through LDS
 //  k_hv_keys     the parts added in order; sort keys: F_l members by descending
 //                estimate (then index); flags of r < l
 //  k_hv_select   the first R in that order join the selection (k_hv_pick after
@@ -191,6 +191,14 @@ __global__ void k_hv_weights(int64_t s, const int32_t *__restrict__ count, const
 constexpr int kHvParts = 8;
 constexpr int kHvPartMin = kHvSumChunk;   // samples of a part, at least
 
+// acc + x with the rounding error kept in low (x, acc >= 0; exact where acc >= x):
+// another order of the samples must not lose digits against one chain.
+__device__ __forceinline__ void add_comp(double &acc, double &low, double x) {
+    const double s = acc + x;
+    low = low + (x - (s - acc));
+    acc = s;
+}
+
 static int64_t hv_part_samples(int64_t s) {
     const int64_t p = (s + kHvParts - 1) / kHvParts;
     return p < kHvPartMin ? kHvPartMin : p;
@@ -221,7 +229,7 @@ __global__ __launch_bounds__(kHvThreads) void k_hv_sum(const float *__restrict__
     const int64_t b0 = (int64_t)blockIdx.y * per;
     const int64_t b1 = b0 + per < nrel ? b0 + per : nrel;
     const bool any = ballot(mine) != 0ull;
-    double acc = 0.0;
+    double acc = 0.0, low = 0.0;
     for (int64_t q0 = b0; q0 < b1; q0 += kHvSumChunk) {
         const int nq = b1 - q0 < kHvSumChunk ? (int)(b1 - q0) : kHvSumChunk;
         const int nr = (nq + kU - 1) / kU * kU;
@@ -251,11 +259,11 @@ __global__ __launch_bounds__(kHvThreads) void k_hv_sum(const float *__restrict__
 #pragma unroll
                 for (int u = 0; u < kU; ++u) a[u] = dom[u] ? ws[q + u] : 0.0;
 #pragma unroll
-                for (int u = 0; u < kU; ++u) acc = acc + a[u];
+                for (int u = 0; u < kU; ++u) add_comp(acc, low, a[u]);
             }
         }
     }
-    if (mine) part[(int64_t)blockIdx.y * N + p] = acc;
+    if (mine) part[(int64_t)blockIdx.y * N + p] = acc + low;
 }
 
 // Estimates from their parts; members of F_l with their sort keys (descending
@@ -274,9 +282,9 @@ __global__ void k_hv_keys(int64_t N, int64_t s, int parts, const int32_t *__rest
     double e = -INFINITY;
     if (!err && i < N) {
         if (r <= l) {
-            double acc = part[i];
-            for (int q = 1; q < parts; ++q) acc = acc + part[(int64_t)q * N + i];
-            e = acc * hs->V / (double)s;
+            double acc = part[i], low = 0.0;
+            for (int q = 1; q < parts; ++q) add_comp(acc, low, part[(int64_t)q * N + i]);
+            e = (acc + low) * hs->V / (double)s;
         }
         d[i] = e;
     }
