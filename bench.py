@@ -13,8 +13,9 @@ Prints one JSON line (rank 0, N=1).  The roofline object covers the dominant
 phase (the dominance counts): algorithmic work M*N*(N-1)/2 pair-objective
 compares per launch (every unordered pair decided once) divided by the phase's
 event-timed duration, against the vector-ALU rate 256 CUs x 64 lanes x 2.4 GHz.
-The block-bitset kernels decide 64 pairs per probe, so this is an effective
-pair-decision rate, not a VALU utilisation, and it can exceed 1; the issue
+Bounding boxes decide most pairs of blocks and a probe decides 128 pairs, so
+this is an effective pair-decision rate, not a VALU utilisation, and it can
+exceed 1; the issue
 utilisation is roofline.valu_issue: the phase's counted VALU instructions
 (SQ_INSTS_VALU, profiles/dominance_count_large_counters.json) over its event
 time against 1024 SIMDs x 2.4 GHz / 4.  traffic is the phase's HBM bytes from
@@ -624,10 +625,9 @@ def main():
         },
         "roofline": {
             "bound": "alu",
-            "kernel": "dominance counts (block bitsets: k_build_wide + k_fwd_all_wide, 128-member "
-                      "tables, for 4 <= M <= 10; k_build_blocks + k_fwd_all, 64-member tables, "
-                      "otherwise; out-degrees from the in-degree probes for M >= 4, a backward pass "
-                      "k_bwd_all below)",
+            "kernel": "dominance counts (spatially ordered 128-member tables: k_pair_build, "
+                      "k_pair_list, and the first pass of k_pairs_list, in-degrees and out-degrees "
+                      "from one probe)",
             "achieved": achieved,
             "peak": peak,
             "unit": "Tcmp/s",
@@ -635,9 +635,9 @@ def main():
             "traffic": traffic,
             "work_per_launch": f"{cmp_per_launch:.4e} pair-objective compares (M*N*(N-1)/2: every "
                                "unordered pair decided once)",
-            "note": "effective pair-decision rate: one block-bitset probe decides 64 or 128 pairs "
-                    "with M key searches and M mask ANDs, so frac is not a VALU utilisation and can "
-                    "exceed 1",
+            "note": "effective pair-decision rate: most pairs of 128-point blocks are decided by "
+                    "their bounding boxes, the others by a probe of 128 pairs with up to M key "
+                    "searches and mask ANDs, so frac is not a VALU utilisation and can exceed 1",
             "frac_counts_and_peeling": cmp_per_launch / ((phases["dominance_count"] + phases["peel"])
                                                           / 1e3) / PEAK_CMP_PER_S,
             # counted VALU instructions of the phase (rocprofv3 SQ_INSTS_VALU)

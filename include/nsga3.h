@@ -113,7 +113,9 @@ void nsga3_destroy(nsga3_ctx *ctx);
  * in nsga3_select. */
 nsga3_status nsga3_reserve(nsga3_ctx *ctx, int64_t N_max, int32_t M_max, int32_t H_max);
 
-/* Bytes of workspace a call of this size needs (host-only query). */
+/* Bytes of workspace a call of this size needs at least (host-only query).  A
+ * context without a cap, or with one that allows it, takes more where that makes
+ * calls faster (masks of dominance pairs kept for the ranks). */
 nsga3_status nsga3_workspace_size(int64_t N, int32_t M, int32_t H, size_t *bytes);
 
 /*
@@ -263,9 +265,10 @@ nsga3_status nsga3_rvea_select(nsga3_ctx *ctx, const float *objs, int64_t N, int
  * device's shapes (host queries only).  Every call on a device shares that
  * device's array: calls that overlap in time on one device (different
  * streams, or different host threads) race and give undefined results;
- * calls on one stream are ordered and safe.  Levels beyond the 24th front are
- * peeled by one work-group (no cooperative launch), so inputs with very many
- * fronts are slower than with nsga3_select.
+ * calls on one stream are ordered and safe.  Where the masks that nsga3_select
+ * keeps do not fit the array as well, levels beyond the 24th front are peeled by
+ * one work-group (no cooperative launch), so inputs with very many fronts are
+ * slower than with nsga3_select.
  */
 #define NSGA3_NOALLOC_MAX_WORKSPACE (32u << 20)
 nsga3_status nsga3_select_noalloc(const float *objs, int64_t N, int32_t M, const float *refs,

@@ -19,9 +19,10 @@
 // others are copied together in order, the next pass over them gives front 1,
 // and so on; masks are stored in the last pass only, for what is left.
 //
-// Whole selections, key-sum order -> this path: N = 200k, M = 5 2.65 -> 1.39 ms,
-// N = 100k, M = 10 0.95 -> 0.61 ms, N = 50k, M = 4 0.74 -> 0.53 ms, N = 20k, M = 3
-// 0.76 -> 0.45 ms, N = 10k, M = 2 4.2 -> 0.86 ms, N = 200 0.25 -> 0.12 ms.
+// Whole selections, key-sum order -> this path (with the stages after it as
+// they are now): N = 200k, M = 5 2.65 -> 1.35 ms, N = 100k, M = 10 0.95 -> 0.55 ms,
+// N = 50k, M = 4 0.74 -> 0.52 ms, N = 20k, M = 3 0.76 -> 0.38 ms, N = 10k, M = 2
+// 4.1 -> 0.69 ms, N = 200 0.24 -> 0.074 ms.
 #pragma once
 
 #include "bitdom_wide.h"

@@ -70,3 +70,24 @@ def test_ranks_and_degrees_match_oracle(N, M, kind):
                                       (3000, 12, "same")])
 def test_key_sum_order_matches_oracle(N, M, kind, monkeypatch):
     _check(_objs(kind, N, M, 3 * N + M), monkeypatch, pairs=False)
+
+
+def test_four_streams_at_once():
+    """Contexts on four streams, each with rank launches that wait for their own
+    work-groups, beside each other."""
+    import torch
+    probs = [(_objs("sphere", n, m, n), m) for n, m in ((90000, 5), (70000, 4), (30000, 3), (8000, 2))]
+    refs = [torch.eye(m, device="cuda") + 0.1 for _, m in probs]
+    objs = [torch.from_numpy(f).cuda() for f, _ in probs]
+    ctx = [nsga3.Context(0) for _ in probs]
+    want = [nsga3.select(o, r, len(o) // 2, ctx=c).rank.clone() for o, r, c in zip(objs, refs, ctx)]
+    streams = [torch.cuda.Stream() for _ in probs]
+    torch.cuda.synchronize()
+    got = []
+    for _ in range(5):
+        for o, r, c, s in zip(objs, refs, ctx, streams):
+            with torch.cuda.stream(s):
+                got.append(nsga3.select(o, r, len(o) // 2, ctx=c))
+    torch.cuda.synchronize()
+    for q, g in enumerate(got):
+        assert g.info().status == 0 and torch.equal(g.rank, want[q % len(probs)])
