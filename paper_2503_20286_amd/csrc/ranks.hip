@@ -21,8 +21,8 @@ namespace nsga3 {
 // the far corner of objective space are the longest by far, and 64-point
 // groups next to each other go to different work-groups.
 //
-// Small problems take one work-group, others one persistent launch with a
-// barrier per level; the points' state is in registers where a wave owns one
+// Small problems take one work-group, others one persistent launch of several
+// in step; the points' state is in registers where a wave owns one
 // group.  The unranked sets go from level to level through global memory by
 // device-scope stores and loads (one work-group: through LDS); every 64-bit
 // word carries its level, so a work-group waits for the words themselves and
@@ -401,11 +401,8 @@ __device__ __forceinline__ uint32_t rank_level(const PairInst &I, int32_t level,
                 }
                 if (kKeep) P.low = low;
             } else if (!kKeep && lane < M) {
-                if (rel == 0)
-                    low = I.low[(size_t)h * 16 + lane];
-                else
-                    low = kSolo ? S.half[h * M + lane]
-                                : (uint32_t)agent_ld(&I.ex[ex_word<M>(I, rel, lane, h)]);
+                low = rel == 0 ? I.low[(size_t)h * 16 + lane]
+                               : (uint32_t)agent_ld(&I.ex[ex_word<M>(I, rel, lane, h)]);
             }
             if (kSolo && lane < M) S.half[h * M + lane] = low;
             keep_low = low;
