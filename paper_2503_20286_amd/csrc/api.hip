@@ -71,6 +71,7 @@ struct nsga3_ctx {
     bool wide_levels;               // LaunchCfg::wide_levels
     bool engine_wide;               // batched counts over 128-member tables
     bool pairs;                     // spatially ordered path where its workspace fits
+    int rank_groups, rank_started;  // LaunchCfg's
     volatile int32_t *last_fronts;  // pinned: front count, then level sizes, of the latest call
     std::vector<hipEvent_t> ev_pool;   // NSGA3_NUM_PHASES + 1 events per recorded call
     size_t ev_used;
@@ -335,6 +336,8 @@ LaunchCfg ctx_cfg(const nsga3_ctx *ctx, int M, int64_t N) {
     cfg.wide = ctx->wide;
     cfg.wide_levels = ctx->wide_levels;
     cfg.lds_build_max = ctx->lds_build_max;
+    cfg.rank_groups = ctx->rank_groups;
+    cfg.rank_started = ctx->rank_started;
     // The previous call's front count and level sizes arrive asynchronously
     // in pinned memory; they only size launches (a stale or torn read shifts
     // work between the enqueued levels and the tail, never the results).
@@ -435,7 +438,8 @@ SortViews sort_views(char *w, const Layout &L, const nsga3_problem &p, int32_t *
 }
 
 // The spatially ordered path's problem over the workspace w carved by L.
-PairInst pair_inst(char *w, const Layout &L, const nsga3_problem &p, int32_t *rank_o) {
+PairInst pair_inst(char *w, const Layout &L, const nsga3_problem &p, int32_t *rank_o,
+                   const LaunchCfg &cfg) {
 #define WS(T, f) reinterpret_cast<T *>(w + L.f)
     PairInst I = {};
     I.objs = p.objs;
@@ -445,9 +449,6 @@ PairInst pair_inst(char *w, const Layout &L, const nsga3_problem &p, int32_t *ra
     I.nB = (int32_t)((p.N + kWBlk - 1) / kWBlk);
     I.nBpad = (I.nB + 63) / 64 * 64;
     pair_cell_bits(p.N, p.M, I.bits, &I.T);
-    const int waves = pair_phases(p.N, p.M) ? kRestWaves : kRankWaves;
-    const int full = (2 * I.nB + waves - 1) / waves;
-    I.groups = full < kRankMaxGroups ? full : kRankMaxGroups;
     I.spl = WS(uint32_t, spl);
     I.cell = WS(uint32_t, cell);
     I.code = WS(uint32_t, code);
@@ -481,6 +482,7 @@ PairInst pair_inst(char *w, const Layout &L, const nsga3_problem &p, int32_t *ra
     I.dom_in = p.dom_in;
     I.dom_out = p.dom_out;
 #undef WS
+    rank_shape(I, cfg.rank_groups > 0 ? cfg.rank_groups : cfg.num_cus / 4, cfg.rank_started);
     return I;
 }
 
@@ -515,7 +517,7 @@ hipError_t enqueue_select(const EnqArgs &a, const nsga3_problem &p, hipStream_t 
     refa.rhat16 = WS(uint16_t, rhat16);
     hipError_t e;
     if (a.pairs) {
-        const PairInst pi = pair_inst(w, L, p, rank_o);
+        const PairInst pi = pair_inst(w, L, p, rank_o, a.cfg);
         e = run_pairs(pi, refa, WS(uint32_t, zero), (int64_t)L.zero_words, mk, stream);
     } else {
         int32_t *zero_p[] = {WS(int32_t, dom_in_s), WS(int32_t, dom_out_s), WS(int32_t, rho),
@@ -759,6 +761,11 @@ nsga3_status nsga3_create(nsga3_ctx **out, int device, const nsga3_options *opt)
                           "NSGA3_LEVEL_LDS_BUILD", "NSGA3_HOST_LEVELS", "NSGA3_PEEL_BLOCKS_PER_CU",
                           "NSGA3_PHASE_A_BLOCKS_PER_CU"})
         if (getenv(e)) c->pairs = false;
+    // NSGA3_RANK_GROUPS: work-groups the rank launch of that path wants, at most;
+    // NSGA3_RANK_STARTED: how many it starts (fewer: as where others hold the CUs)
+    c->rank_groups = c->rank_started = 0;
+    if (const char *e = getenv("NSGA3_RANK_GROUPS")) c->rank_groups = atoi(e);
+    if (const char *e = getenv("NSGA3_RANK_STARTED")) c->rank_started = atoi(e);
     c->last_fronts = nullptr;
     {
         void *h = nullptr;
@@ -937,14 +944,14 @@ nsga3_status nsga3_hype_select(nsga3_ctx *ctx, const float *objs, int64_t N, int
     // and 64-member tables of all points for the sample probes
     const nsga3_problem p = {objs, N, M, vref, 1, n, selected, rank_o, nullptr, nullptr,
                              nullptr, nullptr, nullptr};
+    const LaunchCfg cfg = ctx_cfg(ctx, M, N);
     hipError_t e;
     if (pairs) {
-        PairInst pi = pair_inst(w, L, p, rank_o);
+        PairInst pi = pair_inst(w, L, p, rank_o, cfg);
         pi.tabs64 = reinterpret_cast<uint32_t *>(w + T.tabs);
         const RefArgs none = {};
         e = run_pairs(pi, none, WS(uint32_t, zero), (int64_t)L.zero_words, mk, stream);
     } else {
-        const LaunchCfg cfg = ctx_cfg(ctx, M, N);
         int32_t *zero_p[] = {WS(int32_t, dom_in_s), WS(int32_t, dom_out_s), WS(int32_t, bar),
                              WS(int32_t, work), WS(int32_t, lbstate)};
         const int64_t zero_n[] = {N, N, (int64_t)(sizeof(GridBar) / sizeof(int32_t)), kMaxHostLevels,

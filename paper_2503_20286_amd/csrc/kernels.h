@@ -77,6 +77,9 @@ struct LaunchCfg {
     // levels whose expected front has at most this many points build their
     // tables inside the level kernel (0: never)
     int32_t lds_build_max = 0;
+    // rank launch of the spatially ordered path: most work-groups it may want
+    // (0: by the CUs), and how many it starts (0: those it wants)
+    int rank_groups = 0, rank_started = 0;
 };
 
 // Points left before a peeling tail at or below which one work-group
@@ -115,6 +118,9 @@ struct RefArgs;
 hipError_t run_pairs(const PairInst &I, const RefArgs &R, uint32_t *zero, int64_t nzero,
                      const Marker &mark, hipStream_t s);
 // ---- ranks.hip ------------------------------------------------------------
+// Fills in the launch shape: work-groups (at most max_groups) and what they hold
+// at once; `started` of them are launched (0: all).
+void rank_shape(PairInst &I, int max_groups, int started);
 hipError_t run_ranks(const PairInst &I, int phases, hipStream_t s);
 
 // ---- peel.hip -------------------------------------------------------------

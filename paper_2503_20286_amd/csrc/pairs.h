@@ -42,9 +42,16 @@ constexpr int kPhaseThreads = 1024;     // positions of a compaction chunk
 // wave is enough (N <= 32768; 16 waves took 5 % longer, N = 20k, M = 3 and
 // N = 10k, M = 2), 16 for what the phases leave of larger problems.
 constexpr int kRankWaves = 8, kRestWaves = 16;
-constexpr int kRankMaxGroups = 64;      // of them, at most: the CUs hold four such launches at
-                                        // once, one from each hardware queue, so that none can
-                                        // keep a part of another out while it waits
+// Work-groups of it, at most (and at most a quarter of the CUs, so that four
+// streams' launches run beside each other).  They wait for each other's words,
+// and nothing promises that all of them are on the chip at once: other streams'
+// kernels, other processes or a CU mask may keep some out.  So those that have
+// started form the team (rank_team): it closes when all wanted have started or
+// kTeamWait after its first has waited in vain, works through all points with
+// as many as it has, and a work-group that starts later leaves.  A team waits
+// only for work-groups that are running.
+constexpr int kRankMaxGroups = 64;
+constexpr uint64_t kTeamWait = 10000;   // ticks of the 100 MHz clock: 100 us
 constexpr int kMaxPhases = 8;           // fronts that may be taken off before it
 
 // LDS for the smallest keys of the blocks in the rank launches; a problem with
@@ -77,6 +84,8 @@ struct RankSync {
     int32_t left[kMaxPhases];    // points left after each of them
     uint32_t chunk[kMaxPhases][kPairsMaxN / kPhaseThreads];   // the same of a compaction chunk
     uint32_t items[kMaxPhases + 1], next[kMaxPhases + 1];   // listed and taken items of a pass
+    RankWord team;               // v [15:0] work-groups that have started, [31:16] the closed
+                                 // team's size
     RankWord pool[kMaskPools];   // units taken (v)
 };
 
@@ -89,7 +98,9 @@ struct PairInst {
     int32_t nB;               // 128-point blocks
     int32_t nBpad;            // nB rounded to 64
     int32_t T;                // cell code bits
-    int32_t groups;           // work-groups of the persistent rank launch
+    int32_t groups;           // work-groups wanted by the persistent rank launch
+    int32_t started;          // work-groups it starts (groups, but for tests)
+    int32_t rounds;           // 64-point groups of a wave that its LDS holds at once
     uint8_t bits[16];         // cell code bits per objective
     uint32_t *spl;            // [M * 64] splitters
     uint32_t *cell;           // [2^T + 1] counts, then starts

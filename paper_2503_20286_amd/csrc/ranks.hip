@@ -27,7 +27,8 @@ namespace nsga3 {
 // device-scope stores and loads (one work-group: through LDS); every 64-bit
 // word carries its level, so a work-group waits for the words themselves and
 // not for a barrier after them (a level of N = 20k, M = 3 9.6 us with flags
-// behind the stores).  Large problems come here without their first fronts
+// behind the stores).  Who waits is a team of work-groups that have all started
+// (see kRankMaxGroups).  Large problems come here without their first fronts
 // (see pairs.h).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint64_t agent_ld(const uint64_t *p) {
@@ -223,12 +224,12 @@ __device__ __forceinline__ size_t ex_word(const PairInst &I, int32_t rel, int32_
 }
 
 // One level for the slots of a work-group; `rounds` slots per wave, at most
-// `slots` in all.  Slot q is the 64-point group q * G + g.  Returns the wave's
+// `slots` in all.  Slot q is the 64-point group (q0 + q) * G + g.  Returns the wave's
 // number of points of this front.  kKeep: one slot per wave, its state stays
 // in P over the levels; else it is read from and written to I.pos and I.wit.
 template <int M, int kW, bool kKeep, bool kSolo>
 __device__ __forceinline__ uint32_t rank_level(const PairInst &I, int32_t level, int32_t base, int32_t g,
-                                               int32_t G, int32_t rounds, int32_t slots,
+                                               int32_t G, int32_t q0, int32_t rounds, int32_t slots,
                                                const RankLds &S, RankPoint<M> &P, int32_t *s_n) {
     constexpr int MP = rec_stride(M);
     constexpr int kFirst = 8;  // blocks a wave looks at by itself before sharing a row
@@ -241,7 +242,7 @@ __device__ __forceinline__ uint32_t rank_level(const PairInst &I, int32_t level,
 #pragma unroll 1
     for (int r = 0; r < (kKeep ? 1 : rounds); ++r) {
         const int slot = r * kW + w;
-        const int32_t h = slot * G + g;
+        const int32_t h = (q0 + slot) * G + g;
         if (slot >= slots || h >= nH) break;
         const uint64_t un = uniform(S.U[h]);
         uint64_t open_m = 0;
@@ -298,7 +299,7 @@ __device__ __forceinline__ uint32_t rank_level(const PairInst &I, int32_t level,
 #pragma unroll 1
         for (int r = 0; r < (kKeep ? 1 : rounds); ++r) {
             const int slot = r * kW + w;
-            const int32_t h = slot * G + g;
+            const int32_t h = (q0 + slot) * G + g;
             if (slot >= slots || h >= nH) break;
             const uint64_t om = uniform(S.left[slot]);
             if (!om) continue;
@@ -329,7 +330,7 @@ __device__ __forceinline__ uint32_t rank_level(const PairInst &I, int32_t level,
         for (int32_t u = w; u < nE * nW; u += kW) {
             const int32_t slot = uniform(S.list[u % nE]);
             const int32_t wd = nW - 1 - u / nE;
-            const int32_t h = slot * G + g;
+            const int32_t h = (q0 + slot) * G + g;
             const int32_t bound = uniform(S.bound[slot]);
             const uint64_t *row = S.rows + (size_t)slot * nW;
             if (bound <= wd << 6 || uniform(row[wd] & S.blkU[wd]) == 0ull) continue;
@@ -350,7 +351,7 @@ __device__ __forceinline__ uint32_t rank_level(const PairInst &I, int32_t level,
 #pragma unroll 1
     for (int r = 0; r < (kKeep ? 1 : rounds); ++r) {
         const int slot = r * kW + w;
-        const int32_t h = slot * G + g;
+        const int32_t h = (q0 + slot) * G + g;
         if (slot >= slots || h >= nH) break;
         const uint64_t un = uniform(S.U[h]);
         const uint64_t om = uniform(S.open[slot]);
@@ -491,18 +492,18 @@ __device__ __forceinline__ uint32_t load_unranked(const PairInst &I, int32_t rel
     return mine;
 }
 
-// Stored-block rows of the work-group's slots.
+// Stored-block rows of the work-group's slots from q0 on.
 template <int kW>
-__device__ __forceinline__ void load_rows(const PairInst &I, int32_t g, int32_t G, int32_t slots,
-                                          const RankLds &S) {
+__device__ __forceinline__ void load_rows(const PairInst &I, int32_t g, int32_t G, int32_t q0,
+                                          int32_t slots, const RankLds &S) {
     const int32_t nW = I.nBpad / 64;
     for (int32_t q = (int32_t)threadIdx.x; q < slots * nW; q += kW * kWave) {
-        const int32_t tile = (q / nW * G + g) >> 1;
+        const int32_t tile = ((q0 + q / nW) * G + g) >> 1;
         S.rows[q] = tile < I.nB ? I.nz[(size_t)tile * nW + q % nW] : 0ull;
     }
     if (S.idx)
         for (int32_t q = (int32_t)threadIdx.x; q < slots * I.nBpad; q += kW * kWave) {
-            const int32_t tile = (q / I.nBpad * G + g) >> 1;
+            const int32_t tile = ((q0 + q / I.nBpad) * G + g) >> 1;
             S.idx[q] = tile < I.nB ? I.idx[(size_t)tile * I.nBpad + q % I.nBpad] : 0u;
         }
 }
@@ -514,20 +515,60 @@ __device__ __forceinline__ uint32_t rank_done(const PairInst &I, int32_t level0)
     return n;
 }
 
-// Every level from level0 on, for the points that I still holds.
+// This work-group's number g in the team of the launch and the team's size G (0:
+// the team has closed without it).  Every member returns the same size: it is
+// the wanted number once that many have started, else what one exchange of the
+// word fixed, and later starts do not change those bits.
+__device__ __forceinline__ void rank_team(const PairInst &I, int32_t *s_team) {
+    if (threadIdx.x == 0) {
+        uint32_t *word = reinterpret_cast<uint32_t *>(&I.sync->team.v);
+        const uint32_t want = (uint32_t)I.groups;
+        const uint32_t old = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t g = old & 0xffffu;
+        uint32_t G = 0;
+        if (old >> 16 == 0u && g < want) {
+            uint32_t v = old + 1u;
+            const uint64_t t0 = wall_clock64();
+            while (true) {
+                G = v >> 16 ? v >> 16 : ((v & 0xffffu) >= want ? want : 0u);
+                if (G) break;
+                if (wall_clock64() - t0 > kTeamWait) {
+                    // (v has no size yet; where another work-group changed the word it is read again)
+                    const uint32_t closed = v | v << 16;
+                    if (__hip_atomic_compare_exchange_strong(word, &v, closed, __ATOMIC_RELAXED,
+                                                             __ATOMIC_RELAXED,
+                                                             __HIP_MEMORY_SCOPE_AGENT))
+                        v = closed;
+                    continue;
+                }
+                __builtin_amdgcn_s_sleep(1);
+                v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        s_team[0] = (int32_t)g;
+        s_team[1] = (int32_t)G;
+    }
+    __syncthreads();
+}
+
+// Every level from level0 on, for the points that I still holds, by work-group g
+// of G.  Without kKeep a wave has any number of slots, I.rounds of them in LDS
+// at once.
 template <int M, int kW, bool kKeep, bool kSolo>
-__device__ __forceinline__ void rank_levels(PairInst I, int32_t level0, uint32_t *dyn,
-                                            uint32_t *s_new, uint32_t *s_fp, int32_t *s_np) {
+__device__ __forceinline__ void rank_levels(const PairInst &I, int32_t g, int32_t G, int32_t level0,
+                                            uint32_t *dyn, uint32_t *s_new, uint32_t *s_fp,
+                                            int32_t *s_np) {
     uint32_t &s_f = *s_fp;
     int32_t &s_n = *s_np;
     const int tid = (int)threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int lane = (int)lane_id();
-    const int32_t g = kSolo ? 0 : (int32_t)blockIdx.x, G = kSolo ? 1 : (int32_t)gridDim.x;
-    const int32_t rounds = (2 * I.nB + G * kW - 1) / (G * kW);
+    const int32_t all = (2 * I.nB + G * kW - 1) / (G * kW);
+    const int32_t rounds = kKeep ? 1 : min(all, I.rounds);
     RankLds S;
     rank_lds_words(I.nBpad, M, I.lowK, rounds * kW, kSolo, &S, dyn);
-    load_rows<kW>(I, g, G, rounds * kW, S);
+    load_rows<kW>(I, g, G, 0, rounds * kW, S);
     RankPoint<M> P;
     uint32_t done = 0;             // points ranked before this level
     bool found = false;
@@ -555,6 +596,7 @@ __device__ __forceinline__ void rank_levels(PairInst I, int32_t level0, uint32_t
     __syncthreads();
     for (int32_t level = level0;; ++level) {
         if (tid == 0) s_n = 0;
+        if (!kKeep && all > rounds && level > level0) load_rows<kW>(I, g, G, 0, rounds * kW, S);
         const uint32_t mine = load_unranked<M, kW, kSolo>(I, level - level0, S, s_f);
         if (!kSolo) {
             const uint32_t n = wave_sum(mine);
@@ -576,8 +618,20 @@ __device__ __forceinline__ void rank_levels(PairInst I, int32_t level0, uint32_t
             }
             prev = left;
         }
-        const uint32_t fresh = rank_level<M, kW, kKeep, kSolo>(I, level, level0, g, G, rounds,
-                                                             rounds * kW, S, P, &s_n);
+        uint32_t fresh = 0;
+#pragma unroll 1
+        for (int32_t r0 = 0; r0 < (kKeep ? 1 : all); r0 += rounds) {
+            if (r0 > 0) {
+                lds_wait();
+                __syncthreads();
+                if (tid == 0) s_n = 0;
+                load_rows<kW>(I, g, G, r0 * kW, rounds * kW, S);
+                lds_wait();
+                __syncthreads();
+            }
+            fresh = rank_level<M, kW, kKeep, kSolo>(I, level, level0, g, G, r0 * kW, rounds,
+                                                    rounds * kW, S, P, &s_n);
+        }
         if (kSolo && lane == 0) s_new[w] = fresh;
         lds_wait();
         __syncthreads();
@@ -601,8 +655,19 @@ __global__ __launch_bounds__(kRankWaves * kWave) void k_ranks(PairInst I) {
     __shared__ uint32_t s_new[kRankWaves];
     __shared__ uint32_t s_f;
     __shared__ int32_t s_n;
+    __shared__ int32_t s_team[2];
     if (I.sc->err) return;
-    rank_levels<M, kRankWaves, true, kSolo>(I, 0, dyn, s_new, &s_f, &s_n);
+    if constexpr (kSolo) {
+        rank_levels<M, kRankWaves, true, true>(I, 0, 1, 0, dyn, s_new, &s_f, &s_n);
+    } else {
+        rank_team(I, s_team);
+        const int32_t g = uniform(s_team[0]), G = uniform(s_team[1]);
+        if (G == 0) return;
+        if (2 * I.nB <= G * kRankWaves)
+            rank_levels<M, kRankWaves, true, false>(I, g, G, 0, dyn, s_new, &s_f, &s_n);
+        else
+            rank_levels<M, kRankWaves, false, false>(I, g, G, 0, dyn, s_new, &s_f, &s_n);
+    }
 }
 
 // The levels that the first `phases` fronts leave (their number of points is
@@ -613,34 +678,55 @@ __global__ __launch_bounds__(kRestWaves * kWave) void k_ranks_rest(PairInst I, i
     __shared__ uint32_t s_new[kRestWaves];
     __shared__ uint32_t s_f;
     __shared__ int32_t s_n;
+    __shared__ int32_t s_team[2];
     if (I.sc->err) return;
     I = phase_inst(I);
-    if (2 * I.nB <= (int32_t)gridDim.x * kRestWaves)
-        rank_levels<M, kRestWaves, true, false>(I, phases, dyn, s_new, &s_f, &s_n);
+    rank_team(I, s_team);
+    const int32_t g = uniform(s_team[0]), G = uniform(s_team[1]);
+    if (G == 0) return;
+    if (2 * I.nB <= G * kRestWaves)
+        rank_levels<M, kRestWaves, true, false>(I, g, G, phases, dyn, s_new, &s_f, &s_n);
     else
-        rank_levels<M, kRestWaves, false, false>(I, phases, dyn, s_new, &s_f, &s_n);
+        rank_levels<M, kRestWaves, false, false>(I, g, G, phases, dyn, s_new, &s_f, &s_n);
 }
 
-static size_t ranks_lds_bytes(const PairInst &I, int slots, bool solo) {
-    return 4 * rank_lds_words(I.nBpad, I.M, I.lowK, slots, solo, nullptr, nullptr);
+// Problems that one work-group holds, a slot a wave.
+static bool rank_solo(const PairInst &I, int phases) {
+    return phases == 0 && 2 * I.nB <= kRankWaves;
+}
+
+// LDS of a rank launch whose waves hold `rounds` slots each.  (Fewer blocks than
+// at the start may bring the mask units into LDS.)
+static size_t ranks_lds_bytes(const PairInst &I, int phases, int rounds) {
+    const int waves = phases > 0 ? kRestWaves : kRankWaves;
+    return 4 * (rank_lds_words(I.nBpad, I.M, I.lowK, rounds * waves, rank_solo(I, phases), nullptr,
+                               nullptr) +
+                (phases > 0 ? kRankIdxWords : 0));
+}
+
+void rank_shape(PairInst &I, int max_groups, int started) {
+    constexpr size_t kLds = 163840 - 512;  // (the rest is the launches' static part)
+    const int phases = pair_phases(I.N, I.M);
+    const int waves = phases ? kRestWaves : kRankWaves;
+    const int full = (2 * I.nB + waves - 1) / waves;
+    int most = max_groups < kRankMaxGroups ? max_groups : kRankMaxGroups;
+    if (most < 1) most = 1;
+    I.groups = full < most ? full : most;
+    I.started = started > 0 ? started : I.groups;
+    I.rounds = (2 * I.nB + I.groups * waves - 1) / (I.groups * waves);
+    while (I.rounds > 1 && ranks_lds_bytes(I, phases, I.rounds) > kLds) --I.rounds;
 }
 
 template <int M>
 static hipError_t launch_ranks(const PairInst &I, int phases, hipStream_t s) {
-    const dim3 gr((unsigned)I.groups);
-    if (phases > 0) {
-        const int per = I.groups * kRestWaves, rounds = (2 * I.nB + per - 1) / per;
-        // (fewer blocks may bring the mask units into LDS)
-        hipLaunchKernelGGL(k_ranks_rest<M>, gr, dim3(kRestWaves * kWave),
-                           ranks_lds_bytes(I, rounds * kRestWaves, false) + 4 * kRankIdxWords, s, I,
-                           phases);
-    } else if (I.groups == 1) {
-        hipLaunchKernelGGL((k_ranks<M, true>), gr, dim3(kRankWaves * kWave),
-                           ranks_lds_bytes(I, kRankWaves, true), s, I);
-    } else {
-        hipLaunchKernelGGL((k_ranks<M, false>), gr, dim3(kRankWaves * kWave),
-                           ranks_lds_bytes(I, kRankWaves, false), s, I);
-    }
+    const dim3 gr((unsigned)I.started);
+    const size_t lds = ranks_lds_bytes(I, phases, I.rounds);
+    if (phases > 0)
+        hipLaunchKernelGGL(k_ranks_rest<M>, gr, dim3(kRestWaves * kWave), lds, s, I, phases);
+    else if (rank_solo(I, phases))
+        hipLaunchKernelGGL((k_ranks<M, true>), dim3(1), dim3(kRankWaves * kWave), lds, s, I);
+    else
+        hipLaunchKernelGGL((k_ranks<M, false>), gr, dim3(kRankWaves * kWave), lds, s, I);
     return hipGetLastError();
 }
 
