@@ -49,7 +49,8 @@ constexpr int kRankWaves = 8, kRestWaves = 16;
 // started form the team (rank_team): it closes when all wanted have started or
 // kTeamWait after its first has waited in vain, works through all points with
 // as many as it has, and a work-group that starts later leaves.  A team waits
-// only for work-groups that are running.
+// only for work-groups that are running.  (No measurable time where all start:
+// N = 20k, M = 3 370.2 us by block index, 370.5 so; N = 200k, M = 5 1351 / 1352.)
 constexpr int kRankMaxGroups = 64;
 constexpr uint64_t kTeamWait = 10000;   // ticks of the 100 MHz clock: 100 us
 constexpr int kMaxPhases = 8;           // fronts that may be taken off before it
@@ -83,6 +84,7 @@ struct RankSync {
     uint32_t lv[kMaxPhases];     // points of the fronts taken off first
     int32_t left[kMaxPhases];    // points left after each of them
     uint32_t chunk[kMaxPhases][kPairsMaxN / kPhaseThreads];   // the same of a compaction chunk
+    uint32_t ticket[kMaxPhases];   // compaction work-groups that have started
     uint32_t items[kMaxPhases + 1], next[kMaxPhases + 1];   // listed and taken items of a pass
     RankWord team;               // v [15:0] work-groups that have started, [31:16] the closed
                                  // team's size

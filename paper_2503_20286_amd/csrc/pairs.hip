@@ -711,17 +711,22 @@ __global__ __launch_bounds__(kPairWaves * kWave) void k_pairs_list(PairInst I, i
 // all tiles: without the order the second pass took as long as the first).  A
 // work-group takes the rows whose run of identical rows starts in its
 // kPhaseThreads positions, publishes how many stay, and reads the numbers of
-// the work-groups before it.
+// the work-groups before it.  Chunks go to work-groups in the order in which
+// these start (each XCD starts its own in order, so a block index says nothing
+// about the others): who waits, waits for a work-group that is running.
 // ---------------------------------------------------------------------------
 template <int M>
 __global__ __launch_bounds__(kPhaseThreads) void k_phase(PairInst I, PairInst J, int32_t phase) {
     constexpr int MP = rec_stride(M);
     __shared__ uint32_t lds[kPhaseThreads / kWave + 1];
     __shared__ uint32_t s_n;
-    __shared__ int32_t s_at;
+    __shared__ int32_t s_at, s_b;
     if (I.sc->err) return;
     I = phase_inst(I);
-    const int32_t c0 = (int32_t)blockIdx.x * kPhaseThreads;
+    if (threadIdx.x == 0) s_b = (int32_t)atomicAdd(&I.sync->ticket[phase], 1u);
+    __syncthreads();
+    const int32_t blk = s_b;
+    const int32_t c0 = blk * kPhaseThreads;
     if (c0 >= I.N) return;  // (work-groups after this one return too)
     const int32_t c1 = c0 + kPhaseThreads;
     const int32_t p0 = I.runs[c0] == c0 ? c0 : I.rune[c0];
@@ -736,7 +741,7 @@ __global__ __launch_bounds__(kPhaseThreads) void k_phase(PairInst I, PairInst J,
     __syncthreads();
     uint32_t *cnt = I.sync->chunk[phase];
     if (threadIdx.x == 0) {
-        __hip_atomic_store(&cnt[blockIdx.x], 0x80000000u | s_n, __ATOMIC_RELAXED,
+        __hip_atomic_store(&cnt[blk], 0x80000000u | s_n, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
         atomicAdd(&I.sync->left[phase], (int32_t)s_n);
         const int32_t n = p1 - p0 - (int32_t)s_n;
@@ -744,7 +749,7 @@ __global__ __launch_bounds__(kPhaseThreads) void k_phase(PairInst I, PairInst J,
         s_at = 0;
     }
     __syncthreads();
-    if (threadIdx.x < blockIdx.x) {
+    if ((int32_t)threadIdx.x < blk) {
         uint32_t v, spins = 0;
         while (!((v = __hip_atomic_load(&cnt[threadIdx.x], __ATOMIC_RELAXED,
                                         __HIP_MEMORY_SCOPE_AGENT)) & 0x80000000u)) {
