@@ -39,7 +39,10 @@ __device__ __forceinline__ void copy_rec(uint32_t *__restrict__ d, const uint32_
 
 // ---------------------------------------------------------------------------
 // split (one launch per level): single-pass ordered partition with a
-// decoupled look-back over per-block counts.
+// decoupled look-back over per-block counts.  Tiles go to blocks in the order in
+// which these start (each XCD starts its own in order, so a block index says
+// nothing about the others): who waits, waits for a block that is running.  The
+// ticket is the entry behind the blocks' states.
 // ---------------------------------------------------------------------------
 template <int M>
 __global__ __launch_bounds__(kThreads) void k_split(
@@ -51,7 +54,11 @@ __global__ __launch_bounds__(kThreads) void k_split(
     constexpr int MP = rec_stride(M);
     __shared__ uint32_t lds[17];
     __shared__ uint32_t s_pref[2];
-    if (threadIdx.x == 0) lb_next[blockIdx.x] = 0;  // ready for the next level
+    __shared__ int32_t s_blk;
+    if (threadIdx.x == 0) {  // ready for the next level
+        lb_next[blockIdx.x] = 0;
+        if (blockIdx.x == 0) lb_next[gridDim.x] = 0;
+    }
     if (sc->err) return;
     const int32_t n = n_static >= 0 ? n_static : usize[level - 1];
     if (n_static < 0 && n > 0 && fsize[level - 1] == 0) {  // impossible for a partial order
@@ -62,7 +69,11 @@ __global__ __launch_bounds__(kThreads) void k_split(
         if (blockIdx.x == 0 && threadIdx.x == 0) { fsize[level] = 0; usize[level] = 0; }
         return;
     }
-    const int32_t e0 = (int32_t)blockIdx.x * kSplitTile;
+    if (threadIdx.x == 0)
+        s_blk = (int32_t)atomicAdd((unsigned long long *)&lb_cur[gridDim.x], 1ull);
+    __syncthreads();
+    const int32_t blk = s_blk;
+    const int32_t e0 = blk * kSplitTile;
     if (e0 >= n) return;
     const int32_t nb = (n + kSplitTile - 1) / kSplitTile;
     // each thread owns kSplitItems consecutive elements
@@ -87,14 +98,14 @@ __global__ __launch_bounds__(kThreads) void k_split(
         const uint32_t bf = tot >> 16, bu = tot & 0xffffu;
         const int lane = (int)lane_id();
         uint32_t pf = 0, pu = 0;
-        if (blockIdx.x == 0) {
+        if (blk == 0) {
             if (lane == 0)
                 __hip_atomic_store(&lb_cur[0], lb_pack(2, bf, bu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else {
             if (lane == 0)
-                __hip_atomic_store(&lb_cur[blockIdx.x], lb_pack(1, bf, bu), __ATOMIC_RELAXED,
+                __hip_atomic_store(&lb_cur[blk], lb_pack(1, bf, bu), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
-            int32_t base = (int32_t)blockIdx.x - 1;
+            int32_t base = blk - 1;
             uint64_t spins = 0;
             while (true) {
                 const int32_t q = base - lane;
@@ -120,13 +131,13 @@ __global__ __launch_bounds__(kThreads) void k_split(
                 base -= kWave;
             }
             if (lane == 0)
-                __hip_atomic_store(&lb_cur[blockIdx.x], lb_pack(2, pf + bf, pu + bu), __ATOMIC_RELAXED,
+                __hip_atomic_store(&lb_cur[blk], lb_pack(2, pf + bf, pu + bu), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
         }
         if (lane == 0) {
             s_pref[0] = pf;
             s_pref[1] = pu;
-            if ((int32_t)blockIdx.x == nb - 1) {
+            if (blk == nb - 1) {
                 fsize[level] = (int32_t)(pf + bf);
                 usize[level] = (int32_t)(pu + bu);
             }

@@ -40,3 +40,27 @@ def test_any_team_ranks_every_point(kind, N, M, groups, started, monkeypatch):
         assert np.array_equal(res.dom_in.cpu().numpy(), din)
         assert np.array_equal(res.dom_out.cpu().numpy(), dout)
     ctx.close()
+
+
+def test_streams_of_both_paths_at_once():
+    """Four contexts on four streams: above the spatial path's limit (cooperative
+    peel), with fronts taken off first, one rank launch, one work-group."""
+    import torch
+    probs = [(_objs("sphere", n, m, n), m) for n, m in ((210000, 4), (120000, 5), (20000, 3), (900, 2))]
+    refs = [torch.eye(m, device="cuda") + 0.1 for _, m in probs]
+    objs = [torch.from_numpy(f).cuda() for f, _ in probs]
+    ctx = [nsga3.Context(0) for _ in probs]
+    want = [nsga3.select(o, r, len(o) // 2, ctx=c) for o, r, c in zip(objs, refs, ctx)]
+    streams = [torch.cuda.Stream() for _ in probs]
+    torch.cuda.synchronize()
+    got = []
+    for _ in range(4):
+        for o, r, c, s in zip(objs, refs, ctx, streams):
+            with torch.cuda.stream(s):
+                got.append(nsga3.select(o, r, len(o) // 2, ctx=c))
+    torch.cuda.synchronize()
+    for q, g in enumerate(got):
+        w = want[q % len(probs)]
+        assert g.info().status == 0
+        for k in ("rank", "dom_in", "dom_out", "selected"):
+            assert torch.equal(getattr(g, k), getattr(w, k)), (q, k)
