@@ -93,7 +93,7 @@ struct Layout {
     size_t rank, niche, dist64, rhat64, rhat32, rhat16, p_asf, p_idx, p_nad;
     size_t rho, bcount, bstart, bcursor, gstart, bd, bi, selflag, sc, bar;
     // spatially ordered path (layout_pairs)
-    size_t spl, cell, code, slot, trec, box, nz, idx, mask, low, ex, pos, wit, sync, runs2, rune2, din2, list;
+    size_t spl, heavy, cell, code, slot, trec, box, nz, idx, mask, low, ex, pos, wit, sync, runs2, rune2, din2, list;
     size_t zero, zero_words;   // counters the path clears first
     size_t total;
 };
@@ -182,7 +182,7 @@ Layout layout_pairs(int64_t N, int M, int H) {
     int T = 0;
     pair_cell_bits(N, M, bits, &T);
     L.zero = c;
-    L.cell = bump(c, 4 * (((size_t)1 << T) + 1));
+    L.cell = bump(c, 4 * ((size_t)pair_cells(T) + 1));
     L.dom_in_s = bump(c, 4 * n);
     L.dom_out_s = bump(c, 4 * n);
     L.nz = bump(c, nB * nBp / 8);
@@ -195,6 +195,7 @@ Layout layout_pairs(int64_t N, int M, int H) {
     const size_t ot = oneshot_temp_bytes(N);
     L.temp = bump(c, ot > temp ? ot : temp);
     L.spl = bump(c, 4 * 64 * (size_t)M);
+    L.heavy = bump(c, 4 * (1 + (size_t)kHeavyRows * (M + 1)));
     L.code = bump(c, 4 * n);
     L.slot = bump(c, 4 * n);
     L.trec = bump(c, 4 * n * MP);
@@ -451,6 +452,7 @@ PairInst pair_inst(char *w, const Layout &L, const nsga3_problem &p, int32_t *ra
     pair_cell_bits(p.N, p.M, I.bits, &I.T);
     I.spl = WS(uint32_t, spl);
     I.cell = WS(uint32_t, cell);
+    I.heavy = WS(uint32_t, heavy);
     I.code = WS(uint32_t, code);
     I.slot = WS(uint32_t, slot);
     I.trec = WS(uint32_t, trec);

@@ -34,6 +34,10 @@ constexpr int64_t kPairsMaxN = 204800;   // largest problem of this path
 constexpr int kSplitterSample = 1024;   // keys sampled per objective for the cell splitters
 constexpr int kSplitterMaxBits = 6;     // cells per objective: at most 64
 constexpr int kCellMaxBits = 16;
+constexpr int kHeavyRows = 64;          // rows that are a large share of the points: cells of their own
+constexpr int kHeavySample = 16;        // of the sampled rows, at least
+constexpr int kHeavyMinN = 4096;        // fewer points count their cells (at most 20 us; finding the
+                                        // rows costs every call 2 us)
 constexpr int kListItem = 8;            // blocks of a listed pair item
 constexpr int kListGroups = 1536;       // work-groups that take them (six a CU)
 constexpr int kPairWaves = 4;           // 128-point tiles of a pair work-group (one per wave)
@@ -105,7 +109,8 @@ struct PairInst {
     int32_t rounds;           // 64-point groups of a wave that its LDS holds at once
     uint8_t bits[16];         // cell code bits per objective
     uint32_t *spl;            // [M * 64] splitters
-    uint32_t *cell;           // [2^T + 1] counts, then starts
+    uint32_t *cell;           // [pair_cells(T) + 1] counts, then starts
+    uint32_t *heavy;          // number of heavy rows, then hash and keys of each
     uint32_t *code, *slot;    // [N] cell, arrival position in it
     uint32_t *trec;           // [N * rec_stride] records in cell order (keys, point index);
                               // afterwards the other buffer of the phases
@@ -162,6 +167,10 @@ __device__ __forceinline__ PairInst phase_inst(PairInst I) {
 inline int pair_phases(int64_t N, int M) {
     return N <= 32768 ? 0 : N <= 65536 || M >= 8 ? 2 : 5;
 }
+
+// Cells of T code bits, and behind them those of the heavy rows.
+__host__ __device__ inline int pair_heavy_cell(int T) { return T < 2 ? 4 : 1 << T; }
+__host__ __device__ inline int pair_cells(int T) { return pair_heavy_cell(T) + kHeavyRows; }
 
 inline void pair_cell_bits(int64_t N, int M, uint8_t *bits, int *T) {
     int lg = 0;

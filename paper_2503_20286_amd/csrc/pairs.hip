@@ -13,15 +13,9 @@ namespace nsga3 {
 // ---------------------------------------------------------------------------
 // order: splitters per objective, cell counts, placement, order inside a cell
 // ---------------------------------------------------------------------------
-// Quantile splitters of one objective from an evenly spaced sample (sorted by
-// a bitonic network in LDS).  Only the order of the points depends on them,
-// never a result.
-__device__ __forceinline__ void splitters_item(const PairInst &I, int k, uint32_t *s) {
-    const int nb = I.bits[k];
-    if (nb == 0) return;
-    const int S = I.N < kSplitterSample ? I.N : kSplitterSample;
+// Sorts one value a thread by a bitonic network.
+__device__ __forceinline__ void sort_sample(uint32_t v, uint32_t *s) {
     const int t = (int)threadIdx.x;
-    uint32_t v = t < S ? order_key(I.objs[((int64_t)t * I.N / S) * I.M + k]) : 0xffffffffu;
     for (int len = 2; len <= kSplitterSample; len <<= 1) {
         for (int d = len >> 1; d > 0; d >>= 1) {
             uint32_t o;
@@ -39,27 +33,106 @@ __device__ __forceinline__ void splitters_item(const PairInst &I, int k, uint32_
     }
     s[t] = v;
     __syncthreads();
-    const int n = 1 << nb;
-    if (t < n - 1) I.spl[k * 64 + t] = s[(int)((int64_t)(t + 1) * S / n)];
 }
 
-// Splitters (block k < M: objective k), the call's scalars, and zeros for the
-// counters.
+// Sampled points: one of each of up to kSplitterSample equal stretches, anywhere in
+// it, so that populations with a period are met in all its places.
+__device__ __forceinline__ int sample_size(const PairInst &I) {
+    return I.N < kSplitterSample ? I.N : kSplitterSample;
+}
+__device__ __forceinline__ uint32_t sample_point(const PairInst &I, int t) {
+    const uint32_t N = (uint32_t)I.N, u = (uint32_t)t;  // (t N < 2^28)
+    if (N < (uint32_t)kSplitterSample) return u < N ? u : 0u;
+    const uint32_t a = u * N / kSplitterSample, b = (u + 1u) * N / kSplitterSample;
+    return a + __umulhi(u * 0x9e3779b1u, b - a);
+}
+
+// Hash of a row of keys, 22 bits.
+__device__ __forceinline__ uint32_t row_hash(uint32_t h, uint32_t key) {
+    h = (h ^ key) * 0x85ebca6bu;
+    return h ^ (h >> 15);
+}
+__device__ __forceinline__ int hash_key(int q, int M) { return M <= 5 ? q : q * M / 5; }
+__device__ __forceinline__ uint32_t row_hash_end(uint32_t h) { return (h * 0xc2b2ae35u) >> 10; }
+
+// Quantile splitters of objective k < M from the sample; k == M: the rows that it
+// holds kHeavySample times (one point in 64 or more is identical to each), which
+// get cells of their own, in which nothing is compared (200k identical rows, M =
+// 5: the call 81 ms when each counted its cell, 22.7 by searches in it, 15.6 so, of
+// which 15.1 go to the one reference's bucket).
+// Only the order of the points depends on either, never a result.
+__device__ __forceinline__ void sample_item(const PairInst &I, int k, uint32_t *s, uint32_t *lds) {
+    const int M = I.M;
+    const int S = sample_size(I);
+    const int t = (int)threadIdx.x;
+    const float *row = I.objs + (int64_t)sample_point(I, t) * M;
+    uint32_t v;
+    if (k < M) {
+        v = order_key(row[k]);
+    } else if (I.N <= kHeavyMinN) {
+        if (t == 0) I.heavy[0] = 0u;
+        return;
+    } else {
+        // (five keys tell rows apart well enough, the cells' codes compare them all)
+        float f[5];
+#pragma unroll
+        for (int q = 0; q < 5; ++q)
+            if (q < M) f[q] = row[hash_key(q, M)];
+        v = 0;
+#pragma unroll
+        for (int q = 0; q < 5; ++q)
+            if (q < M) v = row_hash(v, order_key(f[q]));
+        v = row_hash_end(v) << 10 | (uint32_t)t;
+        // nothing to sort unless some bucket of hashes holds as many
+        s[t] = 0u;
+        __syncthreads();
+        if (t < S) atomicAdd(&s[v >> 22], 1u);
+        lds_wait();
+        __syncthreads();
+        const uint32_t c = s[t];
+        if (!__syncthreads_or(c >= (uint32_t)kHeavySample)) {
+            if (t == 0) I.heavy[0] = 0u;
+            return;
+        }
+    }
+    sort_sample(t < S ? v : 0xffffffffu, s);  // (one copy of it: the launch waits for its code, too)
+    if (k < M) {
+        const int n = 1 << I.bits[k];
+        if (t < n - 1) I.spl[k * 64 + t] = s[(int)((int64_t)(t + 1) * S / n)];
+        return;
+    }
+    const uint32_t g = s[t] >> 10;
+    const bool is = (t == 0 || s[t - 1] >> 10 != g) && t + kHeavySample <= S &&
+                    s[t + kHeavySample - 1] >> 10 == g;
+    uint32_t n;
+    const uint32_t j = block_exclusive_scan(is ? 1u : 0u, lds, &n);  // ascending in the hash
+    if (t == 0) I.heavy[0] = n < (uint32_t)kHeavyRows ? n : (uint32_t)kHeavyRows;
+    if (is && j < (uint32_t)kHeavyRows) {
+        uint32_t *e = I.heavy + 1 + j * (uint32_t)(M + 1);
+        row = I.objs + (int64_t)sample_point(I, (int)(s[t] & 1023u)) * M;
+        e[0] = g;
+        for (int q = 0; q < M; ++q) e[1 + q] = order_key(row[q]);
+    }
+}
+
+// Splitters (block k < M: objective k), heavy rows (block M), the call's scalars,
+// and zeros for the counters.
 __global__ __launch_bounds__(kSplitterSample) void k_pair_setup(PairInst I, uint32_t *zero,
                                                                 int64_t nzero, int nfill) {
     __shared__ uint32_t s[kSplitterSample];
-    const int b = (int)blockIdx.x;
-    if (b < I.M) {
-        splitters_item(I, b, s);
+    __shared__ uint32_t lds[kSplitterSample / kWave + 1];
+    if ((int)blockIdx.x <= I.M) {
+        sample_item(I, (int)blockIdx.x, s, lds);
         return;
     }
-    if (b == I.M) {
+    const int b = (int)blockIdx.x - I.M - 1;
+    if (b == 0) {
         init_scalars(I.sc, (int)threadIdx.x);
         if (threadIdx.x < kWBlk)
             I.mask[(size_t)kMaskPools * I.poolUnits * kWBlk + threadIdx.x] =
                 make_uint4(~0u, ~0u, ~0u, ~0u);
     }
-    const int64_t t = (int64_t)(b - I.M) * kSplitterSample + threadIdx.x;
+    const int64_t t = (int64_t)b * kSplitterSample + threadIdx.x;
     for (int64_t q = t; q < nzero; q += (int64_t)nfill * kSplitterSample) zero[q] = 0u;
 }
 
@@ -77,6 +150,7 @@ __global__ __launch_bounds__(256) void k_cell_code(PairInst I) {
     bool bad = false;
     uint32_t code = 0;
     uint32_t bk[16];
+    const int nh = (int)I.heavy[0];
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
         if (k < M) {
@@ -101,16 +175,41 @@ __global__ __launch_bounds__(256) void k_cell_code(PairInst I) {
         for (int k = 0; k < 16; ++k)
             if (k < M && pl < (int)I.bits[k]) code = (code << 1) | ((bk[k] >> pl) & 1u);
     if (ballot(bad) && lane_id() == 0) atomicOr(&I.sc->err, (uint32_t)kErrNonfiniteObj);
-    // one atomic for a wave whose points share a cell (many identical rows)
-    const uint32_t c0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)code);
-    uint32_t slot = 0;
-    const uint64_t act = ballot(in);
-    if (ballot(in && code == c0) == act) {
-        if (lane_id() == 0 && act) slot = atomicAdd(&I.cell[c0], (uint32_t)__popcll(act));
-        slot = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot) + lanes_below(act);
-    } else if (in) {
-        slot = atomicAdd(&I.cell[code], 1u);
+    if (nh > 0 && in) {
+        uint32_t hash = 0;
+        for (int q = 0; q < 5 && q < M; ++q)
+            hash = row_hash(hash, order_key(I.objs[i * M + hash_key(q, M)]));
+        hash = row_hash_end(hash);
+        int j = 0;  // heavy rows of smaller hash
+        for (int s = nh; s > 0;) {
+            const int q = s >> 1;
+            const bool go = I.heavy[1 + (j + q) * (M + 1)] < hash;
+            j = go ? j + q + 1 : j;
+            s = go ? s - q - 1 : q;
+        }
+        if (j < nh) {
+            const uint32_t *e = I.heavy + 1 + j * (M + 1);
+            bool eq = e[0] == hash;
+            for (int k = 0; k < M && eq; ++k) eq = e[1 + k] == order_key(I.objs[i * M + k]);
+            if (eq) code = (uint32_t)(pair_heavy_cell(I.T) + j);
+        }
     }
+    // points of a wave that share a cell take one atomic, the first few cells'
+    // (heavy rows, or tight clusters)
+    uint32_t slot = 0;
+    uint64_t act = ballot(in);
+    for (int q = 0; q < (nh > 0 ? 4 : 1) && act; ++q) {
+        const int l = __builtin_ctzll(act);
+        const uint32_t c0 = (uint32_t)__builtin_amdgcn_readlane((int)code, l);
+        const uint64_t same = ballot(((act >> lane_id()) & 1) != 0 && code == c0);
+        if (nh == 0 && same != act) break;
+        uint32_t n = 0;
+        if ((int)lane_id() == l) n = atomicAdd(&I.cell[c0], (uint32_t)__popcll(same));
+        n = (uint32_t)__builtin_amdgcn_readlane((int)n, l) + lanes_below(same);
+        if ((same >> lane_id()) & 1) slot = n;
+        act &= ~same;
+    }
+    if ((act >> lane_id()) & 1) slot = atomicAdd(&I.cell[code], 1u);
     if (in) {
         I.code[i] = code;
         I.slot[i] = slot;
@@ -127,11 +226,11 @@ __global__ __launch_bounds__(1024) void k_cell_scan(PairInst I, RefArgs R) {
         reference_item(R, I.M, (int)(blockIdx.x - 1) * 1024 + (int)threadIdx.x, I.sc);
         return;
     }
-    // a thread's up to 64 consecutive counts stay in registers between the sum
+    // a thread's up to 68 consecutive counts stay in registers between the sum
     // and the starts (65536 cells: 24 us when they were read one by one, twice)
-    constexpr int kVec = (1 << kCellMaxBits) / 1024 / 4;
-    const int n = 1 << I.T;
-    const int per = n >= 4096 ? n / 1024 : 4;  // (a multiple of 4; few cells: few threads)
+    const int n = pair_cells(I.T);
+    constexpr int kVec = ((1 << kCellMaxBits) + kHeavyRows + 4095) / 4096;
+    const int per = (n + 4095) / 4096 * 4;
     const int s0 = (int)threadIdx.x * per;
     uint32_t *c = I.cell + s0;
     uint32_t v[4 * kVec];
@@ -139,12 +238,7 @@ __global__ __launch_bounds__(1024) void k_cell_scan(PairInst I, RefArgs R) {
 #pragma unroll
     for (int q = 0; q < kVec; ++q) {
         uint4 x = make_uint4(0, 0, 0, 0);
-        if (4 * q < per && s0 + 4 * q + 4 <= n)
-            x = *reinterpret_cast<const uint4 *>(c + 4 * q);
-        else if (q == 0 && n < 4 && s0 == 0) {
-            x.x = c[0];
-            x.y = n > 1 ? c[1] : 0u;
-        }
+        if (4 * q < per && s0 + 4 * q < n) x = *reinterpret_cast<const uint4 *>(c + 4 * q);
         v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
         sum += x.x + x.y + x.z + x.w;
     }
@@ -158,12 +252,7 @@ __global__ __launch_bounds__(1024) void k_cell_scan(PairInst I, RefArgs R) {
         x.z = x.y + v[4 * q + 1];
         x.w = x.z + v[4 * q + 2];
         run = x.w + v[4 * q + 3];
-        if (4 * q < per && s0 + 4 * q + 4 <= n)
-            *reinterpret_cast<uint4 *>(c + 4 * q) = x;
-        else if (q == 0 && n < 4 && s0 == 0) {
-            c[0] = x.x;
-            if (n > 1) c[1] = x.y;
-        }
+        if (4 * q < per && s0 + 4 * q < n) *reinterpret_cast<uint4 *>(c + 4 * q) = x;
     }
     if (threadIdx.x == 0) I.cell[n] = tot;
 }
@@ -188,43 +277,202 @@ __global__ __launch_bounds__(256) void k_cell_place(PairInst I) {
 
 // Final position: inside its cell a point comes after every lexicographically
 // smaller row and every identical row of smaller index, so identical rows end
-// up adjacent (they share a cell).
-template <int M>
-__global__ __launch_bounds__(256) void k_cell_sort(PairInst I) {
-    constexpr int MP = rec_stride(M);
-    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (p >= I.N) return;
-    uint32_t x[M];
+// up adjacent (they share a cell).  A point counts its cell alone where that is
+// small; the splitters cut each objective by itself, so identical rows and
+// objectives that move together may put any share of the points into one cell.
+constexpr int kCellOwn = 256;     // positions of a work-group
+constexpr uint32_t kCellWide = 1024;   // points of a cell that a point counts alone
+
+// x before y in the order of rows (kEq: or the same).
+template <int M, bool kEq>
+__device__ __forceinline__ bool row_before(const uint32_t (&x)[M], const uint32_t *y, int stride) {
+    bool lt = false, eq = true;
 #pragma unroll
-    for (int k = 0; k < M; ++k) x[k] = I.trec[(size_t)p * MP + k];
-    const uint32_t i = I.trec[(size_t)p * MP + M];
-    const uint32_t c = I.code[i];
-    const uint32_t c0 = I.cell[c], c1 = I.cell[c + 1];
-    uint32_t less = 0, same = 0, before = 0;
-    for (uint32_t q = c0; q < c1; ++q) {
-        const uint32_t *r = I.trec + (size_t)q * MP;
-        bool lt = false, eq = true;
-#pragma unroll
-        for (int k = 0; k < M; ++k) {
-            const uint32_t y = r[k];
-            lt = lt || (eq && y < x[k]);
-            eq = eq && y == x[k];
-        }
-        less += lt ? 1u : 0u;
-        same += eq ? 1u : 0u;
-        before += (eq && r[M] < i) ? 1u : 0u;
+    for (int k = 0; k < M; ++k) {
+        const uint32_t v = y[k * stride];
+        lt = lt || (eq && x[k] < v);
+        eq = eq && x[k] == v;
     }
-    const uint32_t run = c0 + less, at = run + before;
+    return lt || (kEq && eq);
+}
+
+// Record, point index and run of identical rows [run, end) of position at.
+template <int M>
+__device__ __forceinline__ void put_row(const PairInst &I, const uint32_t (&x)[M], uint32_t i,
+                                        uint32_t at, uint32_t run, uint32_t end) {
+    constexpr int MP = rec_stride(M);
     uint32_t v[MP];
 #pragma unroll
-    for (int k = 0; k < MP; ++k) v[k] = k < M ? x[k] : (k == M ? at : 0u);
+    for (int k = 0; k < MP; ++k) v[k] = k < M ? x[k < M ? k : 0] : (k == M ? at : 0u);
     uint4 *dst = reinterpret_cast<uint4 *>(I.recs + (size_t)at * MP);
 #pragma unroll
     for (int q = 0; q < MP / 4; ++q)
         dst[q] = make_uint4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
     I.sval[at] = i;
     I.runs[at] = (int32_t)run;
-    I.rune[at] = (int32_t)(run + same);
+    I.rune[at] = (int32_t)end;
+}
+
+// A wide cell [c0, c1), of which the work-group has the points at positions
+// [a, b): they are put in order in LDS, and every point of the cell is looked up
+// among them; the numbers of points that fall between them give each one's
+// place.  The cell costs a work-group its size / 256 times three searches of 8
+// steps instead of its size (N = 200k, M = 5, rows near one line, 27k points in
+// a cell: the call 19.4 ms alone, 14.1 so, 0.34 of them here).
+template <int M>
+struct WideCell {
+    uint32_t key[M][kCellOwn];
+    uint32_t idx[kCellOwn];
+    uint32_t le[kCellOwn + 1], lt[kCellOwn + 1], at[kCellOwn + 1];
+    uint32_t scan[kCellOwn / kWave + 1];
+};
+
+template <int M>
+__device__ __forceinline__ void wide_cell(const PairInst &I, WideCell<M> &W, uint32_t c0, uint32_t c1,
+                                          uint32_t a, uint32_t b) {
+    constexpr int MP = rec_stride(M);
+    const int t = (int)threadIdx.x;
+    const int n = (int)(b - a);
+    uint32_t x[M], i = 0xffffffffu;   // (places past the last point: after every row)
+#pragma unroll
+    for (int k = 0; k < M; ++k) x[k] = 0xffffffffu;
+    if (t < n) {
+        const uint32_t *r = I.trec + (size_t)(a + (uint32_t)t) * MP;
+#pragma unroll
+        for (int k = 0; k < M; ++k) x[k] = r[k];
+        i = r[M];
+    }
+    for (int len = 2; len <= kCellOwn; len <<= 1) {
+        for (int d = len >> 1; d > 0; d >>= 1) {
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < M; ++k) W.key[k][t] = x[k];
+            W.idx[t] = i;
+            __syncthreads();
+            const int o = t ^ d;
+            const uint32_t oi = W.idx[o];
+            const bool lt = row_before<M, false>(x, &W.key[0][o], kCellOwn);
+            const bool le = row_before<M, true>(x, &W.key[0][o], kCellOwn);
+            const bool first = lt || (le && i < oi);
+            if (first != (((t & len) == 0) == ((t & d) == 0))) {
+#pragma unroll
+                for (int k = 0; k < M; ++k) x[k] = W.key[k][o];
+                i = oi;
+            }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < M; ++k) W.key[k][t] = x[k];
+    W.idx[t] = i;
+    for (int q = t; q <= kCellOwn; q += kCellOwn) W.le[q] = W.lt[q] = W.at[q] = 0u;
+    __syncthreads();
+    for (uint32_t q = c0 + (uint32_t)t; q < c1; q += kCellOwn) {
+        uint32_t y[M];
+        const uint32_t *r = I.trec + (size_t)q * MP;
+#pragma unroll
+        for (int k = 0; k < M; ++k) y[k] = r[k];
+        const uint32_t yi = r[M];
+        int lo = 0, hi;   // points here before y's row, and not after it
+        for (int s = n; s > 0;) {
+            const int h = s >> 1;
+            const bool go = !row_before<M, true>(y, &W.key[0][lo + h], kCellOwn);
+            lo = go ? lo + h + 1 : lo;
+            s = go ? s - h - 1 : h;
+        }
+        hi = lo;
+        if (lo < n && !row_before<M, false>(y, &W.key[0][lo], kCellOwn)) {
+            for (int s = n - lo; s > 0;) {
+                const int h = s >> 1;
+                const bool go = !row_before<M, false>(y, &W.key[0][hi + h], kCellOwn);
+                hi = go ? hi + h + 1 : hi;
+                s = go ? s - h - 1 : h;
+            }
+        }
+        int e = lo;       // and those of its row up to its own index
+        for (int s = hi - lo; s > 0;) {
+            const int h = s >> 1;
+            const bool go = W.idx[e + h] <= yi;
+            e = go ? e + h + 1 : e;
+            s = go ? s - h - 1 : h;
+        }
+        atomicAdd(&W.le[lo], 1u);
+        atomicAdd(&W.lt[hi], 1u);
+        atomicAdd(&W.at[e], 1u);
+    }
+    lds_wait();
+    __syncthreads();
+    // point s comes after every y that falls at s or before
+    uint32_t tot;
+    const uint32_t vle = W.le[t], vlt = W.lt[t], vat = W.at[t];
+    const uint32_t le = vle + block_exclusive_scan(vle, W.scan, &tot);
+    __syncthreads();
+    const uint32_t lt = vlt + block_exclusive_scan(vlt, W.scan, &tot);
+    __syncthreads();
+    const uint32_t at = c0 + vat + block_exclusive_scan(vat, W.scan, &tot);
+    if (t < n) put_row<M>(I, x, i, at, c0 + lt, c0 + le);
+    lds_wait();
+    __syncthreads();
+}
+
+template <int M>
+__global__ __launch_bounds__(kCellOwn) void k_cell_sort(PairInst I) {
+    constexpr int MP = rec_stride(M);
+    __shared__ WideCell<M> W;
+    __shared__ uint32_t s_from;
+    const uint32_t p0 = blockIdx.x * (uint32_t)kCellOwn, p = p0 + threadIdx.x, N = (uint32_t)I.N;
+    uint32_t c0 = 0, c1 = 0;
+    if (p < N) {
+        uint32_t x[M];
+#pragma unroll
+        for (int k = 0; k < M; ++k) x[k] = I.trec[(size_t)p * MP + k];
+        const uint32_t i = I.trec[(size_t)p * MP + M];
+        const uint32_t c = I.code[i];
+        c0 = I.cell[c];
+        c1 = I.cell[c + 1];
+        if (c >= (uint32_t)pair_heavy_cell(I.T)) {  // identical rows, in any order
+            put_row<M>(I, x, i, p, c0, c1);
+            c1 = c0;
+        } else if (c1 - c0 <= kCellWide) {
+            uint32_t less = 0, same = 0, before = 0;
+            for (uint32_t q = c0; q < c1; ++q) {
+                const uint32_t *r = I.trec + (size_t)q * MP;
+                bool lt = false, eq = true;
+#pragma unroll
+                for (int k = 0; k < M; ++k) {
+                    const uint32_t y = r[k];
+                    lt = lt || (eq && y < x[k]);
+                    eq = eq && y == x[k];
+                }
+                less += lt ? 1u : 0u;
+                same += eq ? 1u : 0u;
+                before += (eq && r[M] < i) ? 1u : 0u;
+            }
+            const uint32_t run = c0 + less;
+            put_row<M>(I, x, i, run + before, run, run + same);
+        }
+    }
+    const bool wide = c1 - c0 > kCellWide;
+    if (!__syncthreads_or(wide)) return;
+    // the wide cells of the work-group's positions, in order (its first points here tell)
+    for (uint32_t from = p0;;) {
+        if (threadIdx.x == 0) s_from = 0xffffffffu;
+        __syncthreads();
+        if (wide && p >= from) atomicMin(&s_from, p);
+        lds_wait();
+        __syncthreads();
+        const uint32_t a = s_from;
+        if (a == 0xffffffffu) return;
+        __syncthreads();
+        __shared__ uint32_t s_c[2];
+        if (p == a) { s_c[0] = c0; s_c[1] = c1; }
+        lds_wait();
+        __syncthreads();
+        const uint32_t d0 = s_c[0], d1 = s_c[1];
+        const uint32_t end = min(p0 + (uint32_t)kCellOwn, N), b = min(d1, end);
+        wide_cell<M>(I, W, d0, d1, a, b);
+        from = b;
+    }
 }
 
 // Small problems: the whole order by one work-group of a thread a point.  A
@@ -237,7 +485,6 @@ constexpr int kOrderOneRefs = 4096;   // (it also scales the references, and cle
 template <int M>
 __global__ __launch_bounds__(kOrderOne) void k_order_one(PairInst I, RefArgs R, uint32_t *zero,
                                                          int64_t nzero) {
-    constexpr int MP = rec_stride(M);
     __shared__ uint32_t row[kOrderOne * M];
     __shared__ uint32_t smin[M];
     const int t = (int)threadIdx.x;
@@ -279,17 +526,7 @@ __global__ __launch_bounds__(kOrderOne) void k_order_one(PairInst I, RefArgs R, 
             same += eq ? 1u : 0u;
             before += (eq && q < t) ? 1u : 0u;
         }
-        const uint32_t at = less + before;
-        uint32_t v[MP];
-#pragma unroll
-        for (int k = 0; k < MP; ++k) v[k] = k < M ? x[k] : (k == M ? at : 0u);
-        uint4 *dst = reinterpret_cast<uint4 *>(I.recs + (size_t)at * MP);
-#pragma unroll
-        for (int q = 0; q < MP / 4; ++q)
-            dst[q] = make_uint4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-        I.sval[at] = (uint32_t)t;
-        I.runs[at] = (int32_t)less;
-        I.rune[at] = (int32_t)(less + same);
+        put_row<M>(I, x, (uint32_t)t, less + before, less, less + same);
     }
     __syncthreads();
     if (t < M) I.sc->min_key[t] = smin[t];
@@ -648,9 +885,9 @@ __global__ __launch_bounds__(256) void k_pair_list(PairInst I, int32_t pass) {
         const int32_t a = wd * 64 + lane;
         const bool in = a < nB;
         bool ok[kPairWaves];
-        uint32_t need[kPairWaves];
+        uint32_t need[kPairWaves], apart[kPairWaves];  // (boxes that only touch: no strict inequality)
 #pragma unroll
-        for (int u = 0; u < kPairWaves; ++u) { ok[u] = in; need[u] = 0; }
+        for (int u = 0; u < kPairWaves; ++u) { ok[u] = in; need[u] = apart[u] = 0; }
 #pragma unroll
         for (int k = 0; k < M; ++k) {
             const uint32_t alo = in ? I.box[(size_t)k * nBp + a] : 0u;
@@ -658,12 +895,13 @@ __global__ __launch_bounds__(256) void k_pair_list(PairInst I, int32_t pass) {
 #pragma unroll
             for (int u = 0; u < kPairWaves; ++u) {
                 ok[u] = ok[u] && alo <= hi[u][k];
+                apart[u] |= alo ^ hi[u][k];
                 need[u] |= ahi > lo[u][k] ? 1u << k : 0u;
             }
         }
         uint32_t any = 0;
 #pragma unroll
-        for (int u = 0; u < kPairWaves; ++u) any |= ok[u] ? 1u << (28 + u) : 0u;
+        for (int u = 0; u < kPairWaves; ++u) any |= ok[u] && apart[u] != 0u ? 1u << (28 + u) : 0u;
         const uint64_t m = ballot(any != 0u);
         int32_t at = 0;
         if (lane == 0 && m) at = atomicAdd(&s_n, (int32_t)__popcll(m));
@@ -709,9 +947,8 @@ __global__ __launch_bounds__(kPairWaves * kWave) void k_pairs_list(PairInst I, i
 // phases: the points nobody dominates are front `phase`; the others go to J in
 // the same order (a block that straddled two distant chunks would meet half of
 // all tiles: without the order the second pass took as long as the first).  A
-// work-group takes the rows whose run of identical rows starts in its
-// kPhaseThreads positions, publishes how many stay, and reads the numbers of
-// the work-groups before it.  Chunks go to work-groups in the order in which
+// work-group takes kPhaseThreads positions, publishes how many stay, and reads
+// the numbers of the work-groups before it.  Chunks go to work-groups in the order in which
 // these start (each XCD starts its own in order, so a block index says nothing
 // about the others): who waits, waits for a work-group that is running.
 // ---------------------------------------------------------------------------
@@ -719,7 +956,6 @@ template <int M>
 __global__ __launch_bounds__(kPhaseThreads) void k_phase(PairInst I, PairInst J, int32_t phase) {
     constexpr int MP = rec_stride(M);
     __shared__ uint32_t lds[kPhaseThreads / kWave + 1];
-    __shared__ uint32_t s_n;
     __shared__ int32_t s_at, s_b;
     if (I.sc->err) return;
     I = phase_inst(I);
@@ -728,23 +964,19 @@ __global__ __launch_bounds__(kPhaseThreads) void k_phase(PairInst I, PairInst J,
     const int32_t blk = s_b;
     const int32_t c0 = blk * kPhaseThreads;
     if (c0 >= I.N) return;  // (work-groups after this one return too)
-    const int32_t c1 = c0 + kPhaseThreads;
-    const int32_t p0 = I.runs[c0] == c0 ? c0 : I.rune[c0];
-    const int32_t p1 = c1 >= I.N ? I.N : (I.runs[c1] == c1 ? c1 : I.rune[c1]);
-    if (threadIdx.x == 0) s_n = 0;
-    __syncthreads();
-    for (int32_t b = p0; b < p1; b += kPhaseThreads) {
-        const int32_t p = b + (int32_t)threadIdx.x;
-        const uint64_t m = ballot(p < p1 && I.din[p < p1 ? p : p0] != 0);
-        if (lane_id() == 0 && m) atomicAdd(&s_n, (uint32_t)__popcll(m));
-    }
-    __syncthreads();
+    const int32_t p = c0 + (int32_t)threadIdx.x;
+    const bool in = p < I.N;
+    const int32_t d = in ? I.din[p] : 0;
+    const uint32_t i = in ? I.sval[p] : 0u;
+    const bool stays = d != 0;
+    uint32_t tot;
+    const uint32_t ex = block_exclusive_scan(stays ? 1u : 0u, lds, &tot);
     uint32_t *cnt = I.sync->chunk[phase];
     if (threadIdx.x == 0) {
-        __hip_atomic_store(&cnt[blk], 0x80000000u | s_n, __ATOMIC_RELAXED,
+        __hip_atomic_store(&cnt[blk], 0x80000000u | tot, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
-        atomicAdd(&I.sync->left[phase], (int32_t)s_n);
-        const int32_t n = p1 - p0 - (int32_t)s_n;
+        atomicAdd(&I.sync->left[phase], (int32_t)tot);
+        const int32_t n = min(kPhaseThreads, I.N - c0) - (int32_t)tot;
         if (n) atomicAdd(&I.sync->lv[phase], (uint32_t)n);
         s_at = 0;
     }
@@ -762,36 +994,25 @@ __global__ __launch_bounds__(kPhaseThreads) void k_phase(PairInst I, PairInst J,
         atomicAdd(&s_at, (int32_t)(v & 0x7fffffffu));
     }
     __syncthreads();
-    int32_t base = s_at;
-    for (int32_t b = p0; b < p1; b += kPhaseThreads) {
-        const int32_t p = b + (int32_t)threadIdx.x;
-        const bool in = p < p1;
-        const int32_t d = in ? I.din[p] : 1;
-        const uint32_t i = in ? I.sval[p] : 0u;
-        const bool stays = in && d != 0;
-        uint32_t tot;
-        const uint32_t ex = block_exclusive_scan(stays ? 1u : 0u, lds, &tot);
-        if (in) {
-            if (I.dom_in) I.dom_in[i] = d;
-            if (I.dom_out) I.dom_out[i] = I.dout[p];
-            if (!stays) I.rank[i] = phase;
-        }
-        if (stays) {
-            const int32_t q = base + (int32_t)ex;
-            uint32_t v[MP];
+    if (in) {
+        if (I.dom_in) I.dom_in[i] = d;
+        if (I.dom_out) I.dom_out[i] = I.dout[p];
+        if (!stays) I.rank[i] = phase;
+    }
+    if (stays) {
+        const int32_t q = s_at + (int32_t)ex;
+        uint32_t v[MP];
 #pragma unroll
-            for (int k = 0; k < MP; ++k) v[k] = I.recs[(size_t)p * MP + k];
-            v[M] = (uint32_t)q;
-            uint4 *dst = reinterpret_cast<uint4 *>(J.recs + (size_t)q * MP);
+        for (int k = 0; k < MP; ++k) v[k] = I.recs[(size_t)p * MP + k];
+        v[M] = (uint32_t)q;
+        uint4 *dst = reinterpret_cast<uint4 *>(J.recs + (size_t)q * MP);
 #pragma unroll
-            for (int k = 0; k < MP / 4; ++k)
-                dst[k] = make_uint4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
-            J.sval[q] = i;
-            J.runs[q] = q - (p - I.runs[p]);
-            J.rune[q] = q + (I.rune[p] - p);
-            J.din[q] = 0;
-        }
-        base += (int32_t)tot;
+        for (int k = 0; k < MP / 4; ++k)
+            dst[k] = make_uint4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
+        J.sval[q] = i;
+        J.runs[q] = q - (p - I.runs[p]);  // (a run of identical rows stays whole)
+        J.rune[q] = q + (I.rune[p] - p);
+        J.din[q] = 0;
     }
 }
 
@@ -862,7 +1083,7 @@ hipError_t run_pairs(const PairInst &I, const RefArgs &R, uint32_t *zero, int64_
     if (!one) {
         const int nfill = (int)((nzero + 4 * kSplitterSample - 1) / (4 * kSplitterSample));
         const int nf = nfill < 1 ? 1 : nfill > 512 ? 512 : nfill;
-        hipLaunchKernelGGL(k_pair_setup, dim3((unsigned)(I.M + nf)), dim3(kSplitterSample), 0, s, I,
+        hipLaunchKernelGGL(k_pair_setup, dim3((unsigned)(I.M + 1 + nf)), dim3(kSplitterSample), 0, s, I,
                            zero, nzero, nf);
         const unsigned nbN = (unsigned)((I.N + 255) / 256);
         hipLaunchKernelGGL(k_cell_code, dim3(nbN), dim3(256), 0, s, I);
