@@ -72,6 +72,7 @@ struct nsga3_ctx {
     bool engine_wide;               // batched counts over 128-member tables
     bool pairs;                     // spatially ordered path where its workspace fits
     int rank_groups, rank_started;  // LaunchCfg's
+    int64_t mask_units;             // LaunchCfg's
     volatile int32_t *last_fronts;  // pinned: front count, then level sizes, of the latest call
     std::vector<hipEvent_t> ev_pool;   // NSGA3_NUM_PHASES + 1 events per recorded call
     size_t ev_used;
@@ -339,6 +340,7 @@ LaunchCfg ctx_cfg(const nsga3_ctx *ctx, int M, int64_t N) {
     cfg.lds_build_max = ctx->lds_build_max;
     cfg.rank_groups = ctx->rank_groups;
     cfg.rank_started = ctx->rank_started;
+    cfg.mask_units = ctx->mask_units;
     // The previous call's front count and level sizes arrive asynchronously
     // in pinned memory; they only size launches (a stale or torn read shifts
     // work between the enqueued levels and the tail, never the results).
@@ -465,7 +467,9 @@ PairInst pair_inst(char *w, const Layout &L, const nsga3_problem &p, int32_t *ra
     I.nz = WS(uint64_t, nz);
     I.idx = WS(uint32_t, idx);
     I.mask = WS(uint4, mask);
-    I.poolUnits = (uint32_t)(mask_units((size_t)I.nB) / kMaskPools);
+    size_t units = mask_units((size_t)I.nB);
+    if (cfg.mask_units >= 0 && (size_t)cfg.mask_units < units) units = (size_t)cfg.mask_units;
+    I.poolUnits = (uint32_t)(units / kMaskPools);
     I.din = WS(int32_t, dom_in_s);
     I.dout = WS(int32_t, dom_out_s);
     I.low = WS(uint32_t, low);
@@ -768,6 +772,10 @@ nsga3_status nsga3_create(nsga3_ctx **out, int device, const nsga3_options *opt)
     c->rank_groups = c->rank_started = 0;
     if (const char *e = getenv("NSGA3_RANK_GROUPS")) c->rank_groups = atoi(e);
     if (const char *e = getenv("NSGA3_RANK_STARTED")) c->rank_started = atoi(e);
+    // NSGA3_MASK_UNITS: dominator masks it stores, at most (the others are probed
+    // again wherever a level needs them; same results)
+    c->mask_units = -1;
+    if (const char *e = getenv("NSGA3_MASK_UNITS")) c->mask_units = atoll(e);
     c->last_fronts = nullptr;
     {
         void *h = nullptr;

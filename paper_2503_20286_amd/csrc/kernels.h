@@ -80,6 +80,7 @@ struct LaunchCfg {
     // rank launch of the spatially ordered path: most work-groups it may want
     // (0: by the CUs), and how many it starts (0: those it wants)
     int rank_groups = 0, rank_started = 0;
+    int64_t mask_units = -1;  // stored masks of that path, at most (-1: by the size)
 };
 
 // Points left before a peeling tail at or below which one work-group

@@ -36,19 +36,36 @@ __device__ __forceinline__ uint64_t agent_ld(const uint64_t *p) {
 }
 
 // Dominators of the point at position `at` within block a, from the tables
-// (a pair whose masks were not stored).
+// (a pair whose masks were not stored).  Four objectives' searches go side by
+// side: eight dependent reads for them.
+template <int M>
 __device__ __forceinline__ uint4 probe_again(const PairInst &I, int32_t at, int32_t a) {
-    const int M = I.M, MP = rec_stride(M);
+    constexpr int MP = rec_stride(M);
     const uint32_t *T = I.tabs + (size_t)a * wblk_stride(M);
+    const uint32_t *row = I.recs + (size_t)at * MP;
     uint32_t m[4];
     low_bits128(T[2], m);
-    for (int k = 0; k < M; ++k) {
-        const uint32_t x = I.recs[(size_t)at * MP + k];
-        int c = 0;  // member keys <= x
+#pragma unroll 1
+    for (int k0 = 0; k0 < M; k0 += 4) {
+        uint32_t x[4];
+        int k[4], c[4];  // member keys <= x
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            k[g] = min(k0 + g, M - 1);
+            x[g] = row[k[g]];
+            c[g] = 0;
+        }
+#pragma unroll
         for (int st = 64; st >= 1; st >>= 1)
-            if (T[wblk_key_slot(k, c + st - 1)] <= x) c += st;
-        if (c == 127 && T[wblk_key_slot(k, 127)] <= x) c = 128;
-        for (int q = 0; q < 4; ++q) m[q] &= T[wblk_mask(k, q, c)];
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                c[g] += T[wblk_key_slot(k[g], c[g] + st - 1)] <= x[g] ? st : 0;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            if (c[g] == 127 && T[wblk_key_slot(k[g], 127)] <= x[g]) c[g] = 128;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) m[q] &= T[wblk_mask(k[g], q, c[g])];
+        }
     }
     uint32_t r[4];
     range_bits128(I.runs[at] - a * kWBlk, I.rune[at] - a * kWBlk, r);
@@ -177,7 +194,7 @@ __device__ __forceinline__ int32_t scan_word(const PairInst &I, const RankLds &S
         uint4 m[kAhead];
         int32_t top = 63 - __builtin_clzll(t);
         if ((none >> top) & 1) {  // not stored: this block alone
-            m[0] = probe_again(I, min(h * kWave + lane, I.N - 1), (w << 6) + top);
+            m[0] = probe_again<M>(I, min(h * kWave + lane, I.N - 1), (w << 6) + top);
             t &= ~(1ull << top);
             --most;
 #pragma unroll
@@ -362,11 +379,13 @@ __device__ __forceinline__ uint32_t rank_level(const PairInst &I, int32_t level,
             const bool open = ((om >> lane) & 1) != 0;
             const uint64_t hit = open ? S.hit[slot * kWave + lane] : 0ull;
             if (hit) {
-                // (a block whose masks are not stored is looked at again next level)
                 const uint32_t u = (uint32_t)hit;
-                const int32_t p = (int32_t)(hit >> 32) - (u == kUnitNone ? 0 : 1);
-                uint4 wit = make_uint4(0, 0, 0, 0);
-                if (u != kUnitNone) wit = I.mask[(size_t)u * kWBlk + (h & 1) * kWave + lane];
+                const int32_t p = (int32_t)(hit >> 32) - 1;
+                uint4 wit;
+                if (u != kUnitNone)
+                    wit = I.mask[(size_t)u * kWBlk + (h & 1) * kWave + lane];
+                else
+                    wit = probe_again<M>(I, at, p);
                 if (kKeep) {
                     P.p = p;
                     P.wit = wit;

@@ -1,0 +1,64 @@
+"""GPU: populations whose first fronts are small (uniform, normal, objectives that
+move together in part).  No call slower than in the key-sum order, and the pairs
+whose dominator masks are not stored against the oracle."""
+from __future__ import annotations
+
+import time
+
+import numpy as np
+import pytest
+
+import oracle
+import paper_2503_20286_amd as nsga3
+
+pytestmark = pytest.mark.gpu
+
+
+def _objs(kind, N, M):
+    rng = np.random.Generator(np.random.PCG64(N + M))
+    if kind == "normal":
+        f = rng.standard_normal((N, M))
+    elif kind == "cube":
+        f = rng.random((N, M))
+    else:      # a common part, and so much of their own
+        f = rng.random((N, 1)) + float(kind) * rng.random((N, M))
+    return np.ascontiguousarray(f.astype(np.float32))
+
+
+@pytest.mark.parametrize("N,M,kind", [(200000, 3, "cube"), (200000, 5, "cube"), (50000, 5, "cube"),
+                                      (200000, 4, "normal"), (200000, 5, "0.2"), (200000, 5, "1.0"),
+                                      (100000, 8, "1.0"), (33000, 4, "0.5")])
+def test_no_slower_than_the_key_sum_order(N, M, kind, monkeypatch):
+    import torch
+    o, r = torch.from_numpy(_objs(kind, N, M)).cuda(), torch.eye(M, device="cuda") + 0.1
+    best, out = {}, {}
+    for pairs in ("1", "0"):
+        monkeypatch.setenv("NSGA3_PAIRS", pairs)
+        ctx = nsga3.Context(0)
+        best[pairs] = 1e9
+        for _ in range(4):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            out[pairs] = nsga3.select(o, r, N // 2, ctx=ctx)
+            torch.cuda.synchronize()
+            best[pairs] = min(best[pairs], time.perf_counter() - t)
+        ctx.close()
+    for k in ("rank", "dom_in", "dom_out", "selected"):
+        assert torch.equal(getattr(out["1"], k), getattr(out["0"], k)), k
+    assert best["1"] <= 1.05 * best["0"], best
+
+
+@pytest.mark.parametrize("units", [0, 64, 6400])
+@pytest.mark.parametrize("N,M,kind", [(300, 2, "cube"), (5000, 3, "normal"), (9000, 16, "1.0"),
+                                      (20001, 5, "cube"), (40000, 4, "0.5"), (70000, 3, "cube")])
+def test_pairs_without_stored_masks(N, M, kind, units, monkeypatch):
+    """None of the masks stored, one a counter, or a share of them."""
+    import torch
+    monkeypatch.setenv("NSGA3_MASK_UNITS", str(units))
+    f = _objs(kind, N, M)
+    f[: N // 8] = f[N // 2: N // 2 + N // 8]     # (identical rows do not dominate each other)
+    ctx = nsga3.Context(0)
+    res = nsga3.select(torch.from_numpy(f).cuda(), torch.eye(M, device="cuda") + 0.1, N // 2, ctx=ctx)
+    assert res.info().status == 0
+    assert np.array_equal(res.rank.cpu().numpy(), oracle.ranks(f)[0])
+    ctx.close()
