@@ -479,7 +479,6 @@ PairInst pair_inst(char *w, const Layout &L, const nsga3_problem &p, int32_t *ra
     I.rune2 = WS(int32_t, rune2);
     I.din2 = WS(int32_t, din2);
     I.list = WS(uint4, list);
-    I.dynN = nullptr;
     I.pos = WS(uint16_t, pos);
     I.wit = WS(uint4, wit);
     I.sync = WS(RankSync, sync);

@@ -57,7 +57,7 @@ constexpr int kRankWaves = 8, kRestWaves = 16;
 // N = 20k, M = 3 370.2 us by block index, 370.5 so; N = 200k, M = 5 1351 / 1352.)
 constexpr int kRankMaxGroups = 64;
 constexpr uint64_t kTeamWait = 10000;   // ticks of the 100 MHz clock: 100 us
-constexpr int kMaxPhases = 8;           // fronts that may be taken off before it
+constexpr int kMaxPhases = 5;           // fronts that may be taken off before it
 
 // LDS for the smallest keys of the blocks in the rank launches; a problem with
 // more blocks looks at fewer objectives.
@@ -105,7 +105,6 @@ struct PairInst {
     const float *objs;
     int32_t N, M;
     int64_t K;
-    const int32_t *dynN;      // number of points on the device (null: N)
     int32_t nB;               // 128-point blocks
     int32_t nBpad;            // nB rounded to 64
     int32_t T;                // cell code bits
@@ -116,7 +115,8 @@ struct PairInst {
     uint32_t *spl;            // [M * 64] splitters
     uint32_t *cell;           // [pair_cells(T) + 1] counts, then starts
     uint32_t *heavy;          // number of heavy rows, then hash and keys of each
-    uint32_t *code, *slot;    // [N] cell, arrival position in it
+    uint32_t *code, *slot;    // [N] cell, arrival position in it; code is sval's other buffer
+                              // in the phases
     uint32_t *trec;           // [N * rec_stride] records in cell order (keys, point index);
                               // afterwards the other buffer of the phases
     uint32_t *recs;           // [N * rec_stride] records in final order (keys, position)
@@ -155,17 +155,54 @@ __device__ __forceinline__ void range_bits128(int32_t lo, int32_t hi, uint32_t (
     for (int q = 0; q < 4; ++q) m[q] = b[q] & ~a[q];
 }
 
-// The instance with its size read from the device.
-__device__ __forceinline__ PairInst phase_inst(PairInst I) {
-    if (I.dynN) {
-        I.N = *I.dynN;
-        I.nB = (I.N + kWBlk - 1) / kWBlk;
-        I.nBpad = (I.nB + 63) / 64 * 64;
+// Fronts taken off after `step` phases, and whether no further one is.  A pass for
+// one more front costs as much as the last one, which it makes smaller by twice
+// the front's share of the points: it pays where that share was a tenth in the
+// front before (shells, N = 70k, M = 3: 0.95 ms, with a twentieth 1.03; at N = 200k
+// uniform points, M = 5, 3.7 ms with five fronts whatever they hold, 3.25 so,
+// normal ones, M = 4, 4.4 and 3.6, shells 1.42 either way).
+constexpr uint32_t kPhaseShare = 10;
+struct PhaseAt {
+    int32_t taken;
+    bool stop;
+};
+__device__ __forceinline__ PhaseAt phase_at(const PairInst &I, int32_t step) {
+    if (step == 0) return {0, false};
+    uint32_t lv[kMaxPhases], left[kMaxPhases];
+#pragma unroll
+    for (int q = 0; q < kMaxPhases; ++q) {  // (every load before the first use)
+        lv[q] = q < step ? I.sync->lv[q] : 0u;
+        left[q] = q < step ? (uint32_t)I.sync->left[q] : 0u;
+    }
+    PhaseAt a = {0, false};
+#pragma unroll
+    for (int q = 0; q < kMaxPhases; ++q)
+        if (q < step && !a.stop) {
+            a.taken = q + 1;
+            a.stop = (kPhaseShare - 1u) * lv[q] < left[q];
+        }
+    return a;
+}
+
+// The instance after `taken` fronts: the points left, their number read from the
+// device, in the buffers that they went to.
+__device__ __forceinline__ PairInst phase_inst(PairInst I, int32_t taken) {
+    if (taken == 0) return I;
+    I.N = I.sync->left[taken - 1];
+    I.nB = (I.N + kWBlk - 1) / kWBlk;
+    I.nBpad = (I.nB + 63) / 64 * 64;
+    I.dom_in = I.dom_out = nullptr;
+    if (taken & 1) {
+        I.recs = I.trec;
+        I.sval = I.code;
+        I.runs = I.runs2;
+        I.rune = I.rune2;
+        I.din = I.din2;
     }
     return I;
 }
 
-// Fronts taken off before the masks are stored: none while one 64-point group
+// Fronts taken off before the masks are stored, at most: none while one 64-point group
 // a wave of the rank launch is enough (N <= 32k).
 // Of many objectives the first two fronts hold nearly all points (N = 100k,
 // M = 10: one front; three phases more are twelve empty launches, 54 us).

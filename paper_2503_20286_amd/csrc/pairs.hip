@@ -281,7 +281,10 @@ __global__ __launch_bounds__(256) void k_cell_place(PairInst I) {
 // small; the splitters cut each objective by itself, so identical rows and
 // objectives that move together may put any share of the points into one cell.
 constexpr int kCellOwn = 256;     // positions of a work-group
-constexpr uint32_t kCellWide = 1024;   // points of a cell that a point counts alone
+// Points of a cell that a point counts alone.  (64 / 128 / 256 / 1024: rows that
+// move together in part, N = 200k, M = 8, 118 / 112 / 152 / 378 us for all cells; a
+// shell's cells hold at most 63.)
+constexpr uint32_t kCellWide = 128;
 
 // x before y in the order of rows (kEq: or the same).
 template <int M, bool kEq>
@@ -536,10 +539,13 @@ __global__ __launch_bounds__(kOrderOne) void k_order_one(PairInst I, RefArgs R, 
 // tables and boxes: one block of 128 points per work-group, a wave per objective
 // ---------------------------------------------------------------------------
 template <int M>
-__global__ __launch_bounds__(M * kWave) void k_pair_build(PairInst I) {
+__global__ __launch_bounds__(M * kWave) void k_pair_build(PairInst I, int32_t step) {
     __shared__ int32_t inv[M][kWBlk];
     if (I.sc->err) return;
-    I = phase_inst(I);
+    if (step > 0) {
+        if (phase_at(I, step).taken != step) return;
+        I = phase_inst(I, step);
+    }
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int32_t b = (int32_t)blockIdx.x;
     if (b >= I.nB) return;
@@ -861,12 +867,15 @@ __global__ __launch_bounds__(kPairWaves * kWave) void k_pairs(PairInst I, int32_
 // 40,000 work-groups found 2 blocks or none, and the tiles at the far corner
 // of objective space all 16.)
 template <int M>
-__global__ __launch_bounds__(256) void k_pair_list(PairInst I, int32_t pass) {
+__global__ __launch_bounds__(256) void k_pair_list(PairInst I, int32_t step) {
     __shared__ uint4 ent[kPairsMaxN / kWBlk];
     __shared__ uint32_t lo[kPairWaves][16], hi[kPairWaves][16];
     __shared__ int32_t s_n, s_base;
     if (I.sc->err) return;
-    I = phase_inst(I);
+    if (step > 0) {
+        if (phase_at(I, step).taken != step) return;
+        I = phase_inst(I, step);
+    }
     const int32_t nB = I.nB, nBp = I.nBpad;
     const int32_t tg = (int32_t)blockIdx.x;
     if (tg * kPairWaves >= nB) return;
@@ -911,19 +920,22 @@ __global__ __launch_bounds__(256) void k_pair_list(PairInst I, int32_t pass) {
     }
     __syncthreads();
     const int32_t n = s_n, items = (n + kListItem - 1) / kListItem;
-    if (threadIdx.x == 0) s_base = (int32_t)atomicAdd(&I.sync->items[pass], (uint32_t)items);
+    if (threadIdx.x == 0) s_base = (int32_t)atomicAdd(&I.sync->items[step], (uint32_t)items);
     __syncthreads();
     for (int32_t q = threadIdx.x; q < items * kListItem; q += 256)
         I.list[(size_t)s_base * kListItem + q] = q < n ? ent[q] : make_uint4(0u, 0u, 0u, ~0u);
 }
 
 template <int M, bool kOut, bool kMask>
-__global__ __launch_bounds__(kPairWaves * kWave) void k_pairs_list(PairInst I, int32_t pass) {
+__global__ __launch_bounds__(kPairWaves * kWave) void k_pairs_list(PairInst I, int32_t step) {
     __shared__ __attribute__((aligned(16))) uint32_t lt[wblk_stride(M)];
     __shared__ uint32_t oc[kOut ? kWBlk : 1];
     __shared__ uint32_t s_next;
     if (I.sc->err) return;
-    I = phase_inst(I);
+    const PhaseAt at = phase_at(I, step);
+    const int32_t pass = at.taken;
+    if (!kMask && (pass != step || at.stop)) return;  // (the last pass, which keeps masks, is next)
+    I = phase_inst(I, pass);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int lane = (int)lane_id();
     const uint32_t items = I.sync->items[pass];
@@ -953,12 +965,22 @@ __global__ __launch_bounds__(kPairWaves * kWave) void k_pairs_list(PairInst I, i
 // about the others): who waits, waits for a work-group that is running.
 // ---------------------------------------------------------------------------
 template <int M>
-__global__ __launch_bounds__(kPhaseThreads) void k_phase(PairInst I, PairInst J, int32_t phase) {
+__global__ __launch_bounds__(kPhaseThreads) void k_phase(PairInst I, int32_t phase) {
     constexpr int MP = rec_stride(M);
     __shared__ uint32_t lds[kPhaseThreads / kWave + 1];
     __shared__ int32_t s_at, s_b;
     if (I.sc->err) return;
-    I = phase_inst(I);
+    const PhaseAt pa = phase_at(I, phase);
+    if (pa.taken != phase || pa.stop) return;
+    PairInst J = I;  // where the points that stay go
+    if ((phase & 1) == 0) {
+        J.recs = I.trec;
+        J.sval = I.code;
+        J.runs = I.runs2;
+        J.rune = I.rune2;
+        J.din = I.din2;
+    }
+    I = phase_inst(I, phase);
     if (threadIdx.x == 0) s_b = (int32_t)atomicAdd(&I.sync->ticket[phase], 1u);
     __syncthreads();
     const int32_t blk = s_b;
@@ -1032,7 +1054,7 @@ static hipError_t launch_pairs(const PairInst &I, const RefArgs &R, bool one, ui
         const hipError_t e = run_build_tables(I.recs, I.N, M, I.tabs64, I.sc, s);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_pair_build<M>, dim3((unsigned)I.nB), dim3(M * kWave), 0, s, I);
+    hipLaunchKernelGGL(k_pair_build<M>, dim3((unsigned)I.nB), dim3(M * kWave), 0, s, I, 0);
     const unsigned tgs = (unsigned)((I.nB + kPairWaves - 1) / kPairWaves);
     const dim3 th(kPairWaves * kWave);
     const int phases = pair_phases(I.N, M);
@@ -1053,28 +1075,17 @@ static hipError_t launch_pairs(const PairInst &I, const RefArgs &R, bool one, ui
     else
         hipLaunchKernelGGL((k_pairs_list<M, false, false>), grid, th, 0, s, I, 0);
     mark();
-    PairInst cur = I, alt = I;
-    alt.recs = I.trec;
-    alt.sval = I.code;
-    alt.runs = I.runs2;
-    alt.rune = I.rune2;
-    alt.din = I.din2;
     for (int p = 0; p < phases; ++p) {  // (the sizes are on the device from here on)
         hipLaunchKernelGGL(k_phase<M>, dim3((unsigned)((I.N + kPhaseThreads - 1) / kPhaseThreads)),
-                           dim3(kPhaseThreads), 0, s, cur, alt, p);
-        PairInst t = cur;
-        cur = alt;
-        alt = t;
-        cur.dynN = &I.sync->left[p];
-        cur.dom_in = cur.dom_out = alt.dom_in = alt.dom_out = nullptr;
-        hipLaunchKernelGGL(k_pair_build<M>, dim3((unsigned)I.nB), dim3(M * kWave), 0, s, cur);
-        hipLaunchKernelGGL(k_pair_list<M>, dim3(tgs), dim3(256), 0, s, cur, p + 1);
+                           dim3(kPhaseThreads), 0, s, I, p);
+        hipLaunchKernelGGL(k_pair_build<M>, dim3((unsigned)I.nB), dim3(M * kWave), 0, s, I, p + 1);
+        hipLaunchKernelGGL(k_pair_list<M>, dim3(tgs), dim3(256), 0, s, I, p + 1);
         if (p + 1 < phases)
-            hipLaunchKernelGGL((k_pairs_list<M, false, false>), grid, th, 0, s, cur, p + 1);
+            hipLaunchKernelGGL((k_pairs_list<M, false, false>), grid, th, 0, s, I, p + 1);
         else
-            hipLaunchKernelGGL((k_pairs_list<M, false, true>), grid, th, 0, s, cur, p + 1);
+            hipLaunchKernelGGL((k_pairs_list<M, false, true>), grid, th, 0, s, I, p + 1);
     }
-    return run_ranks(cur, phases, s);
+    return run_ranks(I, phases, s);
 }
 
 hipError_t run_pairs(const PairInst &I, const RefArgs &R, uint32_t *zero, int64_t nzero,

@@ -689,8 +689,8 @@ __global__ __launch_bounds__(kRankWaves * kWave) void k_ranks(PairInst I) {
     }
 }
 
-// The levels that the first `phases` fronts leave (their number of points is
-// on the device).
+// The levels that the fronts taken off in `phases` phases leave (how many and
+// their number of points is on the device).
 template <int M>
 __global__ __launch_bounds__(kRestWaves * kWave) void k_ranks_rest(PairInst I, int32_t phases) {
     extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
@@ -699,7 +699,8 @@ __global__ __launch_bounds__(kRestWaves * kWave) void k_ranks_rest(PairInst I, i
     __shared__ int32_t s_n;
     __shared__ int32_t s_team[2];
     if (I.sc->err) return;
-    I = phase_inst(I);
+    phases = phase_at(I, phases).taken;
+    I = phase_inst(I, phases);
     rank_team(I, s_team);
     const int32_t g = uniform(s_team[0]), G = uniform(s_team[1]);
     if (G == 0) return;

@@ -33,7 +33,8 @@ def _objs(kind, N, M):
 
 
 @pytest.mark.parametrize("N,M,kind", [
-    (1025, 2, "same"), (3000, 3, "run1024"), (3000, 3, "run1025"), (5000, 16, "same"),
+    (1025, 2, "same"), (3000, 3, "run128"), (3000, 3, "run129"), (3000, 3, "run1025"),
+    (5000, 16, "same"), (4096, 3, "line"), (4097, 3, "same"),
     (2600, 2, "two"), (9001, 4, "two"), (20000, 3, "line"), (12000, 2, "few"), (30000, 10, "line"),
     (40000, 5, "run17000"),
 ])

@@ -28,7 +28,8 @@ def _objs(kind, N, M):
 @pytest.mark.parametrize("N,M,kind", [(200000, 3, "cube"), (200000, 5, "cube"), (50000, 5, "cube"),
                                       (200000, 4, "normal"), (200000, 5, "0.2"), (200000, 5, "1.0"),
                                       (100000, 8, "1.0"), (33000, 4, "0.5")])
-def test_no_slower_than_the_key_sum_order(N, M, kind, monkeypatch):
+@pytest.mark.parametrize("counts", [True, False])
+def test_no_slower_than_the_key_sum_order(N, M, kind, counts, monkeypatch):
     import torch
     o, r = torch.from_numpy(_objs(kind, N, M)).cuda(), torch.eye(M, device="cuda") + 0.1
     best, out = {}, {}
@@ -39,11 +40,11 @@ def test_no_slower_than_the_key_sum_order(N, M, kind, monkeypatch):
         for _ in range(4):
             torch.cuda.synchronize()
             t = time.perf_counter()
-            out[pairs] = nsga3.select(o, r, N // 2, ctx=ctx)
+            out[pairs] = nsga3.select(o, r, N // 2, ctx=ctx, want_counts=counts)
             torch.cuda.synchronize()
             best[pairs] = min(best[pairs], time.perf_counter() - t)
         ctx.close()
-    for k in ("rank", "dom_in", "dom_out", "selected"):
+    for k in ("rank", "selected") + (("dom_in", "dom_out") if counts else ()):
         assert torch.equal(getattr(out["1"], k), getattr(out["0"], k)), k
     assert best["1"] <= 1.05 * best["0"], best
 
@@ -62,3 +63,26 @@ def test_pairs_without_stored_masks(N, M, kind, units, monkeypatch):
     assert res.info().status == 0
     assert np.array_equal(res.rank.cpu().numpy(), oracle.ranks(f)[0])
     ctx.close()
+
+
+@pytest.mark.parametrize("N", [35000, 70000])
+@pytest.mark.parametrize("layers", [0, 1, 2, 3, 4, 5, 6])
+def test_fronts_taken_off(N, layers):
+    """So many large fronts before the small ones of a uniform rest: the fronts
+    that are taken off first end after each of them."""
+    import torch
+    rng = np.random.Generator(np.random.PCG64(N + layers))
+    f = 3.0 + rng.random((N, 2))
+    n = N // 8
+    for j in range(layers):
+        x = rng.random(n)
+        f[j * n:(j + 1) * n] = np.stack([x, 1.0 + 0.2 * j - x], 1)
+    f = np.ascontiguousarray(f[rng.permutation(N)].astype(np.float32))
+    res = nsga3.select(torch.from_numpy(f).cuda(), torch.eye(2, device="cuda") + 0.1, N // 2,
+                       ctx=nsga3.Context(0))
+    rank = oracle.ranks(f)[0]
+    l = int(np.sort(rank)[N // 2 - 1])
+    i = res.info()
+    assert np.array_equal(res.rank.cpu().numpy(), rank)
+    assert (i.status, i.num_fronts, i.last_front, i.last_front_size) == (
+        0, int(rank.max()) + 1, l, int((rank == l).sum()))
