@@ -59,6 +59,7 @@ struct nsga3_ctx {
     int peel_bpc[17];
     void *ws;
     size_t ws_bytes;
+    size_t big_failed;              // larger workspace that could not be had, the last one tried (0: none)
     bool profiling;
     int phase_a_bpc;
     bool bitsets;
@@ -262,6 +263,14 @@ struct DeviceGuard {
     }
 };
 
+// Allocates a workspace.  NSGA3_TEST_ALLOC_LIMIT: bytes above which that fails, for
+// tests.
+hipError_t ws_malloc(void **p, size_t bytes) {
+    if (const char *e = getenv("NSGA3_TEST_ALLOC_LIMIT"))
+        if (bytes > (size_t)atoll(e)) return hipErrorOutOfMemory;
+    return hipMalloc(p, bytes);
+}
+
 nsga3_status ensure_ws(nsga3_ctx *ctx, size_t need) {
     if (need <= ctx->ws_bytes) return NSGA3_OK;
     if (ctx->opt.max_workspace_bytes && need > ctx->opt.max_workspace_bytes) return NSGA3_E_NOMEM;
@@ -272,7 +281,7 @@ nsga3_status ensure_ws(nsga3_ctx *ctx, size_t need) {
         ctx->ws_bytes = 0;
     }
     void *p = nullptr;
-    if (hipMalloc(&p, need) != hipSuccess) {
+    if (ws_malloc(&p, need) != hipSuccess) {
         (void)hipGetLastError();
         return NSGA3_E_NOMEM;
     }
@@ -281,20 +290,37 @@ nsga3_status ensure_ws(nsga3_ctx *ctx, size_t need) {
     return NSGA3_OK;
 }
 
-// Workspace for one selection: the spatially ordered path's where it fits
-// (pairs = true), else the smaller one of the key-sum ordered path.
-nsga3_status ensure_select_ws(nsga3_ctx *ctx, int64_t N, int32_t M, int32_t H, bool *pairs) {
-    *pairs = false;
-    if (ctx->pairs && N <= kPairsMaxN) {
-        const nsga3_status st = ensure_ws(ctx, layout_pairs(N, M, H).total);
-        if (st == NSGA3_OK) {
+// Workspace for one call: `big` bytes for the spatially ordered path where they
+// are there or can be had (pairs = true; 0: not that path), else `small` ones for
+// the key-sum ordered path.  The workspace is kept until the bigger one is there,
+// and a size that could not be had is not tried again on every call (smaller
+// ones are).
+nsga3_status ensure_either(nsga3_ctx *ctx, size_t big, size_t small, bool *pairs) {
+    *pairs = big > 0 && big <= ctx->ws_bytes;
+    if (*pairs) return NSGA3_OK;
+    bool failed = false;
+    if (big && (!ctx->opt.max_workspace_bytes || big <= ctx->opt.max_workspace_bytes) &&
+        (!ctx->big_failed || big < ctx->big_failed)) {
+        void *p = nullptr;
+        if (!getenv("NSGA3_TEST_FAIL_ALLOC") && ws_malloc(&p, big) == hipSuccess) {
+            if (ctx->ws) (void)hipFree(ctx->ws);
+            ctx->ws = p;
+            ctx->ws_bytes = big;
             *pairs = true;
             return NSGA3_OK;
         }
-        // no memory for it: do not try again on every call
-        if (!ctx->opt.max_workspace_bytes) ctx->pairs = false;
+        (void)hipGetLastError();
+        failed = true;
     }
-    return ensure_ws(ctx, layout_for(N, M, H, kGridCap).total);
+    const nsga3_status st = ensure_ws(ctx, small);
+    if (failed && st == NSGA3_OK) ctx->big_failed = big;
+    return st;
+}
+
+// The same for one selection.
+nsga3_status ensure_select_ws(nsga3_ctx *ctx, int64_t N, int32_t M, int32_t H, bool *pairs) {
+    const size_t big = ctx->pairs && N <= kPairsMaxN ? layout_pairs(N, M, H).total : 0;
+    return ensure_either(ctx, big, layout_for(N, M, H, kGridCap).total, pairs);
 }
 
 // Phase boundary marker: records the next pooled event when profiling.
@@ -709,6 +735,7 @@ nsga3_status nsga3_create(nsga3_ctx **out, int device, const nsga3_options *opt)
     }
     c->ws = nullptr;
     c->ws_bytes = 0;
+    c->big_failed = 0;
     c->profiling = false;
     c->ev_used = 0;
     c->fixed_levels = 0;
@@ -927,18 +954,17 @@ nsga3_status nsga3_hype_select(nsga3_ctx *ctx, const float *objs, int64_t N, int
     const size_t extra = hype_extra_bytes(N, M, s);
     HypeTail T = {};
     bool pairs = false;
-    Layout L = {};
-    nsga3_status st = NSGA3_E_NOMEM;
-    if (ctx->pairs && N <= kPairsMaxN) {  // as in ensure_select_ws
+    Layout L = layout_for(N, M, 1, kGridCap);
+    const size_t small = L.total + extra;
+    size_t big = 0;
+    if (ctx->pairs && N <= kPairsMaxN)
+        big = hype_tail(layout_pairs(N, M, 1).total, N, M).total + extra;
+    const nsga3_status st = ensure_either(ctx, big, small, &pairs);
+    if (pairs) {
         L = layout_pairs(N, M, 1);
         T = hype_tail(L.total, N, M);
-        st = ensure_ws(ctx, T.total + extra);
-        pairs = st == NSGA3_OK;
-    }
-    if (!pairs) {
-        L = layout_for(N, M, 1, kGridCap);
+    } else {
         T = {L.tabs_all, L.skey, L.skey_alt, L.sval, L.sval_alt, L.temp, L.total};
-        st = ensure_ws(ctx, T.total + extra);
     }
     if (st != NSGA3_OK) return st;
     char *w = (char *)ctx->ws;

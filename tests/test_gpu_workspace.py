@@ -1,0 +1,88 @@
+"""GPU: the workspace of a context where the larger one cannot be had (a failed
+allocation, a cap), and that calls which need no other workspace neither free nor
+allocate: they return while the stream is busy."""
+from __future__ import annotations
+
+import time
+
+import numpy as np
+import pytest
+
+import paper_2503_20286_amd as nsga3
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+def _busy():
+    """Enqueues about 100 ms of work on the current stream."""
+    import torch
+    a = torch.ones((8192, 8192), device="cuda")
+    torch.cuda.synchronize()
+    for _ in range(12):
+        a = (a @ a).clamp_(-1, 1)
+    return a
+
+
+def _problem(N, M):
+    import torch
+    rng = np.random.Generator(np.random.PCG64(N + M))
+    f = workloads.sphere_shell(rng, N, M, lambda r, n: r.uniform(0, 0.5, n), 0.2).astype(np.float32)
+    return torch.from_numpy(f).cuda(), torch.eye(M, device="cuda") + 0.1
+
+
+def _returns_at_once(call):
+    """call() returns while the work enqueued before it still runs."""
+    import torch
+    call()
+    torch.cuda.synchronize()
+    keep = _busy()
+    done = torch.cuda.Event()
+    done.record()
+    r = call()
+    early = not done.query()
+    torch.cuda.synchronize()
+    del keep
+    return early, r
+
+
+def _ms(call):
+    import torch
+    best = 1e9
+    for _ in range(6):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        call()
+        torch.cuda.synchronize()
+        best = min(best, time.perf_counter() - t)
+    return best
+
+
+def test_a_failed_larger_workspace_is_not_tried_again_and_smaller_ones_are(monkeypatch):
+    import torch
+    o, r = _problem(60000, 5)
+    want = nsga3.select(o, r, 30000, ctx=nsga3.Context(0))
+    monkeypatch.setenv("NSGA3_TEST_ALLOC_LIMIT", str(48 << 20))
+    ctx = nsga3.Context(0)
+    early, got = _returns_at_once(lambda: nsga3.select(o, r, 30000, ctx=ctx))
+    assert early
+    for k in ("rank", "dom_in", "dom_out", "selected"):
+        assert torch.equal(getattr(got, k), getattr(want, k)), k
+    # a problem whose larger workspace is to be had takes it, on the same context
+    p, q = _problem(2000, 5)
+    fresh = nsga3.Context(0)
+    assert _ms(lambda: nsga3.select(p, q, 1000, ctx=ctx)) < 1.5 * _ms(
+        lambda: nsga3.select(p, q, 1000, ctx=fresh))
+
+
+def test_hype_keeps_its_workspace_where_the_larger_one_fails(monkeypatch):
+    import torch
+    o, _ = _problem(60000, 3)
+    U = torch.rand((2000, 3), device="cuda")
+    v = (o.max(0).values * 1.1).contiguous()
+    want = nsga3.hype_select(o, v, U, 30000, ctx=nsga3.Context(0))
+    monkeypatch.setenv("NSGA3_TEST_ALLOC_LIMIT", str(48 << 20))
+    ctx = nsga3.Context(0)
+    early, got = _returns_at_once(lambda: nsga3.hype_select(o, v, U, 30000, ctx=ctx))
+    assert early
+    assert torch.equal(got.selected, want.selected) and torch.equal(got.rank, want.rank)
