@@ -110,7 +110,9 @@ void nsga3_destroy(nsga3_ctx *ctx);
 
 /* Grow the context's workspace so that later calls with N <= N_max, M <= M_max,
  * H <= H_max allocate nothing.  Synchronous (allocation).  Sizes are checked as
- * in nsga3_select. */
+ * in nsga3_select.  Under a cap (max_workspace_bytes) that the faster path's
+ * workspace for N_max exceeds, it is sized for the most points whose workspace
+ * does not, and larger calls take the slower path. */
 nsga3_status nsga3_reserve(nsga3_ctx *ctx, int64_t N_max, int32_t M_max, int32_t H_max);
 
 /* Bytes of workspace a call of this size needs at least (host-only query).  A
@@ -141,7 +143,9 @@ nsga3_status nsga3_workspace_size(int64_t N, int32_t M, int32_t H, size_t *bytes
  * scheduling).  Ties are resolved by lowest index everywhere; the "random"
  * member of a crowded niche (Alg. S.1) is its closest remaining member.
  * Workspace grows on demand (synchronous allocation) unless nsga3_reserve was
- * called with sufficient sizes.
+ * called with sufficient sizes.  A captured call, and every call of a context
+ * after one, grows it only where it cannot run otherwise (the graph holds its
+ * address: reserve before capturing).
  */
 nsga3_status nsga3_select(nsga3_ctx *ctx, const float *objs, int64_t N, int32_t M,
                           const float *refs, int32_t H, int64_t K,

@@ -60,6 +60,9 @@ struct nsga3_ctx {
     void *ws;
     size_t ws_bytes;
     size_t big_failed;              // larger workspace that could not be had, the last one tried (0: none)
+    struct Extent { int64_t N; int32_t M, H; };
+    std::vector<Extent> reserved;   // sizes nsga3_reserve promised not to allocate for
+    bool captured;                  // a graph holds the workspace's address
     bool profiling;
     int phase_a_bpc;
     bool bitsets;
@@ -294,12 +297,12 @@ nsga3_status ensure_ws(nsga3_ctx *ctx, size_t need) {
 // are there or can be had (pairs = true; 0: not that path), else `small` ones for
 // the key-sum ordered path.  The workspace is kept until the bigger one is there,
 // and a size that could not be had is not tried again on every call (smaller
-// ones are).
-nsga3_status ensure_either(nsga3_ctx *ctx, size_t big, size_t small, bool *pairs) {
+// ones are).  grow = false: nothing is allocated for the bigger one.
+nsga3_status ensure_either(nsga3_ctx *ctx, size_t big, size_t small, bool grow, bool *pairs) {
     *pairs = big > 0 && big <= ctx->ws_bytes;
     if (*pairs) return NSGA3_OK;
     bool failed = false;
-    if (big && (!ctx->opt.max_workspace_bytes || big <= ctx->opt.max_workspace_bytes) &&
+    if (big && grow && (!ctx->opt.max_workspace_bytes || big <= ctx->opt.max_workspace_bytes) &&
         (!ctx->big_failed || big < ctx->big_failed)) {
         void *p = nullptr;
         if (!getenv("NSGA3_TEST_FAIL_ALLOC") && ws_malloc(&p, big) == hipSuccess) {
@@ -317,10 +320,45 @@ nsga3_status ensure_either(nsga3_ctx *ctx, size_t big, size_t small, bool *pairs
     return st;
 }
 
-// The same for one selection.
-nsga3_status ensure_select_ws(nsga3_ctx *ctx, int64_t N, int32_t M, int32_t H, bool *pairs) {
+// Whether a call on this stream is being captured; a graph that holds the
+// workspace's address keeps it where it is, as far as calls can do without more.
+bool note_capture(nsga3_ctx *ctx, hipStream_t stream) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &st) != hipSuccess) {  // (beside another stream's capture)
+        (void)hipGetLastError();
+        return true;
+    }
+    if (st != hipStreamCaptureStatusNone) ctx->captured = true;
+    return ctx->captured;
+}
+
+bool covered(const nsga3_ctx *ctx, int64_t N, int32_t M, int32_t H) {
+    for (const nsga3_ctx::Extent &r : ctx->reserved)
+        if (N <= r.N && M <= r.M && H <= r.H) return true;
+    return false;
+}
+
+// The same for one selection: calls that a reservation covers, that are captured
+// or that come after a captured one take the bigger workspace only where it is
+// there.
+nsga3_status ensure_select_ws(nsga3_ctx *ctx, int64_t N, int32_t M, int32_t H, hipStream_t stream,
+                              bool *pairs) {
     const size_t big = ctx->pairs && N <= kPairsMaxN ? layout_pairs(N, M, H).total : 0;
-    return ensure_either(ctx, big, layout_for(N, M, H, kGridCap).total, pairs);
+    const bool grow = !note_capture(ctx, stream) && !covered(ctx, N, M, H);
+    return ensure_either(ctx, big, layout_for(N, M, H, kGridCap).total, grow, pairs);
+}
+
+// Largest workspace of the spatially ordered path within the cap for at most N
+// points (its size grows with N): calls above that number take the other path.
+size_t pairs_bytes_within_cap(const nsga3_ctx *ctx, int64_t N, int32_t M, int32_t H) {
+    const size_t cap = ctx->opt.max_workspace_bytes;
+    int64_t hi = N < kPairsMaxN ? N : kPairsMaxN, lo = 0;
+    if (!cap || layout_pairs(hi, M, H).total <= cap) return layout_pairs(hi, M, H).total;
+    while (lo + 1 < hi) {
+        const int64_t mid = (lo + hi) / 2;
+        (layout_pairs(mid, M, H).total <= cap ? lo : hi) = mid;
+    }
+    return lo > 0 ? layout_pairs(lo, M, H).total : 0;
 }
 
 // Phase boundary marker: records the next pooled event when profiling.
@@ -736,6 +774,7 @@ nsga3_status nsga3_create(nsga3_ctx **out, int device, const nsga3_options *opt)
     c->ws = nullptr;
     c->ws_bytes = 0;
     c->big_failed = 0;
+    c->captured = false;
     c->profiling = false;
     c->ev_used = 0;
     c->fixed_levels = 0;
@@ -857,10 +896,14 @@ nsga3_status nsga3_phase_times(nsga3_ctx *ctx, double *ms, int64_t *calls) {
 nsga3_status nsga3_reserve(nsga3_ctx *ctx, int64_t N_max, int32_t M_max, int32_t H_max) {
     if (!ctx || !sizes_ok(N_max, M_max, H_max)) return NSGA3_E_INVALID;
     DeviceGuard g(ctx->device);
+    // (one allocation for both paths)
+    const size_t small = layout_for(N_max, M_max, H_max, kGridCap).total;
+    size_t big = ctx->pairs ? pairs_bytes_within_cap(ctx, N_max, M_max, H_max) : 0;
+    if (big && big < small) big = small;
     bool pairs;
-    nsga3_status st = ensure_select_ws(ctx, N_max < kPairsMaxN ? N_max : kPairsMaxN, M_max, H_max,
-                                       &pairs);
-    if (st == NSGA3_OK) st = ensure_ws(ctx, layout_for(N_max, M_max, H_max, kGridCap).total);
+    const nsga3_status st = ensure_either(ctx, big, small, true, &pairs);
+    if (st == NSGA3_OK && !covered(ctx, N_max, M_max, H_max))
+        ctx->reserved.push_back({N_max, M_max, H_max});
     return st;
 }
 
@@ -872,7 +915,7 @@ nsga3_status nsga3_select(nsga3_ctx *ctx, const float *objs, int64_t N, int32_t 
     if (!sizes_ok(N, M, H) || K < 1 || K > N) return NSGA3_E_INVALID;
     DeviceGuard g(ctx->device);
     bool pairs = false;
-    const nsga3_status st = ensure_select_ws(ctx, N, M, H, &pairs);
+    const nsga3_status st = ensure_select_ws(ctx, N, M, H, stream, &pairs);
     if (st != NSGA3_OK) return st;
     EnqArgs a;
     a.ws = (char *)ctx->ws;
@@ -959,7 +1002,8 @@ nsga3_status nsga3_hype_select(nsga3_ctx *ctx, const float *objs, int64_t N, int
     size_t big = 0;
     if (ctx->pairs && N <= kPairsMaxN)
         big = hype_tail(layout_pairs(N, M, 1).total, N, M).total + extra;
-    const nsga3_status st = ensure_either(ctx, big, small, &pairs);
+    const bool grow = !note_capture(ctx, stream) && !covered(ctx, N, M, 1);
+    const nsga3_status st = ensure_either(ctx, big, small, grow, &pairs);
     if (pairs) {
         L = layout_pairs(N, M, 1);
         T = hype_tail(L.total, N, M);

@@ -86,3 +86,52 @@ def test_hype_keeps_its_workspace_where_the_larger_one_fails(monkeypatch):
     early, got = _returns_at_once(lambda: nsga3.hype_select(o, v, U, 30000, ctx=ctx))
     assert early
     assert torch.equal(got.selected, want.selected) and torch.equal(got.rank, want.rank)
+
+
+def test_reserve_under_a_cap_covers_every_smaller_call():
+    """A cap between the two workspaces of the reserved size: no later call within
+    it allocates, whichever path it takes."""
+    import torch
+    cap = 100 << 20
+    ctx = nsga3.Context(0, max_workspace_bytes=cap)
+    ctx.reserve(200000, 5, 5)
+    sizes = [(n, 5) for n in range(34000, 50000, 2000)]   # (the larger workspace passes 86 to 100 MiB)
+    for N, M in [(200000, 5), (90000, 3)] + sizes + [(2000, 2)]:
+        o, r = _problem(N, M)
+        want = nsga3.select(o, r, N // 2, ctx=nsga3.Context(0))
+        out = nsga3.alloc_outputs(N, N // 2, o.device)
+        torch.cuda.synchronize()
+        keep = _busy()
+        done = torch.cuda.Event()
+        done.record()
+        got = nsga3.select(o, r, N // 2, ctx=ctx, out=out)      # (the context's first of this size)
+        assert not done.query(), (N, M)
+        torch.cuda.synchronize()
+        del keep
+        for k in ("rank", "dom_in", "dom_out", "selected"):
+            assert torch.equal(getattr(got, k), getattr(want, k)), (N, M, k)
+
+
+def test_a_captured_call_and_those_after_it_keep_the_workspace():
+    """A context whose workspace is large enough for the call, but not for the
+    faster path: under capture, and beside the graph afterwards."""
+    import torch
+    ctx = nsga3.Context(0)
+    b, q = _problem(210000, 2)
+    nsga3.select(b, q, 1000, ctx=ctx)
+    o, r = _problem(60000, 5)
+    want = nsga3.select(o, r, 30000, ctx=nsga3.Context(0))
+    out, other = (nsga3.alloc_outputs(60000, 30000, o.device) for _ in range(2))
+    nsga3.select_noalloc(*_problem(500, 5), 250, out=nsga3.alloc_outputs(500, 250, o.device))
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        nsga3.select(o, r, 30000, ctx=ctx, out=out)
+    for _ in range(3):
+        g.replay()
+        nsga3.select(o, r, 30000, ctx=ctx, out=other)
+        torch.cuda.synchronize()
+        for k in ("rank", "dom_in", "dom_out", "selected"):
+            assert torch.equal(getattr(out, k), getattr(want, k)), k
+            assert torch.equal(getattr(other, k), getattr(want, k)), k
+            getattr(out, k).zero_()
