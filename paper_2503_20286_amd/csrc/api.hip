@@ -228,7 +228,7 @@ Layout layout_pairs(int64_t N, int M, int H) {
 
 // Offsets of the arrays a HypE selection needs beside those of its sort.
 struct HypeTail {
-    size_t tabs, skey, skey_alt, sval, sval_alt, temp, total;
+    size_t tabs, skey, skey_alt, sval, sval_alt, temp, part, total;
 };
 
 HypeTail hype_tail(size_t c, int64_t N, int M) {
@@ -241,6 +241,7 @@ HypeTail hype_tail(size_t c, int64_t N, int M) {
     T.sval = bump(c, 4 * n);
     T.sval_alt = bump(c, 4 * n);
     T.temp = bump(c, rt > ct ? rt : ct);
+    T.part = bump(c, 64 * n);
     T.total = c;
     return T;
 }
@@ -533,7 +534,10 @@ PairInst pair_inst(char *w, const Layout &L, const nsga3_problem &p, int32_t *ra
     I.mask = WS(uint4, mask);
     size_t units = mask_units((size_t)I.nB);
     if (cfg.mask_units >= 0 && (size_t)cfg.mask_units < units) units = (size_t)cfg.mask_units;
-    I.poolUnits = (uint32_t)(units / kMaskPools);
+    const size_t pools = (size_t)I.nB * I.nB <= (size_t)kMaskPools ? 1 : (size_t)kMaskPools;
+    I.poolMask = (uint32_t)pools - 1u;
+    I.poolUnits = (uint32_t)(units / pools);
+    I.allUnit = (uint32_t)(pools * I.poolUnits);
     I.din = WS(int32_t, dom_in_s);
     I.dout = WS(int32_t, dom_out_s);
     I.low = WS(uint32_t, low);
@@ -1008,7 +1012,8 @@ nsga3_status nsga3_hype_select(nsga3_ctx *ctx, const float *objs, int64_t N, int
         L = layout_pairs(N, M, 1);
         T = hype_tail(L.total, N, M);
     } else {
-        T = {L.tabs_all, L.skey, L.skey_alt, L.sval, L.sval_alt, L.temp, L.total};
+        // (partial estimates, 64 bytes a point, over the list buffers of the levels)
+        T = {L.tabs_all, L.skey, L.skey_alt, L.sval, L.sval_alt, L.temp, L.fk0, L.total};
     }
     if (st != NSGA3_OK) return st;
     char *w = (char *)ctx->ws;
@@ -1066,9 +1071,7 @@ nsga3_status nsga3_hype_select(nsga3_ctx *ctx, const float *objs, int64_t N, int
         hv.selflag = WS(uint8_t, selflag);
         hv.sc = sc;
         hv.info = info;
-        // partial estimates, 64 bytes a point: over the list buffers of the levels,
-        // or the stored masks
-        hv.part = pairs ? WS(double, mask) : WS(double, fk0);
+        hv.part = reinterpret_cast<double *>(w + T.part);
         hv.extra = w + T.total;
         e = run_hype(hv, stream);
     }

@@ -65,7 +65,8 @@ constexpr int kRankLowBytes = 32768;
 
 
 // Stored masks: units of 2 KiB (128 points x 128 members) handed out from
-// kMaskPools counters.  Up to kMaskFullUnits every pair of blocks has one;
+// kMaskPools counters, or from one where there are no more pairs than those (N <=
+// 1024: nothing is kept for uneven counters, 1 MiB else).  Up to kMaskFullUnits every pair of blocks has one;
 // beyond, a third of the pairs.  The masks are needed by the pairs whose boxes
 // overlap in some objective and lie in order in the others: 10 % of all for
 // sphere-shaped populations, 13-16 % for uniform or normal ones, 23 to 31 %
@@ -81,7 +82,7 @@ inline size_t mask_units(size_t nB) {
     const size_t full = nB * nB;
     const size_t most = full / 3 > kMaskFullUnits ? full / 3 : kMaskFullUnits;
     const size_t u = full < most ? full : most;
-    return (u + kMaskPools - 1) / kMaskPools * kMaskPools + 8 * kMaskPools;
+    return full <= kMaskPools ? full : (u + kMaskPools - 1) / kMaskPools * kMaskPools + 8 * kMaskPools;
 }
 
 // Counters of the rank launches.
@@ -130,7 +131,9 @@ struct PairInst {
     uint32_t *idx;            // [nB][nBpad] mask unit of a stored pair
     uint4 *mask;              // [units + 1][128] dominators of a point within a block; the
                               // last unit is all ones
+    uint32_t poolMask;        // pools - 1 (a power of two)
     uint32_t poolUnits;       // units of one pool
+    uint32_t allUnit;         // the unit that is all ones
     int32_t *din, *dout;      // [N] degrees in final order (zeroed)
     int32_t *runs2, *rune2, *din2;     // [N] other buffers of the phases
     uint32_t *low;            // [2 * nB][16] smallest keys of the points of a 64-point group

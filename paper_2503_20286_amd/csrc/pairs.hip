@@ -129,8 +129,7 @@ __global__ __launch_bounds__(kSplitterSample) void k_pair_setup(PairInst I, uint
     if (b == 0) {
         init_scalars(I.sc, (int)threadIdx.x);
         if (threadIdx.x < kWBlk)
-            I.mask[(size_t)kMaskPools * I.poolUnits * kWBlk + threadIdx.x] =
-                make_uint4(~0u, ~0u, ~0u, ~0u);
+            I.mask[(size_t)I.allUnit * kWBlk + threadIdx.x] = make_uint4(~0u, ~0u, ~0u, ~0u);
     }
     const int64_t t = (int64_t)b * kSplitterSample + threadIdx.x;
     for (int64_t q = t; q < nzero; q += (int64_t)nfill * kSplitterSample) zero[q] = 0u;
@@ -492,8 +491,7 @@ __global__ __launch_bounds__(kOrderOne) void k_order_one(PairInst I, RefArgs R, 
     __shared__ uint32_t smin[M];
     const int t = (int)threadIdx.x;
     init_scalars(I.sc, t);
-    if (t < kWBlk)
-        I.mask[(size_t)kMaskPools * I.poolUnits * kWBlk + t] = make_uint4(~0u, ~0u, ~0u, ~0u);
+    if (t < kWBlk) I.mask[(size_t)I.allUnit * kWBlk + t] = make_uint4(~0u, ~0u, ~0u, ~0u);
     for (int64_t q = t; q < nzero; q += kOrderOne) zero[q] = 0u;
     const int N = I.N;
     const bool in = t < N;
@@ -538,11 +536,12 @@ __global__ __launch_bounds__(kOrderOne) void k_order_one(PairInst I, RefArgs R, 
 // ---------------------------------------------------------------------------
 // tables and boxes: one block of 128 points per work-group, a wave per objective
 // ---------------------------------------------------------------------------
-template <int M>
+// kStep: after `step` fronts were taken off (0 without).
+template <int M, bool kStep>
 __global__ __launch_bounds__(M * kWave) void k_pair_build(PairInst I, int32_t step) {
     __shared__ int32_t inv[M][kWBlk];
     if (I.sc->err) return;
-    if (step > 0) {
+    if constexpr (kStep) {
         if (phase_at(I, step).taken != step) return;
         I = phase_inst(I, step);
     }
@@ -701,7 +700,7 @@ __device__ __forceinline__ void pair_blocks(const PairInst &I, int32_t tg, int32
     if (q1 < N) { r1 = I.runs[q1]; e1 = I.rune[q1]; }
     const Transpose64 tr;
     const uint32_t base = lds_addr(lt);
-    pool = (pool + w) % kMaskPools;
+    pool = (pool + w) & (int)I.poolMask;
     int32_t c0 = 0, c1 = 0;
     int32_t prev = -1;
     uint64_t g = group;
@@ -775,7 +774,7 @@ __device__ __forceinline__ void pair_blocks(const PairInst &I, int32_t tg, int32
         c1 += (int32_t)n1;
         if constexpr (kMask) {
             stored |= 1ull << ai;
-            uint32_t at = kMaskPools * I.poolUnits;  // every member dominates every point
+            uint32_t at = I.allUnit;  // every member dominates every point
             if (!all) {
                 unsigned long long got = 0;
                 if (lane == 0)
@@ -841,7 +840,7 @@ __device__ __forceinline__ void pair_item(const PairInst &I, int32_t tg, int32_t
     const uint64_t mine = ballot(okm), group = ballot(okg);
     if (group)
         pair_blocks<M, kOut, kMask>(I, tg, a, need, group, mine,
-                                    (int)((uint32_t)(5 * tg + a0) % kMaskPools), lt, oc);
+                                    5 * tg + a0, lt, oc);
 }
 
 // Small problems: a work-group takes a group of kPairWaves tiles against a range
@@ -948,7 +947,7 @@ __global__ __launch_bounds__(kPairWaves * kWave) void k_pairs_list(PairInst I, i
         const uint64_t mine = ballot(in && ((e.x >> (28 + w)) & 1u));
         pair_blocks<M, kOut, kMask>(I, __builtin_amdgcn_readfirstlane((int)e.w),
                                     (int32_t)(e.x & 0xffffffu), need, ballot(in), mine,
-                                    (int)(q % kMaskPools), lt, oc);
+                                    (int)q, lt, oc);
         __syncthreads();
         q = s_next;
         __syncthreads();
@@ -1054,7 +1053,7 @@ static hipError_t launch_pairs(const PairInst &I, const RefArgs &R, bool one, ui
         const hipError_t e = run_build_tables(I.recs, I.N, M, I.tabs64, I.sc, s);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_pair_build<M>, dim3((unsigned)I.nB), dim3(M * kWave), 0, s, I, 0);
+    hipLaunchKernelGGL((k_pair_build<M, false>), dim3((unsigned)I.nB), dim3(M * kWave), 0, s, I, 0);
     const unsigned tgs = (unsigned)((I.nB + kPairWaves - 1) / kPairWaves);
     const dim3 th(kPairWaves * kWave);
     const int phases = pair_phases(I.N, M);
@@ -1078,7 +1077,8 @@ static hipError_t launch_pairs(const PairInst &I, const RefArgs &R, bool one, ui
     for (int p = 0; p < phases; ++p) {  // (the sizes are on the device from here on)
         hipLaunchKernelGGL(k_phase<M>, dim3((unsigned)((I.N + kPhaseThreads - 1) / kPhaseThreads)),
                            dim3(kPhaseThreads), 0, s, I, p);
-        hipLaunchKernelGGL(k_pair_build<M>, dim3((unsigned)I.nB), dim3(M * kWave), 0, s, I, p + 1);
+        hipLaunchKernelGGL((k_pair_build<M, true>), dim3((unsigned)I.nB), dim3(M * kWave), 0, s, I,
+                           p + 1);
         hipLaunchKernelGGL(k_pair_list<M>, dim3(tgs), dim3(256), 0, s, I, p + 1);
         if (p + 1 < phases)
             hipLaunchKernelGGL((k_pairs_list<M, false, false>), grid, th, 0, s, I, p + 1);

@@ -135,3 +135,19 @@ def test_a_captured_call_and_those_after_it_keep_the_workspace():
             assert torch.equal(getattr(out, k), getattr(want, k)), k
             assert torch.equal(getattr(other, k), getattr(want, k)), k
             getattr(out, k).zero_()
+
+
+@pytest.mark.parametrize("N", [1, 128, 129, 256, 1024, 1025])
+def test_small_hype_keeps_its_partial_sums_apart(N):
+    """Sizes whose stored masks take less room than the partial estimates."""
+    import oracle
+    o, _ = _problem(N, 3)
+    f = o.cpu().numpy()
+    rng = np.random.Generator(np.random.PCG64(N))
+    U, v = rng.random((6000, 3)).astype(np.float32), (f.max(0) * 1.1 + 0.01).astype(np.float32)
+    import torch
+    g = nsga3.hype_select(o, torch.from_numpy(v).cuda(), torch.from_numpy(U).cuda(), (N + 1) // 2,
+                          ctx=nsga3.Context(0))
+    w = oracle.hype_select(f, v, U, (N + 1) // 2)
+    assert g.info().status == 0 and np.array_equal(g.rank.cpu().numpy(), w.rank)
+    np.testing.assert_allclose(g.d.cpu().numpy(), w.d, rtol=1e-10, atol=1e-300)
