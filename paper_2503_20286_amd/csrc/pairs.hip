@@ -968,6 +968,8 @@ __global__ __launch_bounds__(kPhaseThreads) void k_phase(PairInst I, int32_t pha
     constexpr int MP = rec_stride(M);
     __shared__ uint32_t lds[kPhaseThreads / kWave + 1];
     __shared__ int32_t s_at, s_b;
+    // (the ticket is on its way while the counters are read)
+    if (threadIdx.x == 0) s_b = (int32_t)atomicAdd(&I.sync->ticket[phase], 1u);
     if (I.sc->err) return;
     const PhaseAt pa = phase_at(I, phase);
     if (pa.taken != phase || pa.stop) return;
@@ -980,7 +982,6 @@ __global__ __launch_bounds__(kPhaseThreads) void k_phase(PairInst I, int32_t pha
         J.din = I.din2;
     }
     I = phase_inst(I, phase);
-    if (threadIdx.x == 0) s_b = (int32_t)atomicAdd(&I.sync->ticket[phase], 1u);
     __syncthreads();
     const int32_t blk = s_b;
     const int32_t c0 = blk * kPhaseThreads;
