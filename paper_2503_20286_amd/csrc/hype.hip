@@ -311,9 +311,13 @@ __global__ void k_hv_keys(int64_t N, int64_t s, int parts, const int32_t *__rest
 // The R members of F_l with the smallest (key, index) join the selection: the
 // R-th smallest key by its digits from the top, one work-group over the list
 // of F_l, then (ties across the cut) the index by its digits.  Eight launches
-// of a histogram and a scatter each otherwise (115 us at N = 20k), which stay
-// for populations above kHvSelectMax.
-constexpr int64_t kHvSelectMax = 262144;
+// of a histogram and a scatter each otherwise, which stay for populations above
+// kHvSelectMax.  The list is short where there are several fronts; a population
+// of one front is its worst case (M = 3, by digits / by sort: 5k of N = 200k in F_l
+// 3.06 / 3.17 ms; one front, N = 20k 0.31 / 0.36, 50k 0.44 / 0.45, 200k 1.20 / 0.72,
+// with one member of a thread read at a time 1.48, and 2.30 / 1.59 at 250k).
+constexpr int64_t kHvSelectMax = 204800;
+constexpr int kHvAhead = 8;   // members of a thread that are read at once
 
 template <typename T, typename F>
 __device__ __forceinline__ T hv_digits(int nd, uint32_t n, uint32_t &need, int &sh, uint32_t *hist,
@@ -327,13 +331,11 @@ __device__ __forceinline__ T hv_digits(int nd, uint32_t n, uint32_t &need, int &
         lds_wait();
         __syncthreads();
         sh -= 8;
-        for (uint32_t i0 = 0; i0 < n; i0 += blockDim.x) {
-            const uint32_t i = i0 + threadIdx.x;
-            T v = 0;
-            const bool in = i < n && get(i, v) && (sh + 8 == 8 * nd || (T)(v >> (sh + 8)) == prefix);
+        auto tally = [&](bool in, T v) {
+            in = in && (sh + 8 == 8 * nd || (T)(v >> (sh + 8)) == prefix);
             const uint32_t dg = (uint32_t)(v >> sh) & 255u;
             const uint64_t act = ballot(in);
-            if (!act) continue;
+            if (!act) return;
             // (keys share their top digits: one atomic where a wave agrees)
             const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)dg, __builtin_ctzll(act));
             if (ballot(in && dg == d0) == act) {
@@ -341,6 +343,22 @@ __device__ __forceinline__ T hv_digits(int nd, uint32_t n, uint32_t &need, int &
             } else if (in) {
                 atomicAdd(&hist[dg], 1u);
             }
+        };
+        uint32_t i0 = 0;
+        for (; i0 + kHvAhead * blockDim.x <= n; i0 += kHvAhead * blockDim.x) {
+            T v[kHvAhead];
+            bool in[kHvAhead];
+#pragma unroll
+            for (int u = 0; u < kHvAhead; ++u)
+                in[u] = get(i0 + (uint32_t)u * blockDim.x + threadIdx.x, v[u]);
+#pragma unroll
+            for (int u = 0; u < kHvAhead; ++u) tally(in[u], v[u]);
+        }
+        for (; i0 < n; i0 += blockDim.x) {
+            const uint32_t i = i0 + threadIdx.x;
+            T v = 0;
+            const bool in = i < n && get(i, v);
+            tally(in, v);
         }
         lds_wait();
         __syncthreads();
@@ -396,10 +414,23 @@ __global__ __launch_bounds__(1024) void k_hv_select(const uint64_t *__restrict__
             return key[i] == cut;
         });
     }
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
-        const uint64_t k = key[i] >> sh;
-        if (k < cut || (k == cut && ((uint64_t)val[i] >> vsh) <= vcut)) selflag[val[i]] = 1;
+    auto mark = [&](uint64_t k, uint32_t i) {
+        k >>= sh;
+        if (k < cut || (k == cut && ((uint64_t)i >> vsh) <= vcut)) selflag[i] = 1;
+    };
+    uint32_t i0 = threadIdx.x;
+    for (; i0 + (kHvAhead - 1) * blockDim.x < n; i0 += kHvAhead * blockDim.x) {
+        uint64_t k[kHvAhead];
+        uint32_t i[kHvAhead];
+#pragma unroll
+        for (int u = 0; u < kHvAhead; ++u) {
+            k[u] = key[i0 + (uint32_t)u * blockDim.x];
+            i[u] = val[i0 + (uint32_t)u * blockDim.x];
+        }
+#pragma unroll
+        for (int u = 0; u < kHvAhead; ++u) mark(k[u], i[u]);
     }
+    for (; i0 < n; i0 += blockDim.x) mark(key[i0], val[i0]);
 }
 
 __global__ void k_hv_pick(const uint32_t *__restrict__ val, uint8_t *__restrict__ selflag,

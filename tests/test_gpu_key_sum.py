@@ -74,3 +74,27 @@ def test_hype_of_both_paths_at_size(monkeypatch):
     assert got.info().status == 0
     for k in ("rank", "d", "selected"):
         assert torch.equal(getattr(got, k), getattr(want, k)), k
+
+
+@pytest.mark.parametrize("N,kind", [(8191, "same"), (8192, "same"), (8193, "one"), (65537, "one"),
+                                    (204800, "one"), (204801, "one"), (204801, "same")])
+def test_hype_cut_of_long_last_fronts(N, kind):
+    """The last front's members with the largest estimates, the lower index first,
+    by digits and above the limit by a sort."""
+    import torch
+    rng = np.random.Generator(np.random.PCG64(N))
+    f = np.abs(rng.standard_normal((N, 3)))
+    f /= np.linalg.norm(f, axis=1, keepdims=True)
+    if kind == "same":
+        f = f[rng.integers(0, 40, N)]
+    o = torch.from_numpy(f.astype(np.float32)).cuda()
+    U = torch.rand((600, 3), device="cuda", generator=torch.Generator("cuda").manual_seed(N))
+    v = (o.max(0).values * 1.1).contiguous()
+    n = N // 3
+    r = nsga3.hype_select(o, v, U, n, ctx=nsga3.Context(0))
+    d, rank, l = r.d.cpu().numpy(), r.rank.cpu().numpy(), r.info().last_front
+    last = np.nonzero(rank == l)[0]
+    take = last[np.argsort(-d[last], kind="stable")][: n - int((rank < l).sum())]
+    assert r.info().status == 0 and len(take)
+    assert np.array_equal(r.selected.cpu().numpy(),
+                          np.sort(np.concatenate([np.nonzero(rank < l)[0], take])))
