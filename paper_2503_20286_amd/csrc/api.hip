@@ -221,7 +221,7 @@ Layout layout_pairs(int64_t N, int M, int H) {
     L.wit = bump(c, 16 * kWBlk * nB);
     L.idx = bump(c, 4 * nB * nBp);
     select_layout(L, c, N, M, H);
-    L.mask = bump(c, 16 * (size_t)kWBlk * (mask_units(nB) + 1));
+    L.mask = bump(c, 16 * (size_t)kWBlk * (mask_units(nB, M) + 1));
     L.total = c;
     return L;
 }
@@ -532,7 +532,7 @@ PairInst pair_inst(char *w, const Layout &L, const nsga3_problem &p, int32_t *ra
     I.nz = WS(uint64_t, nz);
     I.idx = WS(uint32_t, idx);
     I.mask = WS(uint4, mask);
-    size_t units = mask_units((size_t)I.nB);
+    size_t units = mask_units((size_t)I.nB, I.M);
     if (cfg.mask_units >= 0 && (size_t)cfg.mask_units < units) units = (size_t)cfg.mask_units;
     const size_t pools = (size_t)I.nB * I.nB <= (size_t)kMaskPools ? 1 : (size_t)kMaskPools;
     I.poolMask = (uint32_t)pools - 1u;

@@ -67,21 +67,24 @@ constexpr int kRankLowBytes = 32768;
 // Stored masks: units of 2 KiB (128 points x 128 members) handed out from
 // kMaskPools counters, or from one where there are no more pairs than those (N <=
 // 1024: nothing is kept for uneven counters, 1 MiB else).  Up to kMaskFullUnits every pair of blocks has one;
-// beyond, a third of the pairs.  The masks are needed by the pairs whose boxes
-// overlap in some objective and lie in order in the others: 10 % of all for
-// sphere-shaped populations, 13-16 % for uniform or normal ones, 23 to 31 %
-// where the objectives move together in part, more than that nowhere found.  A
-// pair without a unit is probed again wherever a level needs it, which is 30
-// times a mask's reads: with a sixteenth of the pairs the ranks of 200k uniform
-// points, M = 5, took 17 ms instead of 1.3 (the workspace 1.7 GB instead of
-// 0.37, which allocate in the same 50 us).
+// beyond, half of the pairs up to kMaskHalfUnits units (and for 10 objectives or
+// more), then a third.  The masks
+// are needed by the pairs whose boxes overlap in some objective and lie in order
+// in the others: 10 % of all for sphere-shaped populations, 13-16 % for uniform or
+// normal ones, 23 to 36 % where the objectives move together in part, the most for
+// few blocks and many objectives.  A pair without a unit is probed again wherever
+// a level needs it, which is 30 times a mask's reads: with a sixteenth of the pairs
+// the ranks of 200k uniform points, M = 5, took 17 ms instead of 1.3 (the
+// workspace 1.7 GB instead of 0.37, which allocate in the same 50 us), and a tenth of
+// the pairs without one at N = 60k, M = 16 6.7 ms instead of 0.33.
 constexpr int kMaskPools = 64;
-constexpr size_t kMaskFullUnits = 16384;
+constexpr size_t kMaskFullUnits = 16384, kMaskHalfUnits = 524288;
 constexpr uint32_t kUnitNone = 0xffffffffu;  // no unit: probe again
-inline size_t mask_units(size_t nB) {
+inline size_t mask_units(size_t nB, int M) {
     const size_t full = nB * nB;
-    const size_t most = full / 3 > kMaskFullUnits ? full / 3 : kMaskFullUnits;
-    const size_t u = full < most ? full : most;
+    size_t u = full / 2 < kMaskHalfUnits || M >= 10 ? full / 2 : kMaskHalfUnits;
+    if (u < full / 3) u = full / 3;
+    if (u < kMaskFullUnits) u = full < kMaskFullUnits ? full : kMaskFullUnits;
     return full <= kMaskPools ? full : (u + kMaskPools - 1) / kMaskPools * kMaskPools + 8 * kMaskPools;
 }
 
