@@ -193,15 +193,17 @@ __global__ __launch_bounds__(256) void k_cell_code(PairInst I) {
             if (eq) code = (uint32_t)(pair_heavy_cell(I.T) + j);
         }
     }
-    // points of a wave that share a cell take one atomic, the first few cells'
-    // (heavy rows, or tight clusters)
+    // points of a wave that share a cell take one atomic, where they are many
+    // (heavy rows, wide cells)
     uint32_t slot = 0;
-    uint64_t act = ballot(in);
-    for (int q = 0; q < (nh > 0 ? 4 : 1) && act; ++q) {
-        const int l = __builtin_ctzll(act);
+    uint64_t act = ballot(in), ask = act;
+    const uint64_t heavy = nh > 0 ? ballot(in && code >= (uint32_t)pair_heavy_cell(I.T)) : 0ull;
+    for (int q = 0; q < 4 && ask; ++q) {
+        const int l = __builtin_ctzll(ask & heavy ? ask & heavy : ask);
         const uint32_t c0 = (uint32_t)__builtin_amdgcn_readlane((int)code, l);
         const uint64_t same = ballot(((act >> lane_id()) & 1) != 0 && code == c0);
-        if (nh == 0 && same != act) break;
+        ask &= ~same;
+        if (__popcll(same) < 8) continue;
         uint32_t n = 0;
         if ((int)lane_id() == l) n = atomicAdd(&I.cell[c0], (uint32_t)__popcll(same));
         n = (uint32_t)__builtin_amdgcn_readlane((int)n, l) + lanes_below(same);
@@ -280,23 +282,10 @@ __global__ __launch_bounds__(256) void k_cell_place(PairInst I) {
 // small; the splitters cut each objective by itself, so identical rows and
 // objectives that move together may put any share of the points into one cell.
 constexpr int kCellOwn = 256;     // positions of a work-group
-// Points of a cell that a point counts alone.  (64 / 128 / 256 / 1024: rows that
-// move together in part, N = 200k, M = 8, 118 / 112 / 152 / 378 us for all cells; a
-// shell's cells hold at most 63.)
+// Points of a cell that a point counts alone.  (64 / 128 / 256, all cells: rows
+// that move together in part, N = 34k, M = 16, 91 / 120 / 152 us, N = 20k, M = 5, 69 / 52 / 48;
+// a front of N = 200k, M = 5, whose cells hold up to 87, 71 / 34 / 34.)
 constexpr uint32_t kCellWide = 128;
-
-// x before y in the order of rows (kEq: or the same).
-template <int M, bool kEq>
-__device__ __forceinline__ bool row_before(const uint32_t (&x)[M], const uint32_t *y, int stride) {
-    bool lt = false, eq = true;
-#pragma unroll
-    for (int k = 0; k < M; ++k) {
-        const uint32_t v = y[k * stride];
-        lt = lt || (eq && x[k] < v);
-        eq = eq && x[k] == v;
-    }
-    return lt || (kEq && eq);
-}
 
 // Record, point index and run of identical rows [run, end) of position at.
 template <int M>
@@ -318,9 +307,10 @@ __device__ __forceinline__ void put_row(const PairInst &I, const uint32_t (&x)[M
 // A wide cell [c0, c1), of which the work-group has the points at positions
 // [a, b): they are put in order in LDS, and every point of the cell is looked up
 // among them; the numbers of points that fall between them give each one's
-// place.  The cell costs a work-group its size / 256 times three searches of 8
-// steps instead of its size (N = 200k, M = 5, rows near one line, 27k points in
-// a cell: the call 19.4 ms alone, 14.1 so, 0.34 of them here).
+// place.  The cell costs a work-group its size / 256 times a search of 8 steps
+// instead of its size.  First keys decide nearly always; the others are read only
+// where two are equal.  (Rows near one line, N = 200k, M = 5, 27k points in a cell:
+// the call 19.4 ms when each point counted its cell, 13.9 so.)
 template <int M>
 struct WideCell {
     uint32_t key[M][kCellOwn];
@@ -335,84 +325,157 @@ __device__ __forceinline__ void wide_cell(const PairInst &I, WideCell<M> &W, uin
     constexpr int MP = rec_stride(M);
     const int t = (int)threadIdx.x;
     const int n = (int)(b - a);
-    uint32_t x[M], i = 0xffffffffu;   // (places past the last point: after every row)
-#pragma unroll
-    for (int k = 0; k < M; ++k) x[k] = 0xffffffffu;
-    if (t < n) {
-        const uint32_t *r = I.trec + (size_t)(a + (uint32_t)t) * MP;
-#pragma unroll
-        for (int k = 0; k < M; ++k) x[k] = r[k];
-        i = r[M];
+    {
+        // (places past the last point: after every row)
+        const uint32_t *r = I.trec + (size_t)(t < n ? a + (uint32_t)t : a) * MP;
+#pragma unroll 1
+        for (int k = 0; k < M; ++k) W.key[k][t] = t < n ? r[k] : 0xffffffffu;
+        W.idx[t] = t < n ? r[M] : 0xffffffffu;
     }
+    // a bitonic network moves first keys and places
+    uint32_t a0 = W.key[0][t], p = (uint32_t)t;
+#pragma unroll 1
     for (int len = 2; len <= kCellOwn; len <<= 1) {
+#pragma unroll 1
         for (int d = len >> 1; d > 0; d >>= 1) {
             __syncthreads();
-#pragma unroll
-            for (int k = 0; k < M; ++k) W.key[k][t] = x[k];
-            W.idx[t] = i;
+            W.le[t] = a0;
+            W.lt[t] = p;
             __syncthreads();
-            const int o = t ^ d;
-            const uint32_t oi = W.idx[o];
-            const bool lt = row_before<M, false>(x, &W.key[0][o], kCellOwn);
-            const bool le = row_before<M, true>(x, &W.key[0][o], kCellOwn);
-            const bool first = lt || (le && i < oi);
-            if (first != (((t & len) == 0) == ((t & d) == 0))) {
-#pragma unroll
-                for (int k = 0; k < M; ++k) x[k] = W.key[k][o];
-                i = oi;
+            const uint32_t b0 = W.le[t ^ d], r = W.lt[t ^ d];
+            int o = a0 < b0 ? -1 : (a0 > b0 ? 1 : 0);
+            if (a0 == 0xffffffffu && o == 0) o = p < r ? -1 : 1;  // (past the last point)
+            if (ballot(o == 0)) {
+#pragma unroll 1
+                for (int k = 1; k < M && ballot(o == 0); ++k) {
+                    const uint32_t v = W.key[k][p], w = W.key[k][r];
+                    o = o != 0 ? o : (v < w ? -1 : (v > w ? 1 : 0));
+                }
+                const uint32_t v = W.idx[p], w = W.idx[r];
+                o = o != 0 ? o : (v < w ? -1 : 1);
+            }
+            if ((o < 0) != (((t & len) == 0) == ((t & d) == 0))) {
+                a0 = b0;
+                p = r;
             }
         }
     }
     __syncthreads();
-#pragma unroll
-    for (int k = 0; k < M; ++k) W.key[k][t] = x[k];
-    W.idx[t] = i;
+#pragma unroll 1
+    for (int k = 0; k <= M; ++k) {  // (the rows after them)
+        uint32_t *row = k < M ? W.key[k < M ? k : 0] : W.idx;
+        const uint32_t v = row[p];
+        __syncthreads();
+        row[t] = v;
+        lds_wait();
+        __syncthreads();
+    }
     for (int q = t; q <= kCellOwn; q += kCellOwn) W.le[q] = W.lt[q] = W.at[q] = 0u;
+    lds_wait();
     __syncthreads();
-    for (uint32_t q = c0 + (uint32_t)t; q < c1; q += kCellOwn) {
-        uint32_t y[M];
-        const uint32_t *r = I.trec + (size_t)q * MP;
+    // four of a thread side by side: by the first key alone, where no other row here
+    // has it
+    constexpr int kAhead = 4;
+#pragma unroll 1
+    for (uint32_t q0 = c0; q0 < c1; q0 += kAhead * kCellOwn) {
+        uint32_t y[kAhead];
+        int at[kAhead];
 #pragma unroll
-        for (int k = 0; k < M; ++k) y[k] = r[k];
-        const uint32_t yi = r[M];
-        int lo = 0, hi;   // points here before y's row, and not after it
-        for (int s = n; s > 0;) {
-            const int h = s >> 1;
-            const bool go = !row_before<M, true>(y, &W.key[0][lo + h], kCellOwn);
-            lo = go ? lo + h + 1 : lo;
-            s = go ? s - h - 1 : h;
+        for (int u = 0; u < kAhead; ++u) {
+            y[u] = I.trec[(size_t)min(q0 + (uint32_t)(u * kCellOwn + t), c1 - 1u) * MP];
+            at[u] = 0;
         }
-        hi = lo;
-        if (lo < n && !row_before<M, false>(y, &W.key[0][lo], kCellOwn)) {
-            for (int s = n - lo; s > 0;) {
-                const int h = s >> 1;
-                const bool go = !row_before<M, false>(y, &W.key[0][hi + h], kCellOwn);
-                hi = go ? hi + h + 1 : hi;
-                s = go ? s - h - 1 : h;
+#pragma unroll
+        for (int s = kCellOwn / 2; s > 0; s >>= 1)
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) at[u] += W.key[0][at[u] + s - 1] < y[u] ? s : 0;
+        bool tie[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const uint32_t v = W.key[0][at[u]];
+            at[u] += v < y[u] ? 1 : 0;   // (the last place)
+            const uint32_t q = q0 + (uint32_t)(u * kCellOwn + t);
+            const bool same = v == y[u];
+            // (a row of the work-group's own, the only one of its first key)
+            const bool own = same && q >= a && q < b &&
+                             (at[u] + 1 >= n || W.key[0][at[u] + 1] != y[u]);
+            tie[u] = same && !own && q < c1;
+            if (q < c1 && !tie[u]) {
+                atomicAdd(&W.le[at[u]], 1u);
+                atomicAdd(&W.lt[at[u] + (own ? 1 : 0)], 1u);
+                atomicAdd(&W.at[at[u] + (own ? 1 : 0)], 1u);
             }
         }
-        int e = lo;       // and those of its row up to its own index
-        for (int s = hi - lo; s > 0;) {
-            const int h = s >> 1;
-            const bool go = W.idx[e + h] <= yi;
-            e = go ? e + h + 1 : e;
-            s = go ? s - h - 1 : h;
+#pragma unroll 1
+        for (int u = 0; u < kAhead; ++u) {
+            const bool on = u == 0 ? tie[0] : u == 1 ? tie[1] : u == 2 ? tie[2] : tie[3];
+            if (!on) continue;
+            const uint32_t q = q0 + (uint32_t)(u * kCellOwn + t);
+            const uint32_t *row = I.trec + (size_t)q * MP;
+            const uint4 f = *reinterpret_cast<const uint4 *>(row);
+            const uint32_t g[4] = {f.x, f.y, f.z, f.w}, y0 = f.x;
+            // points here before the row (first search), and not after it (second)
+            int pos = 0, lo = 0;
+#pragma unroll 1
+            for (int up = 0; up < 2; ++up) {
+                for (int s = n - pos; s > 0;) {
+                    const int h = s >> 1;
+                    const uint32_t v0 = W.key[0][pos + h];
+                    int o = y0 < v0 ? -1 : (y0 > v0 ? 1 : 0);
+#pragma unroll
+                    for (int k = 1; k < 4 && k < M; ++k) {
+                        const uint32_t v = W.key[k][pos + h];
+                        o = o != 0 ? o : (g[k] < v ? -1 : (g[k] > v ? 1 : 0));
+                    }
+#pragma unroll 1
+                    for (int k = 4; k < M && ballot(o == 0); ++k) {
+                        const uint32_t x = row[k], v = W.key[k][pos + h];
+                        o = o != 0 ? o : (x < v ? -1 : (x > v ? 1 : 0));
+                    }
+                    const bool go = o > 0 || (up != 0 && o == 0);
+                    pos = go ? pos + h + 1 : pos;
+                    s = go ? s - h - 1 : h;
+                }
+                if (up == 0) lo = pos;
+                if (pos >= n || W.key[0][pos] != y0) break;
+            }
+            int e = lo;       // and those of its row up to its own index
+            if (pos > lo) {
+                const uint32_t yi = row[M];
+                for (int s = pos - lo; s > 0;) {
+                    const int h = s >> 1;
+                    const bool go = W.idx[e + h] <= yi;
+                    e = go ? e + h + 1 : e;
+                    s = go ? s - h - 1 : h;
+                }
+            }
+            atomicAdd(&W.le[lo], 1u);
+            atomicAdd(&W.lt[pos], 1u);
+            atomicAdd(&W.at[e], 1u);
         }
-        atomicAdd(&W.le[lo], 1u);
-        atomicAdd(&W.lt[hi], 1u);
-        atomicAdd(&W.at[e], 1u);
     }
     lds_wait();
     __syncthreads();
     // point s comes after every y that falls at s or before
-    uint32_t tot;
-    const uint32_t vle = W.le[t], vlt = W.lt[t], vat = W.at[t];
-    const uint32_t le = vle + block_exclusive_scan(vle, W.scan, &tot);
-    __syncthreads();
-    const uint32_t lt = vlt + block_exclusive_scan(vlt, W.scan, &tot);
-    __syncthreads();
-    const uint32_t at = c0 + vat + block_exclusive_scan(vat, W.scan, &tot);
-    if (t < n) put_row<M>(I, x, i, at, c0 + lt, c0 + le);
+    uint32_t tot, sum[3];
+#pragma unroll 1
+    for (int h = 0; h < 3; ++h) {
+        const uint32_t v = (h == 0 ? W.le : h == 1 ? W.lt : W.at)[t];
+        const uint32_t s = v + block_exclusive_scan(v, W.scan, &tot);
+        sum[0] = h == 0 ? s : sum[0];
+        sum[1] = h == 1 ? s : sum[1];
+        sum[2] = h == 2 ? s : sum[2];
+        __syncthreads();
+    }
+    if (t < n) {
+        const uint32_t at = c0 + sum[2];
+        uint32_t *dst = I.recs + (size_t)at * MP;
+#pragma unroll 1
+        for (int k = 0; k < MP; ++k) dst[k] = k < M ? W.key[k < M ? k : 0][t] : (k == M ? at : 0u);
+        I.sval[at] = W.idx[t];
+        I.runs[at] = (int32_t)(c0 + sum[1]);
+        I.rune[at] = (int32_t)(c0 + sum[0]);
+    }
     lds_wait();
     __syncthreads();
 }
@@ -437,6 +500,7 @@ __global__ __launch_bounds__(kCellOwn) void k_cell_sort(PairInst I) {
             c1 = c0;
         } else if (c1 - c0 <= kCellWide) {
             uint32_t less = 0, same = 0, before = 0;
+#pragma unroll 4
             for (uint32_t q = c0; q < c1; ++q) {
                 const uint32_t *r = I.trec + (size_t)q * MP;
                 bool lt = false, eq = true;
