@@ -544,14 +544,17 @@ __global__ __launch_bounds__(kCellOwn) void k_cell_sort(PairInst I) {
 // Small problems: the whole order by one work-group of a thread a point.  A
 // handful of blocks needs no cells: the rows are put in lexicographic order by
 // counting.  Four launches less, and the splitters (N = 200, M = 3: 94 us a
-// call with them).
+// call with them).  One CU makes all N x N x M compares, so the line is at N x M:
+// by one work-group / by cells M = 2, N = 512 148 / 149 us, 640 194 / 176; M = 5, N = 128
+// 93 / 98, 256 111 / 104, 1024 334 / 124; M = 16, N = 64 145 / 144, 1024 878 / 175.
 constexpr int kOrderOne = 1024;
+constexpr int kOrderOneKeys = 1024;
 constexpr int kOrderOneRefs = 4096;   // (it also scales the references, and clears their counters)
 
 template <int M>
 __global__ __launch_bounds__(kOrderOne) void k_order_one(PairInst I, RefArgs R, uint32_t *zero,
                                                          int64_t nzero) {
-    __shared__ uint32_t row[kOrderOne * M];
+    __shared__ uint32_t row[kOrderOneKeys];
     __shared__ uint32_t smin[M];
     const int t = (int)threadIdx.x;
     init_scalars(I.sc, t);
@@ -566,7 +569,7 @@ __global__ __launch_bounds__(kOrderOne) void k_order_one(PairInst I, RefArgs R, 
         const float f = in ? I.objs[(int64_t)t * M + k] : 0.0f;
         bad |= !__builtin_isfinite(f);
         x[k] = order_key(f);
-        row[t * M + k] = x[k];
+        if (in) row[t * M + k] = x[k];
     }
     if (t < M) smin[t] = 0xffffffffu;
     __syncthreads();  // (the scalars, too)
@@ -1155,7 +1158,7 @@ static hipError_t launch_pairs(const PairInst &I, const RefArgs &R, bool one, ui
 
 hipError_t run_pairs(const PairInst &I, const RefArgs &R, uint32_t *zero, int64_t nzero,
                      const Marker &mark, hipStream_t s) {
-    const bool one = I.N <= kOrderOne && R.Hpad <= kOrderOneRefs;
+    const bool one = (int64_t)I.N * I.M <= kOrderOneKeys && R.Hpad <= kOrderOneRefs;
     if (!one) {
         const int nfill = (int)((nzero + 4 * kSplitterSample - 1) / (4 * kSplitterSample));
         const int nf = nfill < 1 ? 1 : nfill > 512 ? 512 : nfill;

@@ -27,7 +27,9 @@ def _objs(kind, N, M):
 
 @pytest.mark.parametrize("N,M,kind", [(200000, 3, "cube"), (200000, 5, "cube"), (50000, 5, "cube"),
                                       (200000, 4, "normal"), (200000, 5, "0.2"), (200000, 5, "1.0"),
-                                      (100000, 8, "1.0"), (33000, 4, "0.5")])
+                                      (100000, 8, "1.0"), (33000, 4, "0.5"), (60000, 16, "0.3"),
+                                      (34000, 16, "0.5"), (1024, 16, "cube"), (765, 13, "normal"),
+                                      (1000, 5, "cube"), (600, 8, "normal"), (300, 10, "cube")])
 @pytest.mark.parametrize("counts", [True, False])
 def test_no_slower_than_the_key_sum_order(N, M, kind, counts, monkeypatch):
     import torch
@@ -37,7 +39,7 @@ def test_no_slower_than_the_key_sum_order(N, M, kind, counts, monkeypatch):
         monkeypatch.setenv("NSGA3_PAIRS", pairs)
         ctx = nsga3.Context(0)
         best[pairs] = 1e9
-        for _ in range(4):
+        for _ in range(4 if N > 5000 else 40):
             torch.cuda.synchronize()
             t = time.perf_counter()
             out[pairs] = nsga3.select(o, r, N // 2, ctx=ctx, want_counts=counts)
@@ -86,3 +88,19 @@ def test_fronts_taken_off(N, layers):
     assert np.array_equal(res.rank.cpu().numpy(), rank)
     assert (i.status, i.num_fronts, i.last_front, i.last_front_size) == (
         0, int(rank.max()) + 1, l, int((rank == l).sum()))
+
+
+@pytest.mark.parametrize("N,M", [(512, 2), (513, 2), (341, 3), (342, 3), (204, 5), (205, 5), (64, 16),
+                                 (65, 16), (1024, 16), (2, 16), (1, 2)])
+def test_small_orders(N, M):
+    """By one work-group up to N x M = 1024 keys, by cells above."""
+    import torch
+    f = _objs("normal", N, M)
+    f[: N // 3] = f[N // 2: N // 2 + N // 3]
+    res = nsga3.select(torch.from_numpy(f).cuda(), torch.eye(M, device="cuda") + 0.1, (N + 1) // 2,
+                       ctx=nsga3.Context(0))
+    din, dout = oracle.dominance(f)[:2]
+    assert res.info().status == 0
+    assert np.array_equal(res.rank.cpu().numpy(), oracle.ranks(f)[0])
+    assert np.array_equal(res.dom_in.cpu().numpy(), din)
+    assert np.array_equal(res.dom_out.cpu().numpy(), dout)
