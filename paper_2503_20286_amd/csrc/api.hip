@@ -77,6 +77,7 @@ struct nsga3_ctx {
     bool pairs;                     // spatially ordered path where its workspace fits
     int rank_groups, rank_started;  // LaunchCfg's
     int64_t mask_units;             // LaunchCfg's
+    int look_polls;                 // LaunchCfg's
     volatile int32_t *last_fronts;  // pinned: front count, then level sizes, of the latest call
     std::vector<hipEvent_t> ev_pool;   // NSGA3_NUM_PHASES + 1 events per recorded call
     size_t ev_used;
@@ -406,6 +407,7 @@ LaunchCfg ctx_cfg(const nsga3_ctx *ctx, int M, int64_t N) {
     cfg.rank_groups = ctx->rank_groups;
     cfg.rank_started = ctx->rank_started;
     cfg.mask_units = ctx->mask_units;
+    cfg.look_polls = ctx->look_polls;
     // The previous call's front count and level sizes arrive asynchronously
     // in pinned memory; they only size launches (a stale or torn read shifts
     // work between the enqueued levels and the tail, never the results).
@@ -555,6 +557,7 @@ PairInst pair_inst(char *w, const Layout &L, const nsga3_problem &p, int32_t *ra
     I.dom_in = p.dom_in;
     I.dom_out = p.dom_out;
 #undef WS
+    I.lookPolls = cfg.look_polls;
     rank_shape(I, cfg.rank_groups > 0 ? cfg.rank_groups : cfg.num_cus / 4, cfg.rank_started);
     return I;
 }
@@ -845,6 +848,10 @@ nsga3_status nsga3_create(nsga3_ctx **out, int device, const nsga3_options *opt)
     // again wherever a level needs them; same results)
     c->mask_units = -1;
     if (const char *e = getenv("NSGA3_MASK_UNITS")) c->mask_units = atoll(e);
+    // NSGA3_LOOK_POLLS: looks at an earlier block's count before a block makes it
+    // itself (0: every count it does not find at once)
+    c->look_polls = LaunchCfg().look_polls;
+    if (const char *e = getenv("NSGA3_LOOK_POLLS")) c->look_polls = atoi(e);
     c->last_fronts = nullptr;
     {
         void *h = nullptr;

@@ -81,6 +81,7 @@ struct LaunchCfg {
     // (0: by the CUs), and how many it starts (0: those it wants)
     int rank_groups = 0, rank_started = 0;
     int64_t mask_units = -1;  // stored masks of that path, at most (-1: by the size)
+    int look_polls = 256;     // looks at another block's count before a block makes it itself
 };
 
 // Points left before a peeling tail at or below which one work-group

@@ -97,7 +97,6 @@ struct RankSync {
     uint32_t lv[kMaxPhases];     // points of the fronts taken off first
     int32_t left[kMaxPhases];    // points left after each of them
     uint32_t chunk[kMaxPhases][kPairsMaxN / kPhaseThreads];   // the same of a compaction chunk
-    uint32_t ticket[kMaxPhases];   // compaction work-groups that have started
     uint32_t items[kMaxPhases + 1], next[kMaxPhases + 1];   // listed and taken items of a pass
     RankWord team;               // v [15:0] work-groups that have started, [31:16] the closed
                                  // team's size
@@ -115,6 +114,7 @@ struct PairInst {
     int32_t groups;           // work-groups wanted by the persistent rank launch
     int32_t started;          // work-groups it starts (groups, but for tests)
     int32_t rounds;           // 64-point groups of a wave that its LDS holds at once
+    int32_t lookPolls;        // looks at a count before a work-group makes it itself
     uint8_t bits[16];         // cell code bits per objective
     uint32_t *spl;            // [M * 64] splitters
     uint32_t *cell;           // [pair_cells(T) + 1] counts, then starts

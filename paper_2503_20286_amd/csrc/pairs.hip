@@ -1026,17 +1026,16 @@ __global__ __launch_bounds__(kPairWaves * kWave) void k_pairs_list(PairInst I, i
 // the same order (a block that straddled two distant chunks would meet half of
 // all tiles: without the order the second pass took as long as the first).  A
 // work-group takes kPhaseThreads positions, publishes how many stay, and reads
-// the numbers of the work-groups before it.  Chunks go to work-groups in the order in which
-// these start (each XCD starts its own in order, so a block index says nothing
-// about the others): who waits, waits for a work-group that is running.
+// the numbers of the work-groups before it.  One of these may not be running, for as
+// long as other streams' kernels hold the CUs of its XCD (each XCD starts its own
+// in order): a number that was not published after I.lookPolls looks is counted
+// here, so that no work-group depends on another's start.
 // ---------------------------------------------------------------------------
 template <int M>
 __global__ __launch_bounds__(kPhaseThreads) void k_phase(PairInst I, int32_t phase) {
     constexpr int MP = rec_stride(M);
     __shared__ uint32_t lds[kPhaseThreads / kWave + 1];
-    __shared__ int32_t s_at, s_b;
-    // (the ticket is on its way while the counters are read)
-    if (threadIdx.x == 0) s_b = (int32_t)atomicAdd(&I.sync->ticket[phase], 1u);
+    __shared__ int32_t s_at;
     if (I.sc->err) return;
     const PhaseAt pa = phase_at(I, phase);
     if (pa.taken != phase || pa.stop) return;
@@ -1049,8 +1048,7 @@ __global__ __launch_bounds__(kPhaseThreads) void k_phase(PairInst I, int32_t pha
         J.din = I.din2;
     }
     I = phase_inst(I, phase);
-    __syncthreads();
-    const int32_t blk = s_b;
+    const int32_t blk = (int32_t)blockIdx.x;
     const int32_t c0 = blk * kPhaseThreads;
     if (c0 >= I.N) return;  // (work-groups after this one return too)
     const int32_t p = c0 + (int32_t)threadIdx.x;
@@ -1071,14 +1069,17 @@ __global__ __launch_bounds__(kPhaseThreads) void k_phase(PairInst I, int32_t pha
     }
     __syncthreads();
     if ((int32_t)threadIdx.x < blk) {
-        uint32_t v, spins = 0;
+        uint32_t v;
+        int32_t looks = 0;
         while (!((v = __hip_atomic_load(&cnt[threadIdx.x], __ATOMIC_RELAXED,
                                         __HIP_MEMORY_SCOPE_AGENT)) & 0x80000000u)) {
-            __builtin_amdgcn_s_sleep(1);
-            if (++spins > (1u << 26)) {  // an earlier work-group never published
-                atomicOr(&I.sc->err, (uint32_t)kErrBarrierTimeout);
+            if (looks++ >= I.lookPolls) {  // (the degrees are this launch's input)
+                const int32_t b = (int32_t)threadIdx.x * kPhaseThreads;
+                v = 0;
+                for (int32_t q = b; q < b + kPhaseThreads; ++q) v += I.din[q] != 0 ? 1u : 0u;
                 break;
             }
+            __builtin_amdgcn_s_sleep(1);
         }
         atomicAdd(&s_at, (int32_t)(v & 0x7fffffffu));
     }

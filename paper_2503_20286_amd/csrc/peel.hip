@@ -39,10 +39,11 @@ __device__ __forceinline__ void copy_rec(uint32_t *__restrict__ d, const uint32_
 
 // ---------------------------------------------------------------------------
 // split (one launch per level): single-pass ordered partition with a
-// decoupled look-back over per-block counts.  Tiles go to blocks in the order in
-// which these start (each XCD starts its own in order, so a block index says
-// nothing about the others): who waits, waits for a block that is running.  The
-// ticket is the entry behind the blocks' states.
+// decoupled look-back over per-block counts.  A block before this one may not be
+// running, for as long as other streams' kernels hold the CUs of its XCD (each
+// XCD starts its own blocks in order): what was not published after `polls`
+// looks is counted here, so that no block depends on another's start.  (Tiles
+// by a ticket, in the order of the starts, took 4 % longer at N = 292k, M = 3.)
 // ---------------------------------------------------------------------------
 template <int M>
 __global__ __launch_bounds__(kThreads) void k_split(
@@ -50,15 +51,12 @@ __global__ __launch_bounds__(kThreads) void k_split(
     const int32_t *__restrict__ scnt, int32_t n_static, int32_t level, uint32_t *__restrict__ fdst,
     uint32_t *__restrict__ udst, int32_t *__restrict__ urun_dst, int32_t *__restrict__ ucnt_dst,
     int32_t *__restrict__ rank_s, int32_t *__restrict__ fsize, int32_t *__restrict__ usize,
-    uint64_t *__restrict__ lb_cur, uint64_t *__restrict__ lb_next, DevScalars *__restrict__ sc) {
+    uint64_t *__restrict__ lb_cur, uint64_t *__restrict__ lb_next, int32_t polls,
+    DevScalars *__restrict__ sc) {
     constexpr int MP = rec_stride(M);
     __shared__ uint32_t lds[17];
     __shared__ uint32_t s_pref[2];
-    __shared__ int32_t s_blk;
-    if (threadIdx.x == 0) {  // ready for the next level
-        lb_next[blockIdx.x] = 0;
-        if (blockIdx.x == 0) lb_next[gridDim.x] = 0;
-    }
+    if (threadIdx.x == 0) lb_next[blockIdx.x] = 0;  // ready for the next level
     if (sc->err) return;
     const int32_t n = n_static >= 0 ? n_static : usize[level - 1];
     if (n_static < 0 && n > 0 && fsize[level - 1] == 0) {  // impossible for a partial order
@@ -69,10 +67,7 @@ __global__ __launch_bounds__(kThreads) void k_split(
         if (blockIdx.x == 0 && threadIdx.x == 0) { fsize[level] = 0; usize[level] = 0; }
         return;
     }
-    if (threadIdx.x == 0)
-        s_blk = (int32_t)atomicAdd((unsigned long long *)&lb_cur[gridDim.x], 1ull);
-    __syncthreads();
-    const int32_t blk = s_blk;
+    const int32_t blk = (int32_t)blockIdx.x;
     const int32_t e0 = blk * kSplitTile;
     if (e0 >= n) return;
     const int32_t nb = (n + kSplitTile - 1) / kSplitTile;
@@ -106,23 +101,31 @@ __global__ __launch_bounds__(kThreads) void k_split(
                 __hip_atomic_store(&lb_cur[blk], lb_pack(1, bf, bu), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
             int32_t base = blk - 1;
-            uint64_t spins = 0;
+            int32_t looks = 0;
             while (true) {
                 const int32_t q = base - lane;
-                const uint64_t v = q >= 0 ? __hip_atomic_load(&lb_cur[q], __ATOMIC_RELAXED,
-                                                              __HIP_MEMORY_SCOPE_AGENT)
-                                          : lb_pack(2, 0, 0);
+                uint64_t v = q >= 0 ? __hip_atomic_load(&lb_cur[q], __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_AGENT)
+                                    : lb_pack(2, 0, 0);
                 const uint32_t st = (uint32_t)(v >> 62);
                 const uint64_t inc = ballot(st == 2);
                 const int first = inc ? __builtin_ctzll(inc) : kWave;   // nearest inclusive lane
                 const uint64_t need = first < kWave - 1 ? ((2ull << first) - 1ull) : ~0ull;
-                if (ballot(st == 0) & need) {
+                uint64_t miss = ballot(st == 0) & need;
+                if (miss && looks < polls) {
                     __builtin_amdgcn_s_sleep(1);
-                    if (++spins > (1ull << 26)) {  // a predecessor never published
-                        if (lane == 0) atomicOr(&sc->err, (uint32_t)kErrBarrierTimeout);
-                        break;
-                    }
+                    ++looks;
                     continue;
+                }
+                for (; miss; miss &= miss - 1) {  // (the counts are this launch's input)
+                    const int l = __builtin_ctzll(miss);
+                    uint32_t cf = 0, cu = 0;
+                    for (int32_t r = 0; r < kSplitTile; r += kWave) {
+                        const int32_t c = scnt[(base - l) * kSplitTile + r + lane];
+                        cf += (uint32_t)__popcll(ballot(c == 0));
+                        cu += (uint32_t)__popcll(ballot(c > 0));
+                    }
+                    if (lane == l) v = lb_pack(1, cf, cu);
                 }
                 const bool take = lane <= first;
                 pf += wave_sum(take ? (uint32_t)(v >> 31) & 0x7fffffffu : 0u);
@@ -573,11 +576,11 @@ static hipError_t launch_peel(const SortViews &v, const LaunchCfg &cfg, hipStrea
         if (k == 0) {
             hipLaunchKernelGGL(k_split<M>, dim3(nbs), dim3(kThreads), 0, s, v.recs, v.runstart,
                                v.dom_in_s, N, 0, v.fk[0], v.uk[0], v.urun[0], v.ucnt[0], v.rank_s,
-                               v.fsize, v.usize, lb_cur, lb_next, v.sc);
+                               v.fsize, v.usize, lb_cur, lb_next, cfg.look_polls, v.sc);
         } else {
             hipLaunchKernelGGL(k_split<M>, dim3(nbs), dim3(kThreads), 0, s, v.uk[p], v.urun[p],
                                v.ucnt[p], -1, k, v.fk[q], v.uk[q], v.urun[q], v.ucnt[q], v.rank_s,
-                               v.fsize, v.usize, lb_cur, lb_next, v.sc);
+                               v.fsize, v.usize, lb_cur, lb_next, cfg.look_polls, v.sc);
         }
         if (cfg.bitsets) {
             const int32_t fe = k < kProfLevels ? cfg.fprev[k] : 0;

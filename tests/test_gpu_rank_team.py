@@ -64,3 +64,20 @@ def test_streams_of_both_paths_at_once():
         assert g.info().status == 0
         for k in ("rank", "dom_in", "dom_out", "selected"):
             assert torch.equal(getattr(g, k), getattr(w, k)), (q, k)
+
+
+@pytest.mark.parametrize("kind,N,M", [("sphere", 120000, 5), ("quant", 66000, 3), ("sphere", 210000, 4),
+                                      ("corr", 205000, 3)])
+def test_counts_not_published_are_made_by_the_block_that_waits(kind, N, M, monkeypatch):
+    """No look at an earlier block's count but the first (front copies of the spatial
+    path, splits of the key-sum order)."""
+    import torch
+    o, r = torch.from_numpy(_objs(kind, N, M, N)).cuda(), torch.eye(M, device="cuda") + 0.1
+    want = nsga3.select(o, r, N // 2, ctx=nsga3.Context(0))
+    monkeypatch.setenv("NSGA3_LOOK_POLLS", "0")
+    ctx = nsga3.Context(0)
+    for _ in range(3):
+        got = nsga3.select(o, r, N // 2, ctx=ctx)
+        assert got.info() == want.info() and got.info().status == 0
+        for k in ("rank", "dom_in", "dom_out", "selected"):
+            assert torch.equal(getattr(got, k), getattr(want, k)), k
