@@ -213,7 +213,8 @@ struct Rescore {
 };
 
 // S adjacent lanes share a point, each with every S-th reference, which are
-// staged in LDS; one lane a point (S = 1) reads them through scalar loads.
+// staged in LDS (one lane a point through scalar loads: 230 us instead of 152 at N =
+// 200k, M = 3, 2000 references, 47.8 and 46.7 at M = 5, 200).
 constexpr int kAssocFloats = 4096;
 
 template <int M, int S>
@@ -225,7 +226,7 @@ __global__ __launch_bounds__(kNormThreads) void k_associate(
     DevScalars *__restrict__ sc) {
     constexpr int kRefs = kAssocFloats / M / S * S;  // references staged at once
     __shared__ int32_t hist[2 * kLdsNicheRefs];
-    __shared__ __attribute__((aligned(16))) float lr[S > 1 ? kRefs * M : 1];
+    __shared__ __attribute__((aligned(16))) float lr[kRefs * M];
     if (sc->err) return;
     const int32_t l = sc->last_front;
     const int sub = S > 1 ? (int)threadIdx.x % S : 0;
@@ -240,7 +241,6 @@ __global__ __launch_bounds__(kNormThreads) void k_associate(
     for (int k = 0; k < M; ++k) { fp[k] = 0.0; y[k] = 0.0f; }
     if (mine) l1 = normalise_point<M>(objs + i * M, sc->z, sc->a, fp, y);
     auto stage = [&](int c0) {
-        if (S == 1) return;
         const int n = (H - c0 < kRefs ? H - c0 : kRefs) * M;
         __syncthreads();
         for (int q = threadIdx.x; q < n; q += kNormThreads) lr[q] = rhat32[(int64_t)c0 * M + q];
@@ -253,13 +253,14 @@ __global__ __launch_bounds__(kNormThreads) void k_associate(
         if (any) {
             int j = sub;
             for (; j + 3 * S < n; j += 4 * S) {
+                float s4[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-                    smax = fmaxf(smax, screen_dot<M>(y, S > 1 ? lr + (j + u * S) * M
-                                                              : rhat32 + (c0 + j + u) * M));
+                    s4[u] = screen_dot<M>(y, lr + (j + u * S) * M);
+                smax = fmaxf(smax, fmaxf(fmaxf(s4[0], s4[1]), fmaxf(s4[2], s4[3])));
             }
             for (; j < n; j += S)
-                smax = fmaxf(smax, screen_dot<M>(y, S > 1 ? lr + j * M : rhat32 + (c0 + j) * M));
+                smax = fmaxf(smax, screen_dot<M>(y, lr + j * M));
         }
     }
     for (int o = 1; o < S; o <<= 1) smax = fmaxf(smax, __shfl_xor(smax, o, 64));
@@ -269,14 +270,14 @@ __global__ __launch_bounds__(kNormThreads) void k_associate(
         if (H > kRefs) stage(c0);
         const int n = H - c0 < kRefs ? H - c0 : kRefs;
         if (any) {
-            for (int jb = 0; jb < n; jb += 4 * S) {
+            int jb = 0;
+            for (; jb + 4 * S <= n; jb += 4 * S) {  // (four in a row: their loads are one)
                 bool pass[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int j = jb + u * S + sub;
-                    const int jc = j < n ? j : n - 1;
-                    const float s = screen_dot<M>(y, S > 1 ? lr + jc * M : rhat32 + (c0 + jc) * M);
-                    pass[u] = mine && j < n && !(s < thr);
+                    const float s = screen_dot<M>(y, lr + j * M);
+                    pass[u] = mine && !(s < thr);
                 }
                 if (!ballot(pass[0] || pass[1] || pass[2] || pass[3])) continue;
 #pragma unroll
@@ -284,6 +285,12 @@ __global__ __launch_bounds__(kNormThreads) void k_associate(
                     R.add(pass[u], c0 + jb + u * S + sub);
                     if (R.full()) R.run(fp, rhat64);
                 }
+            }
+            for (; jb < n; jb += S) {
+                const int j = jb + sub, jc = j < n ? j : n - 1;
+                const float s = screen_dot<M>(y, lr + jc * M);
+                R.add(mine && j < n && !(s < thr), c0 + j);
+                if (R.full()) R.run(fp, rhat64);
             }
         }
     }
@@ -907,10 +914,14 @@ int normalize_partial_blocks(int64_t N) {
 
 // Lanes that share a point of the association: few points leave the chip idle
 // while each lane walks the references alone, many pay for every lane's own
-// normalisation.  1 / 4 / 16 lanes: N = 200, M = 3 14.7 / 7.9 / 6.8 us; 2503, 5
-// 34.4 / 13.9 / 9.2; 10007, 2 14.7 / 10.0 / 14.1; 20000, 3 16.0 / 13.6 / 25.6;
-// 50021, 4 21.9 / 22.7 / 46.9; 200000, 5 52 / 79 / 143.
-static int assoc_split(int64_t N) { return N <= 4096 ? 16 : N <= 32768 ? 4 : 1; }
+// normalisation, and many references are worth more lanes.  1 / 4 / 16 lanes, us
+// (M = 5): N = 3000, 100 references 14.6 / 8.2 / 7.0; 10000, 100 15.4 / 9.2 / 17.7, 500
+// 50.0 / 20.7 / 16.3; 20000, 100 15.9 / 15.3 / 30.4, 500 50.0 / 22.8 / 27.0; 50000, 100 19.8
+// / 28.1 / 68.3, 300 37.6 / 32.2 / 47.7; 100000, 500 59 / 63 / 81; 200000, 2000 236 / 275 / 370.
+static int assoc_split(int64_t N, int H) {
+    if (N <= 4096 || (N <= 16384 && H >= 512)) return 16;
+    return N <= 32768 || (N <= 65536 && H >= 256) ? 4 : 1;
+}
 
 hipError_t run_select_stage(const SelectViews &v, hipStream_t s) {
     const int64_t N = v.N;
@@ -932,7 +943,7 @@ hipError_t run_select_stage(const SelectViews &v, hipStream_t s) {
     const unsigned nbN = (unsigned)((N + 255) / 256);
     v.mark();
     const unsigned nbW = (unsigned)((N + 127) / 128);  // 32 points per wave, 4 waves per block
-    const int S = assoc_split(N);
+    const int S = assoc_split(N, v.H);
     const unsigned nbS = (unsigned)((N * S + kNormThreads - 1) / kNormThreads);
     switch (M) {
 #define NSGA3_ASSOC(m, q)                                                                           \

@@ -104,3 +104,21 @@ def test_small_orders(N, M):
     assert np.array_equal(res.rank.cpu().numpy(), oracle.ranks(f)[0])
     assert np.array_equal(res.dom_in.cpu().numpy(), din)
     assert np.array_equal(res.dom_out.cpu().numpy(), dout)
+
+
+@pytest.mark.parametrize("N,M,H", [(4096, 3, 1), (4097, 2, 511), (16384, 3, 512), (16385, 5, 513),
+                                   (32769, 3, 255), (32769, 4, 256), (65536, 2, 700), (65537, 3, 5000),
+                                   (40000, 10, 4097), (70000, 16, 300)])
+def test_association_lanes(N, M, H):
+    """Where another number of lanes shares a point, and references beyond one
+    staged chunk: niches and distances against float64 over all references."""
+    import torch
+    from tests.gpu_helpers import compare_full, gpu_select
+    rng = np.random.Generator(np.random.PCG64(N + H))
+    u = np.abs(rng.standard_normal((N, M)))
+    f = (u / np.linalg.norm(u, axis=1, keepdims=True) * (1 + 0.02 * rng.random((N, 1)))).astype(np.float32)
+    refs = (rng.random((H, M)) + 1e-3).astype(np.float32)
+    assert torch.cuda.is_available()
+    rep = compare_full(f, refs, N // 2, gpu_select(f, refs, N // 2))
+    rep.pop("near_ties")
+    assert not any(rep.values()), rep
