@@ -117,7 +117,8 @@ nsga3_status nsga3_reserve(nsga3_ctx *ctx, int64_t N_max, int32_t M_max, int32_t
 
 /* Bytes of workspace a call of this size needs at least (host-only query).  A
  * context without a cap, or with one that allows it, takes more where that makes
- * calls faster (masks of dominance pairs kept for the ranks). */
+ * calls faster (masks of dominance pairs kept for the ranks: 1.7 GB at
+ * N = 200,000, M = 5). */
 nsga3_status nsga3_workspace_size(int64_t N, int32_t M, int32_t H, size_t *bytes);
 
 /*
@@ -269,7 +270,8 @@ nsga3_status nsga3_rvea_select(nsga3_ctx *ctx, const float *objs, int64_t N, int
  * device's shapes (host queries only).  Every call on a device shares that
  * device's array: calls that overlap in time on one device (different
  * streams, or different host threads) race and give undefined results;
- * calls on one stream are ordered and safe.  Where the masks that nsga3_select
+ * calls on one stream are ordered and safe.  Nothing the call launches needs
+ * all its work-groups on the device at once.  Where the masks that nsga3_select
  * keeps do not fit the array as well, levels beyond the 24th front are peeled by
  * one work-group (no cooperative launch), so inputs with very many fronts are
  * slower than with nsga3_select.
@@ -376,9 +378,9 @@ nsga3_status nsga3_plan_stage_times(const nsga3_plan *plan, double *item_ms,
 
 /* Phases of one nsga3_select call, for nsga3_phase_times. */
 #define NSGA3_NUM_PHASES 6
-/*   0  keys, ideal point, presort by key sum            (Alg. S.5 first step; sort prerequisite)
+/*   0  keys, ideal point, order of the points           (Alg. S.5 first step; sort prerequisite)
  *   1  dominance counts over all pairs                  (Listing 1, Eq. (6)-(7))
- *   2  front peeling and last front                     (Eq. (8)-(9), Alg. S.3)
+ *   2  fronts and last front                            (Eq. (8)-(9), Alg. S.3)
  *   3  extreme points and intercepts                    (Alg. S.5)
  *   4  association and niche counts                     (Eq. (10)-(12))
  *   5  niche-preserving pick and output compaction      (Alg. S.1, Eq. (13)) */

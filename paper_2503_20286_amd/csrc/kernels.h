@@ -184,7 +184,6 @@ hipError_t run_rvea(const RveaViews &v, hipStream_t s);
 
 // ---- select.hip -----------------------------------------------------------
 size_t oneshot_temp_bytes(int64_t n);   // workspace temp needed by the one-shot niching
-// nsga3_info from the call's device scalars (K selections expected).
 // Indices of the set selection flags in ascending order, and the call's info
 // (may be null).
 void run_compact(const uint8_t *flag, int64_t N, int32_t *out, int64_t K, uint32_t *temp,

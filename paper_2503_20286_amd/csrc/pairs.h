@@ -17,12 +17,13 @@
 // as its unranked points have stored masks.  There the first fronts are taken
 // off whole: a pass for the degrees gives front 0 (nobody dominates it), the
 // others are copied together in order, the next pass over them gives front 1,
-// and so on; masks are stored in the last pass only, for what is left.
+// and so on, as long as a front holds a tenth of the points; masks are stored in
+// the last pass only, for what is left.
 //
 // Whole selections, key-sum order -> this path (with the stages after it as
-// they are now): N = 200k, M = 5 2.65 -> 1.35 ms, N = 100k, M = 10 0.95 -> 0.55 ms,
-// N = 50k, M = 4 0.74 -> 0.52 ms, N = 20k, M = 3 0.76 -> 0.38 ms, N = 10k, M = 2
-// 4.1 -> 0.69 ms, N = 200 0.24 -> 0.074 ms.
+// they are now): N = 200k, M = 5 2.65 -> 1.33 ms, N = 100k, M = 10 0.95 -> 0.55 ms,
+// N = 50k, M = 4 0.74 -> 0.52 ms, N = 20k, M = 3 0.76 -> 0.37 ms, N = 10k, M = 2
+// 4.1 -> 0.68 ms, N = 200 0.24 -> 0.075 ms.
 #pragma once
 
 #include "bitdom_wide.h"
@@ -30,7 +31,11 @@
 
 namespace nsga3 {
 
-constexpr int64_t kPairsMaxN = 204800;   // largest problem of this path
+// Largest problem of this path: the rank launch keeps the unranked set and its
+// work-group's rows in LDS, 158,160 of 163,840 B at this size, and the masks grow with
+// N * N.  One point more takes the key-sum order and about twice the time (M = 5:
+// 1.37 ms here, 2.70 there).
+constexpr int64_t kPairsMaxN = 204800;
 constexpr int kSplitterSample = 1024;   // keys sampled per objective for the cell splitters
 constexpr int kSplitterMaxBits = 6;     // cells per objective: at most 64
 constexpr int kCellMaxBits = 16;
